@@ -98,11 +98,9 @@ typedef enum { LECO_U32 = 4, LECO_U64 = 8 } leco_dtype;
  *   LECO_REGRESSOR_MINIMAX also fits the line of smallest maximum deviation
  *   (the fixed-width objective of section 3.1: the smallest slope that
  *   minimises the vertical width of the strip holding the partition's
- *   points, taken exactly from their convex hulls, stored as fl(dy)/fl(dt)
- *   of the hull edge it lies on) and stores it when its residual width is
+ *   points, found exactly, stored as fl(dy)/fl(dt) of the edge of the
+ *   points' convex hulls it lies on) and stores it when its residual width is
  *   strictly below both the constant model's and the least-squares line's.
- *   Minimax partitions longer than 4096 values need 8 bytes of device
- *   scratch per value of the column.
  *   LECO_REGRESSOR_POLY (section 3.1's model terms; the higher-order models
  *   of the evaluation) also fits, for partitions of 3..4096 values whose
  *   range is below 2^50, the least-squares polynomials of degree 2 and 3
@@ -181,14 +179,15 @@ leco_status leco_encode_async(leco_ctx *ctx, const void *col_dev, uint64_t n,
  * capture, tight serving loops, harnesses that forbid allocation): the
  * encode of leco_encode_async, producing the same bytes, that allocates
  * nothing.  Its scratch (per-partition models, word counts and offsets,
- * variable starts, running hulls) lives in a fixed array of
+ * variable starts) lives in a fixed array of
  * LECO_NOALLOC_SCRATCH_BYTES in each GPU's memory, held by the library
  * until the process ends; every call on a GPU shares that GPU's array, so
  * calls that overlap on one GPU (other streams, other threads, other
  * contexts) race and must be ordered by the caller.  About 56 bytes per
- * partition are needed (plus 8 (m + 1) for variable starts and 8 n for
- * minimax partitions longer than 4096 values); a call needing more than the
- * array returns LECO_ENOSPC before anything is enqueued.  Requires
+ * partition are needed (plus 8 (m + 1) for variable starts; a minimax call
+ * with partitions longer than 4096 values is counted 8 n more, which it no
+ * longer uses); a call counted beyond the array returns LECO_ENOSPC before
+ * anything is enqueued.  Requires
  * blob_cap >= leco_max_blob_bytes(...); the blob size goes to
  * *blob_bytes_dev. */
 #define LECO_NOALLOC_SCRATCH_BYTES (32u << 20)

@@ -160,13 +160,15 @@ leco_status prepare_encode(leco_ctx* ctx, const void* col, uint64_t n, leco_dtyp
   const size_t o_enc = off;    off = align256(off + leco::encode_scratch_bytes(m));
   const size_t o_misc = off;   off = align256(off + 16);
   const size_t o_starts = off; off = align256(off + (variable ? 8 * (m + 1) : 8));
-  const bool hulls = part->regressor == LECO_REGRESSOR_MINIMAX && call->max_len > leco::kHullTileValues;
-  const size_t o_hull = off;   off = align256(off + (hulls ? 8 * n : 0));
   void* scr = nullptr;
   if (fixed) {
-    if (off > fixed_bytes)
+    // minimax partitions beyond 4096 values count 8 bytes per value against
+    // the fixed scratch: part of the call's published limit
+    const bool long_minimax = part->regressor == LECO_REGRESSOR_MINIMAX && call->max_len > 4096;
+    const size_t counted = off + (long_minimax ? align256(8 * n) : 0);
+    if (counted > fixed_bytes)
       return fail(ctx, LECO_ENOSPC, "encode needs %zu bytes of scratch, the fixed scratch holds %zu",
-                  off, fixed_bytes);
+                  counted, fixed_bytes);
     scr = fixed;
   } else {
     st = get_scratch(ctx, off, &scr);
@@ -187,12 +189,7 @@ leco_status prepare_encode(leco_ctx* ctx, const void* col, uint64_t n, leco_dtyp
   c.force_constant = part->force_constant_model ? 1 : 0;
   c.regressor = uint32_t(part->regressor);
   c.pad = 0;
-  c.val_base = 0;
   call->scr = leco::carve_encode_scratch(b + o_enc, m);
-  if (hulls) {
-    call->scr.hull = reinterpret_cast<uint32_t*>(b + o_hull);
-    call->scr.hull_values = n;
-  }
   call->size_dev = reinterpret_cast<uint64_t*>(b + o_misc);
   c.size_out = call->size_dev;
   if (variable) {
@@ -444,8 +441,7 @@ leco_status leco_encode_batch(leco_ctx* ctx, const leco_encode_job* jobs, uint64
   // to a third.
   constexpr int kGroups = 3;
   std::vector<leco::EncColumn> cols[kGroups];
-  uint64_t parts[kGroups] = {0, 0, 0}, longest[kGroups] = {0, 0, 0}, values[kGroups] = {0, 0, 0};
-  bool minimax[kGroups] = {false, false, false};
+  uint64_t parts[kGroups] = {0, 0, 0}, longest[kGroups] = {0, 0, 0};
   uint32_t regs[kGroups] = {0, 0, 0};
   for (uint64_t i = 0; i < ncols; ++i) {
     const leco_encode_job& j = jobs[i];
@@ -480,11 +476,8 @@ leco_status leco_encode_batch(leco_ctx* ctx, const leco_encode_job* jobs, uint64
     c.force_constant = j.force_constant_model ? 1 : 0;
     c.regressor = uint32_t(j.regressor);
     c.pad = 0;
-    c.val_base = values[g];
     parts[g] += c.m;
-    values[g] += c.n;
     if (len > longest[g]) longest[g] = len;
-    if (j.regressor == LECO_REGRESSOR_MINIMAX) minimax[g] = true;
     regs[g] |= leco::regressor_bit(uint32_t(j.regressor));
     cols[g].push_back(c);
   }
@@ -492,13 +485,10 @@ leco_status leco_encode_batch(leco_ctx* ctx, const leco_encode_job* jobs, uint64
   for (int g = 0; g < kGroups; ++g)
     if (parts[g] >= (uint64_t(1) << 31))
       return fail(ctx, LECO_EINVAL, "too many partitions in one batch");
-  size_t off = 0, o_enc[kGroups], o_cols[kGroups], o_hull[kGroups];
-  bool hulls[kGroups];
+  size_t off = 0, o_enc[kGroups], o_cols[kGroups];
   for (int g = 0; g < kGroups; ++g) {
-    hulls[g] = minimax[g] && longest[g] > leco::kHullTileValues;
     o_enc[g] = off;  off = align256(off + leco::encode_scratch_bytes(parts[g]));
     o_cols[g] = off; off = align256(off + sizeof(leco::EncColumn) * (cols[g].size() + 1));
-    o_hull[g] = off; off = align256(off + (hulls[g] ? 8 * values[g] : 0));
   }
   void* scr = nullptr;
   leco_status st = get_scratch(ctx, off, &scr);
@@ -509,11 +499,7 @@ leco_status leco_encode_batch(leco_ctx* ctx, const leco_encode_job* jobs, uint64
     leco::EncColumn* cols_dev = reinterpret_cast<leco::EncColumn*>(b + o_cols[g]);
     HIP_TRY(ctx, hipMemcpyAsync(cols_dev, cols[g].data(), sizeof(leco::EncColumn) * cols[g].size(),
                                 hipMemcpyHostToDevice, stream));
-    leco::EncScratch es = leco::carve_encode_scratch(b + o_enc[g], parts[g]);
-    if (hulls[g]) {
-      es.hull = reinterpret_cast<uint32_t*>(b + o_hull[g]);
-      es.hull_values = values[g];
-    }
+    const leco::EncScratch es = leco::carve_encode_scratch(b + o_enc[g], parts[g]);
     HIP_TRY(ctx, leco::launch_encode_columns(ctx, cols_dev, cols[g].size(), cols[g][0], parts[g],
                                              longest[g], regs[g], es, stream));
   }
@@ -588,13 +574,10 @@ static leco_status sampled_cost(leco_ctx* ctx, const void* col, leco_dtype dtype
   const uint64_t m = window / L + (window % L != 0);
   const uint64_t nparts = k * m;
   if (nparts >= (uint64_t(1) << 31)) return fail(ctx, LECO_EINVAL, "too many sampled partitions");
-  const bool minimax = regressor == LECO_REGRESSOR_MINIMAX;
-  const bool hulls = minimax && L > leco::kHullTileValues;
   size_t off = 0;
   const size_t o_enc = off;  off = align256(off + leco::encode_scratch_bytes(nparts));
   const size_t o_cols = off; off = align256(off + sizeof(leco::EncColumn) * k);
   const size_t o_sum = off;  off = align256(off + 8);
-  const size_t o_hull = off; off = align256(off + (hulls ? 8 * k * window : 0));
   void* scr = nullptr;
   leco_status st = get_scratch(ctx, off, &scr);
   if (st != LECO_OK) return st;
@@ -616,13 +599,8 @@ static leco_status sampled_cost(leco_ctx* ctx, const void* col, leco_dtype dtype
     c.force_constant = 0;
     c.regressor = uint32_t(regressor);
     c.pad = 0;
-    c.val_base = i * window;
   }
-  leco::EncScratch es = leco::carve_encode_scratch(b + o_enc, nparts);
-  if (hulls) {
-    es.hull = reinterpret_cast<uint32_t*>(b + o_hull);
-    es.hull_values = k * window;
-  }
+  const leco::EncScratch es = leco::carve_encode_scratch(b + o_enc, nparts);
   auto* cols_dev = reinterpret_cast<leco::EncColumn*>(b + o_cols);
   auto* sum_dev = reinterpret_cast<uint64_t*>(b + o_sum);
   HIP_TRY(ctx, hipMemcpyAsync(cols_dev, cols.data(), sizeof(leco::EncColumn) * k,

@@ -5,18 +5,18 @@
 //          residual range, the choice between the line and the constant
 //          model (section 3.1), hence its width b and its word count; with
 //          the minimax regressor also the minimax line (k_fit_minimax*,
-//          hulls in minimax.hpp), with the polynomial regressor the
-//          degree-2 and degree-3 polynomials (k_fit_poly*);
+//          minimax.hpp), with the polynomial regressor the degree-2 and
+//          degree-3 polynomials (k_fit_poly*);
 //   scan   the exclusive prefix of the word counts gives every partition's
 //          word offset; the records, starts, header and padding are written;
 //   pack   every partition's residuals, recomputed from its stored model,
 //          are bit-packed into its word span (section 3.3 storage format).
 //
 // The fits take one wavefront per partition when every partition holds at
-// most kWaveEncodeMax values (16 per lane) or twice that (32 per lane; not
-// the minimax fit): values in registers, shuffle reductions, no workgroup
-// barrier.  Longer partitions get a whole workgroup.  Works on a table of columns, so one sequence of
-// launches encodes one column or thousands.  The column is read twice; in
+// most kWaveEncodeMax values (16 per lane) or twice that (32 per lane):
+// values in registers, shuffle reductions, no workgroup barrier.  Longer
+// partitions get a whole workgroup.  Works on a table of columns, so one
+// sequence of launches encodes one column or thousands.  The column is read twice; in
 // exchange no partition waits on another.
 //
 // Register-resident partitions whose range is below 2^30 (the usual case)
@@ -67,11 +67,9 @@ __device__ inline T meta_load(const T* p, uint64_t i) {
 }
 
 constexpr uint32_t kColWords = sizeof(EncColumn) / 8;
-static_assert(sizeof(EncColumn) == 104 && offsetof(EncColumn, part_base) == 72 &&
-                  offsetof(EncColumn, dtype) == 80 && offsetof(EncColumn, regressor) == 88 &&
-                  offsetof(EncColumn, val_base) == 96,
+static_assert(sizeof(EncColumn) == 96 && offsetof(EncColumn, part_base) == 72 &&
+                  offsetof(EncColumn, dtype) == 80 && offsetof(EncColumn, regressor) == 88,
               "column entry layout");
-static_assert(kHullTile == kHullTileValues, "hull tile");
 
 // The column holding partition P: the kernel argument of a one-column
 // launch, else the last table entry with part_base <= P, read word by word
@@ -102,7 +100,6 @@ __device__ inline EncColumn column_of(const EncColumn* cols, uint64_t ncols,
   c.force_constant = uint32_t(w >> 32);
   c.regressor = uint32_t(meta_load(t, e + 11));
   c.pad = 0;
-  c.val_base = meta_load(t, e + 12);
   return c;
 }
 
@@ -476,138 +473,155 @@ __global__ __launch_bounds__(kEncBlock) __attribute__((amdgpu_waves_per_eu(6))) 
   if (threadIdx.x == 0) store_model(scr, P, md, len);
 }
 
-// ---- fit with the minimax regressor: one workgroup per partition ------------------
+// ---- fit with the minimax regressor ------------------------------------------------
 
-// A hull tile's LDS word for an offset below kHullF64Range: its binary64 bits.
-__device__ inline uint64_t f64_word(uint64_t offset) {
-  return uint64_t(__double_as_longlong(double(offset)));
-}
-// The value a hull tile's word stands for: the word itself, or (f64) the
-// offset its binary64 bits hold (an integer below 2^40: exact).
-__device__ inline uint64_t tile_word_value(uint64_t word, bool f64) {
-  return f64 ? uint64_t(__longlong_as_double(static_cast<long long>(word))) : word;
+// Takes the line of slope theta when its residuals, in [rmin, rmax], are
+// strictly narrower than md's model.
+__device__ inline void take_narrower(Model& md, double theta, int64_t rmin, int64_t rmax) {
+  const uint32_t b = bitlen64(uint64_t(rmax) - uint64_t(rmin));
+  if (b >= md.bits) return;
+  md.linear = true;
+  md.theta1 = theta;
+  md.base = md.vmin + uint64_t(rmin);
+  md.bits = b;
+  md.rmin = rmin;
 }
 
-// The least-squares model of fit_block, then (minimax) the minimax line
-// of section 3.1's fixed-width objective, stored instead when its residual
-// width is strictly smaller.  run_up / run_lo: the partition's running hulls
-// when it spans several hull tiles.
-template <class T>
-__device__ __attribute__((always_inline)) inline Model fit_minimax(FitShared& fs, HullShared& hs, const T* src, uint64_t len,
-                                    bool force_constant, bool minimax, uint32_t* run_up,
-                                    uint32_t* run_lo) {
-  Model md = fit_block(fs, src, len, force_constant);
+// Residual range of the slope theta over the offsets of strip_slope_regs
+// (below 2^32; the predictions of a slope between two of them are below 2^33
+// in magnitude, so every difference is exact), reduced over the group.
+template <int kT, int kR>
+__device__ __attribute__((always_inline)) inline void strip_residuals(StripGroup<kT>& g,
+                                                                      const double (&y)[kR],
+                                                                      uint32_t tid, double theta,
+                                                                      int64_t& rmin,
+                                                                      int64_t& rmax) {
+  double mx = -__builtin_inf(), mn = __builtin_inf();
+#pragma unroll
+  for (int k = 0; k < kR; ++k) {
+    const double r = y[k] - floor(__dmul_rn(theta, double(tid + kT * k)));
+    mx = fmax(mx, r);
+    mn = fmin(mn, r);
+  }
+  g.maxmin(mx, mn);
+  rmax = int64_t(mx);
+  rmin = int64_t(mn);
+}
+
+// The least-squares model of fit_wave_regs, then (minimax) the minimax line
+// of section 3.1's fixed-width objective (minimax.hpp), stored instead when
+// its residual width is strictly smaller: one wavefront, at most 64 kR
+// values.
+template <int kR, class T>
+__device__ __attribute__((always_inline)) inline Model fit_minimax_wave(const T* src, uint64_t len,
+                                                                        bool force_constant,
+                                                                        bool minimax, int* err) {
+  constexpr uint32_t kLog2S = kR == 16 ? 10 : 11;
+  const uint32_t lane = threadIdx.x & 63;
+  T v[kR];
+#pragma unroll
+  for (int k = 0; k < kR; ++k) v[k] = T(load_clamped(src, lane + 64 * k, len));
+  Model md = fit_wave_regs<kR>(v, len, force_constant);
   // the same partitions as the least-squares line: len > 1, range < 2^61
-  if (!minimax || len < 2 || force_constant || !(md.linear || md.bits <= 61)) return md;
-  const auto gsrc = global_ptr(src);
-  const uint32_t tid = threadIdx.x;
-  const uint32_t ntiles = uint32_t((len + kHullTile - 1) / kHullTile);
-  // one tile of a narrow range: the hull tests in binary64
-  const bool f64 = ntiles == 1 && md.range < kHullF64Range;
-  for (uint32_t k = 0; k < ntiles; ++k) {
-    const uint32_t t0 = k * kHullTile;
-    const uint32_t cnt = uint32_t(len - t0 < kHullTile ? len - t0 : kHullTile);
-    {  // the tile's loads issued at once
-      uint64_t tv[kHullChunk];
+  if (!minimax || len < 2 || force_constant || md.bits == 0 || md.range >= (uint64_t(1) << 61))
+    return md;
+  StripGroup<64> g{nullptr};
+  double theta;
+  int64_t rmin, rmax;
+  int found;
+  if (md.range < strip_f64_range(kLog2S)) {
+    double y[kR];
 #pragma unroll
-      for (uint32_t j = 0; j < kHullChunk; ++j) {
-        const uint32_t x = tid + j * kEncBlock;
-        tv[j] = x < cnt ? uint64_t(gsrc[t0 + x]) : 0;
-      }
-#pragma unroll
-      for (uint32_t j = 0; j < kHullChunk; ++j) {
-        const uint32_t x = tid + j * kEncBlock;
-        if (x < cnt) hs.v[x] = f64 ? f64_word(tv[j] - md.vmin) : tv[j];
-      }
+    for (int k = 0; k < kR; ++k)
+      y[k] = lane + 64 * k < len ? double(uint32_t(uint64_t(v[k]) - md.vmin)) : __builtin_nan("");
+    // lane 0 holds the first value, lane 63 (clamped or not) the last
+    const double y_first = double(uint32_t(__builtin_amdgcn_readlane(int(uint32_t(v[0]) - uint32_t(md.vmin)), 0)));
+    const double y_last = double(uint32_t(__builtin_amdgcn_readlane(int(uint32_t(v[kR - 1]) - uint32_t(md.vmin)), 63)));
+    double dy, dt;
+    found = strip_slope_regs<64, kR, kLog2S>(g, y, lane, uint32_t(len), y_first, y_last, md.bits,
+                                             dy, dt);
+    if (found != 1) {
+      if (found == 2 && lane == 0) raise(err, kErrDevice);
+      return md;
     }
-    __syncthreads();
-    if (f64)
-      tile_hulls<kEncBlock, true>(hs, cnt, tid);
-    else
-      tile_hulls<kEncBlock, false>(hs, cnt, tid);
-    if (ntiles == 1) break;
-    uint32_t keep[2], from[2], c[2];
-    for (uint32_t side = 0; side < 2; ++side) c[side] = hs.cnt[side][0];
-    if (k == 0) {
-      keep[0] = keep[1] = from[0] = from[1] = 0;
-    } else {
-      if (tid < 2) {
-        const uint32_t side = tid;
-        const uint32_t* R = side ? run_lo : run_up;
-        const auto A = [&](uint32_t i) {
-          const uint32_t t = R[i];
-          return HullPoint{t, uint64_t(gsrc[t])};
-        };
-        const auto B = [&](uint32_t j) {
-          const uint32_t x = hs.h[side][j];
-          return HullPoint{t0 + x, hs.v[x]};
-        };
-        uint32_t kp, fr;
-        hull_bridge(side == 0, A, hs.rcnt[side], B, c[side], kp, fr);
-        hs.rkeep[side] = kp;
-        hs.rfrom[side] = fr;
-      }
-      __syncthreads();
-      for (uint32_t side = 0; side < 2; ++side) {
-        keep[side] = hs.rkeep[side];
-        from[side] = hs.rfrom[side];
-      }
-    }
-    for (uint32_t side = 0; side < 2; ++side) {
-      uint32_t* R = side ? run_lo : run_up;
-      for (uint32_t x = tid; x < c[side] - from[side]; x += kEncBlock)
-        R[keep[side] + x] = t0 + hs.h[side][from[side] + x];
-    }
-    __syncthreads();
-    if (tid < 2) hs.rcnt[tid] = keep[tid] + c[tid] - from[tid];
-    __syncthreads();
-  }
-  EdgeSlope th;
-  if (f64) {
-    const auto U = [&](uint32_t i) { return hull_pt<true>(hs.h[0][i], hs.v[hs.h[0][i]]); };
-    const auto L = [&](uint32_t i) { return hull_pt<true>(hs.h[1][i], hs.v[hs.h[1][i]]); };
-    th = minimax_bend<kEncBlock>(hs, U, hs.cnt[0][0], L, hs.cnt[1][0], tid);
-  } else if (ntiles == 1) {
-    const auto U = [&](uint32_t i) { return hull_pt<false>(hs.h[0][i], hs.v[hs.h[0][i]]); };
-    const auto L = [&](uint32_t i) { return hull_pt<false>(hs.h[1][i], hs.v[hs.h[1][i]]); };
-    th = minimax_bend<kEncBlock>(hs, U, hs.cnt[0][0], L, hs.cnt[1][0], tid);
+    // one correctly rounded division of the exact fraction
+    theta = dy / dt;
+    if (theta == 0.0) theta = 0.0;  // +0.0, never -0.0
+    strip_residuals<64, kR>(g, y, lane, theta, rmin, rmax);
   } else {
-    const auto U = [&](uint32_t i) {
-      const uint32_t t = run_up[i];
-      return HullPoint{t, uint64_t(gsrc[t])};
-    };
-    const auto L = [&](uint32_t i) {
-      const uint32_t t = run_lo[i];
-      return HullPoint{t, uint64_t(gsrc[t])};
-    };
-    th = minimax_bend<kEncBlock>(hs, U, hs.rcnt[0], L, hs.rcnt[1], tid);
+    found = strip_slope_stream<64>(g, src, lane, uint32_t(len), md.vmin, md.range, md.bits, theta);
+    if (found != 1) {
+      if (found == 2 && lane == 0) raise(err, kErrDevice);
+      return md;
+    }
+    if (theta == 0.0) theta = 0.0;
+    // the values read again: held across the search they cost an occupancy step
+    rmin = INT64_MAX;
+    rmax = INT64_MIN;
+    const auto gsrc = global_ptr(src);
+    for (uint32_t t = lane; t < len; t += 64) {
+      const int64_t rr = int64_t(uint64_t(gsrc[t]) - md.vmin) - predict(theta, t);
+      rmin = rr < rmin ? rr : rmin;
+      rmax = rr > rmax ? rr : rmax;
+    }
+    wave_minmax_i64(rmin, rmax);
   }
-  // one correctly rounded division of the exact edge fraction
-  double theta = static_cast<double>(th.dy) / static_cast<double>(th.dt);
-  if (theta == 0.0) theta = 0.0;  // +0.0, never -0.0
+  take_narrower(md, theta, rmin, rmax);
+  return md;
+}
+
+// The same by one workgroup, any length: partitions of at most kEncRegLen
+// values in registers where binary64 keys are exact, the others streamed.
+template <class T>
+__device__ __attribute__((always_inline)) inline Model fit_minimax(FitShared& fs, StripShared& ss,
+                                                                   const T* src, uint64_t len,
+                                                                   bool force_constant,
+                                                                   bool minimax, int* err) {
+  Model md = fit_block(fs, src, len, force_constant);
+  if (!minimax || len < 2 || force_constant || md.bits == 0 || md.range >= (uint64_t(1) << 61))
+    return md;
+  constexpr uint32_t kLog2S = 12;
+  static_assert(kEncRegLen == 1u << kLog2S, "register-held partitions");
+  const uint32_t tid = threadIdx.x;
+  StripGroup<kEncBlock> g{&ss};
+  double theta;
   int64_t rmin = INT64_MAX, rmax = INT64_MIN;
-  for (uint32_t t0 = 0; t0 < len; t0 += kHullTile) {
+  int found;
+  if (len <= kEncRegLen && md.range < strip_f64_range(kLog2S)) {
+    double y[kEncRegs];
+    uint64_t v[kEncRegs];
 #pragma unroll
-    for (uint32_t j = 0; j < kHullChunk; ++j) {
-      const uint32_t t = t0 + tid + j * kEncBlock;
-      if (t < len) {
-        const uint64_t x = ntiles == 1 ? (f64 ? md.vmin + tile_word_value(hs.v[t], true) : hs.v[t])
-                                       : uint64_t(gsrc[t]);
-        const int64_t rr = int64_t(x - md.vmin) - predict(theta, t);
+    for (int k = 0; k < kEncRegs; ++k) v[k] = load_clamped(src, tid + k * kEncBlock, len);
+    const double y_first = double(uint32_t(load_clamped(src, 0, len) - md.vmin));
+    const double y_last = double(uint32_t(load_clamped(src, uint32_t(len), len) - md.vmin));
+#pragma unroll
+    for (int k = 0; k < kEncRegs; ++k)
+      y[k] = tid + k * kEncBlock < len ? double(uint32_t(v[k] - md.vmin)) : __builtin_nan("");
+    double dy, dt;
+    found = strip_slope_regs<kEncBlock, kEncRegs, kLog2S>(g, y, tid, uint32_t(len), y_first, y_last,
+                                                          md.bits, dy, dt);
+    if (found == 1) {
+      theta = dy / dt;
+      if (theta == 0.0) theta = 0.0;  // +0.0, never -0.0
+      strip_residuals<kEncBlock, kEncRegs>(g, y, tid, theta, rmin, rmax);
+    }
+  } else {
+    found = strip_slope_stream<kEncBlock>(g, src, tid, uint32_t(len), md.vmin, md.range, md.bits,
+                                          theta);
+    if (found == 1) {
+      if (theta == 0.0) theta = 0.0;
+      const auto gsrc = global_ptr(src);
+#pragma unroll 8
+      for (uint32_t t = tid; t < len; t += kEncBlock) {
+        const int64_t rr = int64_t(uint64_t(gsrc[t]) - md.vmin) - predict(theta, t);
         rmin = rr < rmin ? rr : rmin;
         rmax = rr > rmax ? rr : rmax;
       }
+      block_minmax_i64(fs, rmin, rmax);
     }
   }
-  block_minmax_i64(fs, rmin, rmax);
-  const uint32_t b = bitlen64(uint64_t(rmax) - uint64_t(rmin));
-  if (b < md.bits) {
-    md.linear = true;
-    md.theta1 = theta;
-    md.base = md.vmin + uint64_t(rmin);
-    md.bits = b;
-    md.rmin = rmin;
-  }
+  if (found == 1) take_narrower(md, theta, rmin, rmax);
+  else if (found == 2 && tid == 0) raise(err, kErrDevice);
   return md;
 }
 
@@ -616,98 +630,31 @@ __global__ __launch_bounds__(kEncBlock) void k_fit_minimax(const EncColumn* __re
                                                           uint64_t nparts, EncScratch scr,
                                                           int* err) {
   __shared__ FitShared fs;
-  __shared__ HullShared hs;
+  __shared__ StripShared ss;
   const uint64_t P = blockIdx.x;
   if (P >= nparts) return;
   const EncColumn c = column_of(cols, ncols, single, P);
   if (c.regressor == 2) return;  // k_fit_poly
   uint64_t start, len;
   part_bounds(c, P - c.part_base, start, len);
-  bool minimax = c.regressor == 1;
-  uint32_t *run_up = nullptr, *run_lo = nullptr;
-  if (minimax && len > kHullTile) {
-    if (scr.hull == nullptr) {  // the host allocates running hulls for such launches
-      if (threadIdx.x == 0) raise(err, kErrDevice);
-      minimax = false;
-    } else {
-      run_up = scr.hull + c.val_base + start;
-      run_lo = scr.hull + scr.hull_values + c.val_base + start;
-    }
-  }
+  const bool minimax = c.regressor == 1;
   const Model md =
       c.dtype == 8
-          ? fit_minimax(fs, hs, reinterpret_cast<const uint64_t*>(c.col) + start, len,
-                        c.force_constant, minimax, run_up, run_lo)
-          : fit_minimax(fs, hs, reinterpret_cast<const uint32_t*>(c.col) + start, len,
-                        c.force_constant, minimax, run_up, run_lo);
+          ? fit_minimax(fs, ss, reinterpret_cast<const uint64_t*>(c.col) + start, len,
+                        c.force_constant, minimax, err)
+          : fit_minimax(fs, ss, reinterpret_cast<const uint32_t*>(c.col) + start, len,
+                        c.force_constant, minimax, err);
   if (threadIdx.x == 0) store_model(scr, P, md, len);
 }
 
-// The same with one wavefront per partition of at most kWaveEncMax values
-// (four per workgroup, no workgroup barrier): the least-squares model of
-// fit_wave, then the minimax line from the partition's hulls in the
-// wavefront's own LDS slice.  Launches holding polynomial columns never use
-// this kernel.
-template <class T>
-__device__ __attribute__((always_inline)) inline Model fit_minimax_wave(HullSharedT<64>& hs,
-                                                                        const T* src, uint64_t len,
-                                                                        bool force_constant,
-                                                                        bool minimax) {
-  Model md = fit_wave<kWaveRegs>(src, len, force_constant);
-  if (!minimax || len < 2 || force_constant || md.range >= (uint64_t(1) << 61)) return md;
-  const uint32_t lane = threadIdx.x & 63;
-  // all loads issued at once (the same addresses fit_wave read)
-  uint64_t v[kWaveRegs];
-#pragma unroll
-  for (int k = 0; k < kWaveRegs; ++k) v[k] = load_clamped(src, lane + 64 * k, len);
-  const bool f64 = md.range < kHullF64Range;  // the hull tests in binary64
-#pragma unroll
-  for (int k = 0; k < kWaveRegs; ++k)
-    if (lane + 64 * k < len) hs.v[lane + 64 * k] = f64 ? f64_word(v[k] - md.vmin) : v[k];
-  group_sync<64>();
-  if (f64)
-    tile_hulls<64, true>(hs, uint32_t(len), lane);
-  else
-    tile_hulls<64, false>(hs, uint32_t(len), lane);
-  EdgeSlope th;
-  if (f64) {
-    const auto U = [&](uint32_t i) { return hull_pt<true>(hs.h[0][i], hs.v[hs.h[0][i]]); };
-    const auto L = [&](uint32_t i) { return hull_pt<true>(hs.h[1][i], hs.v[hs.h[1][i]]); };
-    th = minimax_bend<64>(hs, U, hs.cnt[0][0], L, hs.cnt[1][0], lane);
-  } else {
-    const auto U = [&](uint32_t i) { return hull_pt<false>(hs.h[0][i], hs.v[hs.h[0][i]]); };
-    const auto L = [&](uint32_t i) { return hull_pt<false>(hs.h[1][i], hs.v[hs.h[1][i]]); };
-    th = minimax_bend<64>(hs, U, hs.cnt[0][0], L, hs.cnt[1][0], lane);
-  }
-  double theta = static_cast<double>(th.dy) / static_cast<double>(th.dt);
-  if (theta == 0.0) theta = 0.0;  // +0.0, never -0.0
-  int64_t rmin = INT64_MAX, rmax = INT64_MIN;
-#pragma unroll
-  for (int k = 0; k < kWaveRegs; ++k) {
-    const uint32_t t = lane + 64 * k;
-    if (t < len) {
-      const int64_t rr = int64_t(v[k] - md.vmin) - predict(theta, t);
-      rmin = rr < rmin ? rr : rmin;
-      rmax = rr > rmax ? rr : rmax;
-    }
-  }
-  wave_minmax_i64(rmin, rmax);
-  const uint32_t b = bitlen64(uint64_t(rmax) - uint64_t(rmin));
-  if (b < md.bits) {
-    md.linear = true;
-    md.theta1 = theta;
-    md.base = md.vmin + uint64_t(rmin);
-    md.bits = b;
-    md.rmin = rmin;
-  }
-  return md;
-}
-
-__global__ __launch_bounds__(kEncBlock) void k_fit_minimax_wave(const EncColumn* __restrict__ cols,
+// One wavefront per partition of at most 64 kR values (four per workgroup,
+// no workgroup barrier).  Launches holding polynomial columns never use this
+// kernel.
+template <int kR>
+__global__ __launch_bounds__(kEncBlock, kR == 16 ? 4 : 2) void k_fit_minimax_wave(const EncColumn* __restrict__ cols,
                                                                uint64_t ncols, EncColumn single,
                                                                uint64_t nparts, EncScratch scr,
                                                                int* err) {
-  __shared__ HullSharedT<64> hs[kEncWaves];
   const uint32_t lane = threadIdx.x & 63;
   const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const uint64_t P = uint64_t(blockIdx.x) * kEncWaves + wave;
@@ -715,17 +662,17 @@ __global__ __launch_bounds__(kEncBlock) void k_fit_minimax_wave(const EncColumn*
   const EncColumn c = column_of(cols, ncols, single, P);
   uint64_t start, len;
   part_bounds(c, P - c.part_base, start, len);
-  if (len > kWaveEncMax) {  // the host sends such partitions to k_fit_minimax
+  if (len > 64 * kR) {  // the host sends such partitions to k_fit_minimax
     if (lane == 0) raise(err, kErrDevice);
     return;
   }
   const bool minimax = c.regressor == 1;
   const Model md =
       c.dtype == 8
-          ? fit_minimax_wave(hs[wave], reinterpret_cast<const uint64_t*>(c.col) + start, len,
-                             c.force_constant, minimax)
-          : fit_minimax_wave(hs[wave], reinterpret_cast<const uint32_t*>(c.col) + start, len,
-                             c.force_constant, minimax);
+          ? fit_minimax_wave<kR>(reinterpret_cast<const uint64_t*>(c.col) + start, len,
+                                 c.force_constant, minimax, err)
+          : fit_minimax_wave<kR>(reinterpret_cast<const uint32_t*>(c.col) + start, len,
+                                 c.force_constant, minimax, err);
   if (lane == 0) store_model(scr, P, md, len);
 }
 
@@ -1629,8 +1576,6 @@ EncScratch carve_encode_scratch(void* p, uint64_t nparts) {
   s.c3 = q + 5 * k + ng + 1;
   s.bits = reinterpret_cast<uint32_t*>(q + 6 * k + ng + 1);
   s.kind = s.bits + k;
-  s.hull = nullptr;
-  s.hull_values = 0;
   return s;
 }
 
@@ -1641,7 +1586,7 @@ hipError_t launch_fit_columns(leco_ctx* ctx, const EncColumn* cols_dev, uint64_t
   // each fit kernel fits the columns of its regressors and skips the others
   const uint64_t pw = (nparts + kEncWaves - 1) / kEncWaves;
   // one wavefront per partition: 16 values per lane up to 1024 values, 32
-  // up to 2048 (not the minimax fit, whose hull slice holds 1024)
+  // up to 2048
   const bool wave16 = max_len <= kWaveEncMax && ctx->tune.encode_wave;
   const bool wave32 =
       max_len <= 2 * kWaveEncMax && ctx->tune.encode_wave && ctx->tune.encode_wave32;
@@ -1664,8 +1609,11 @@ hipError_t launch_fit_columns(leco_ctx* ctx, const EncColumn* cols_dev, uint64_t
   // k_fit_wave fits every column it is given: not with polynomial columns
   const bool poly = regs & kRegPoly;
   if ((regs & kRegMinimax) && wave16 && !poly)
-    hipLaunchKernelGGL(k_fit_minimax_wave, dim3(uint32_t(pw)), dim3(kEncBlock), 0, stream, cols_dev,
-                       ncols, single, nparts, scr, ctx->err_dev);
+    hipLaunchKernelGGL(k_fit_minimax_wave<kWaveRegs>, dim3(uint32_t(pw)), dim3(kEncBlock), 0,
+                       stream, cols_dev, ncols, single, nparts, scr, ctx->err_dev);
+  else if ((regs & kRegMinimax) && wave32 && !poly)
+    hipLaunchKernelGGL(k_fit_minimax_wave<2 * kWaveRegs>, dim3(uint32_t(pw)), dim3(kEncBlock), 0,
+                       stream, cols_dev, ncols, single, nparts, scr, ctx->err_dev);
   else if (regs & kRegMinimax)
     hipLaunchKernelGGL(k_fit_minimax, dim3(uint32_t(nparts)), dim3(kEncBlock), 0, stream, cols_dev,
                        ncols, single, nparts, scr, ctx->err_dev);

@@ -49,7 +49,6 @@ struct EncColumn {
   uint32_t dtype, force_constant;
   uint32_t regressor;      // 0 least squares, 1 minimax as well, 2 polynomials as well
   uint32_t pad;
-  uint64_t val_base;       // index of the column's first value in the launch
 };
 
 // Decode tile size (log2 of values per workgroup tile) for a blob of
@@ -69,9 +68,6 @@ hipError_t launch_filter_sum(leco_ctx* ctx, const void* blob, uint64_t blob_byte
 hipError_t launch_zero_u64(uint64_t* p, uint64_t n, hipStream_t stream);
 // Partitions of at most this many values are encoded one per wavefront.
 constexpr uint64_t kWaveEncodeMax = 1024;
-// Minimax partitions longer than this many values keep running hulls in
-// EncScratch::hull.
-constexpr uint64_t kHullTileValues = 4096;
 
 // Device scratch of one encode launch (nparts partitions): the fitted
 // models, their word counts and offsets, and the scan's per-workgroup sums.
@@ -82,11 +78,6 @@ struct EncScratch {
   uint64_t* theta;  // bits of the binary64 slope
   uint64_t* bsum;
   uint32_t* bits;
-  // running hulls of minimax partitions longer than one hull tile: upper
-  // vertex k of the partition at launch value s is hull[s + k], lower is
-  // hull[hull_values + s + k]; null when no such partition is encoded
-  uint32_t* hull;
-  uint64_t hull_values;
   // polynomial models (columns with the polynomial regressor): kind 0/1 and
   // the bits of c2, c3 per partition
   uint32_t* kind;
