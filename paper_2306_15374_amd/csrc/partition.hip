@@ -29,10 +29,18 @@
 // rounds of alternating parity, every chunk whose left neighbour's end
 // state changed is walked again from it until it keeps a boundary its
 // recorded run also kept.  A run of merges spanning c chunks takes about c
-// rounds.  Within a run, 64 steps are sized at once (one per lane), and a
-// long current partition is represented by the convex hulls of its points,
-// which bound its residuals exactly for any slope, so a step costs the
-// values it adds rather than the whole union.
+// rounds.  Within a run, 256 steps are sized at once (one per thread of a
+// workgroup), and a long current partition is represented by the convex hulls
+// of its points, so a step costs neither the union's values nor those it adds.
+//
+// What bounds a column whose runs are long (a noisy polyline of 1e7 values:
+// partitions of two values merged into partitions of up to 370,000) is the
+// latency of the batches along its longest run: 256 steps in about 8 us.  With
+// one wavefront, 64 steps a batch, every added value broadcast to all lanes
+// and the hulls kept by a serial chain it was 60 us for 64, and short chunks
+// re-walked most of the column in every round: 512 -> 64 ms (in order: hulls
+// by parallel peeling, unions sized by bounds of two hulls, 4096-boundary
+// chunks and a workgroup per walker), sorted normal samples 30 -> 16 ms.
 #include <math.h>
 
 #include <utility>
@@ -41,6 +49,7 @@
 #include "fit.hpp"
 #include "internal.hpp"
 #include "leco_dev.hpp"
+#include "minimax.hpp"
 
 namespace leco {
 
@@ -527,33 +536,71 @@ struct FitShared {
   double theta1;
 };
 
+// Value summary of a range of the column: smallest and largest value, and
+// the sums of v and of t * v (t counted from the range's first position)
+// modulo 2^128: the least-squares slope needs no more (N is the same for
+// shifted values, and exact because |N| < 2^121).
+struct RangeSum {
+  uint64_t vmin, vmax;
+  U128 sy, sty;
+};
+
 // Bytes that the partition v[s, e) costs in a variable-length blob: its
 // 32-byte record, its 8-byte start and its residual words, with the model
-// the encoder would choose.  Called by every thread of the workgroup.
+// the encoder would choose; sum receives its summary.  Called by every
+// thread of the workgroup.  Each pass issues the loads of kLongLoads values
+// per thread together (a loop of one load per step waited for memory every
+// 256 values).
+constexpr uint32_t kLongLoads = 8;
+
 __device__ uint64_t range_cost(FitShared& sh, const uint8_t* col, uint32_t dtype, uint64_t s,
-                               uint64_t e) {
+                               uint64_t e, RangeSum& sum) {
   const uint64_t len = e - s;
   const uint8_t* src = col + s * dtype;
   uint64_t vmin = ~uint64_t(0), vmax = 0;
   U128 sv{0, 0}, stv{0, 0};
-  for (uint64_t t = threadIdx.x; t < len; t += kEncBlock) {
-    const uint64_t x = load_value(src, dtype, t);
-    vmin = x < vmin ? x : vmin;
-    vmax = x > vmax ? x : vmax;
-    sv = add128(sv, U128{x, 0});
-    stv = add128(stv, mul64x64(t, x));
+  for (uint64_t t0 = threadIdx.x; t0 < len; t0 += kEncBlock * kLongLoads) {
+    uint64_t x[kLongLoads];
+#pragma unroll
+    for (uint32_t k = 0; k < kLongLoads; ++k) {
+      const uint64_t t = t0 + k * kEncBlock;
+      x[k] = load_value(src, dtype, t < len ? t : len - 1);
+    }
+#pragma unroll
+    for (uint32_t k = 0; k < kLongLoads; ++k) {
+      const uint64_t t = t0 + k * kEncBlock;
+      if (t < len) {
+        vmin = x[k] < vmin ? x[k] : vmin;
+        vmax = x[k] > vmax ? x[k] : vmax;
+        sv = add128(sv, U128{x[k], 0});
+        stv = add128(stv, mul64x64(t, x[k]));
+      }
+    }
   }
   block_minmax_u64(sh, vmin, vmax);
+  block_sum_u128x2(sh, sv, stv);
+  sum = RangeSum{vmin, vmax, sv, stv};
   const uint64_t range = vmax - vmin;
   Model md{vmin, vmin, 0.0, bitlen64(range), false, 0, range};
   if (len > 1 && range < (uint64_t(1) << 61)) {
-    block_sum_u128x2(sh, sv, stv);
     const double th = block_slope(sh, len, sv, stv);
     int64_t rmin = INT64_MAX, rmax = INT64_MIN;
-    for (uint64_t t = threadIdx.x; t < len; t += kEncBlock) {
-      const int64_t rr = int64_t(load_value(src, dtype, t) - vmin) - predict(th, uint32_t(t));
-      rmin = rr < rmin ? rr : rmin;
-      rmax = rr > rmax ? rr : rmax;
+    for (uint64_t t0 = threadIdx.x; t0 < len; t0 += kEncBlock * kLongLoads) {
+      uint64_t x[kLongLoads];
+#pragma unroll
+      for (uint32_t k = 0; k < kLongLoads; ++k) {
+        const uint64_t t = t0 + k * kEncBlock;
+        x[k] = load_value(src, dtype, t < len ? t : len - 1);
+      }
+#pragma unroll
+      for (uint32_t k = 0; k < kLongLoads; ++k) {
+        const uint64_t t = t0 + k * kEncBlock;
+        if (t < len) {
+          const int64_t rr = int64_t(x[k] - vmin) - predict(th, uint32_t(t));
+          rmin = rr < rmin ? rr : rmin;
+          rmax = rr > rmax ? rr : rmax;
+        }
+      }
     }
     block_minmax_i64(sh, rmin, rmax);
     choose_model(md, th, rmin, rmax);
@@ -567,7 +614,8 @@ constexpr uint64_t kLaneRangeMax = 32;
 constexpr uint64_t kWaveRangeMax = 8192;
 
 // range_cost computed by one lane alone.
-__device__ uint64_t range_cost_lane(const uint8_t* col, uint32_t dtype, uint64_t s, uint64_t e) {
+__device__ uint64_t range_cost_lane(const uint8_t* col, uint32_t dtype, uint64_t s, uint64_t e,
+                                    RangeSum& sum) {
   const uint64_t len = e - s;
   const uint8_t* src = col + s * dtype;
   uint64_t vmin = ~uint64_t(0), vmax = 0;
@@ -579,6 +627,7 @@ __device__ uint64_t range_cost_lane(const uint8_t* col, uint32_t dtype, uint64_t
     sv = add128(sv, U128{x, 0});
     stv = add128(stv, mul64x64(t, x));
   }
+  sum = RangeSum{vmin, vmax, sv, stv};
   const uint64_t range = vmax - vmin;
   Model md{vmin, vmin, 0.0, bitlen64(range), false, 0, range};
   if (len > 1 && range < (uint64_t(1) << 61)) {
@@ -602,13 +651,19 @@ __global__ __launch_bounds__(kEncBlock) void k_costs_short(const uint8_t* __rest
                                                            uint64_t count, uint32_t span,
                                                            uint64_t max_len,
                                                            const uint8_t* __restrict__ dirty,
-                                                           uint64_t* __restrict__ out) {
+                                                           uint64_t* __restrict__ out,
+                                                           RangeSum* __restrict__ sums) {
   const uint64_t stride = uint64_t(gridDim.x) * blockDim.x;
   for (uint64_t j = uint64_t(blockIdx.x) * blockDim.x + threadIdx.x; j < count; j += stride) {
     if (dirty && !dirty[j]) continue;
     const uint64_t s = starts[j], e = starts[j + span];
-    if (e - s > max_len) out[j] = kNoMerge;
-    else if (e - s <= kLaneRangeMax) out[j] = range_cost_lane(col, dtype, s, e);
+    if (e - s > max_len) {
+      out[j] = kNoMerge;
+    } else if (e - s <= kLaneRangeMax) {
+      RangeSum sum;
+      out[j] = range_cost_lane(col, dtype, s, e, sum);
+      if (sums) sums[j] = sum;
+    }
   }
 }
 
@@ -623,7 +678,7 @@ __global__ __launch_bounds__(kEncBlock) void k_costs_short(const uint8_t* __rest
 constexpr int kCostRegs = 8;
 
 template <class T>
-__device__ uint64_t range_cost_wave_regs(const T* src, uint64_t len) {
+__device__ uint64_t range_cost_wave_regs(const T* src, uint64_t len, RangeSum& sum) {
   const uint32_t lane = threadIdx.x & 63;
   const auto g = global_ptr(src);
   uint64_t x[kCostRegs];
@@ -645,10 +700,11 @@ __device__ uint64_t range_cost_wave_regs(const T* src, uint64_t len) {
     }
   }
   wave_minmax_u64(vmin, vmax);
+  wave_sum_u128x2(sv, stv);
+  sum = RangeSum{vmin, vmax, sv, stv};
   const uint64_t range = vmax - vmin;
   Model md{vmin, vmin, 0.0, bitlen64(range), false, 0, range};
   if (len > 1 && range < (uint64_t(1) << 61)) {
-    wave_sum_u128x2(sv, stv);
     const double th = ls_slope(len, sv, stv);
     int64_t rmin = INT64_MAX, rmax = INT64_MIN;
 #pragma unroll
@@ -666,13 +722,14 @@ __device__ uint64_t range_cost_wave_regs(const T* src, uint64_t len) {
   return kRecordBytes + 8 + 8 * ((len * md.bits + 63) >> 6);
 }
 
-__device__ uint64_t range_cost_wave(const uint8_t* col, uint32_t dtype, uint64_t s, uint64_t e) {
+__device__ uint64_t range_cost_wave(const uint8_t* col, uint32_t dtype, uint64_t s, uint64_t e,
+                                    RangeSum& sum) {
   const uint32_t lane = threadIdx.x & 63;
   const uint64_t len = e - s;
   const uint8_t* src = col + s * dtype;
   if (len <= 64u * kCostRegs)
-    return dtype == 8 ? range_cost_wave_regs(reinterpret_cast<const uint64_t*>(src), len)
-                      : range_cost_wave_regs(reinterpret_cast<const uint32_t*>(src), len);
+    return dtype == 8 ? range_cost_wave_regs(reinterpret_cast<const uint64_t*>(src), len, sum)
+                      : range_cost_wave_regs(reinterpret_cast<const uint32_t*>(src), len, sum);
   // longer ranges in blocks of 64 kCostRegs values, each block's loads
   // issued together (indices clamped, the extra lanes masked)
   uint64_t vmin = ~uint64_t(0), vmax = 0;
@@ -696,10 +753,11 @@ __device__ uint64_t range_cost_wave(const uint8_t* col, uint32_t dtype, uint64_t
     }
   }
   wave_minmax_u64(vmin, vmax);
+  wave_sum_u128x2(sv, stv);
+  sum = RangeSum{vmin, vmax, sv, stv};
   const uint64_t range = vmax - vmin;
   Model md{vmin, vmin, 0.0, bitlen64(range), false, 0, range};
   if (len > 1 && range < (uint64_t(1) << 61)) {
-    wave_sum_u128x2(sv, stv);
     const double th = ls_slope(len, sv, stv);
     int64_t rmin = INT64_MAX, rmax = INT64_MIN;
     for (uint64_t t0 = 0; t0 < len; t0 += 64u * kCostRegs) {
@@ -748,7 +806,7 @@ __device__ inline bool cost_candidate(const uint64_t* starts, uint64_t count, ui
 
 // out[j] = cost of v[starts[j], starts[j + span]) for j < count (only
 // where dirty[j], if dirty is given), or kNoMerge when that is longer than
-// max_len: one wavefront per range of more than kLaneRangeMax and at most
+// max_len, and sums[j] (if given) its summary: one wavefront per range of more than kLaneRangeMax and at most
 // kWaveRangeMax values; the others are left to k_costs_short and
 // k_costs_long.
 __global__ __launch_bounds__(kEncBlock) void k_costs(const uint8_t* __restrict__ col,
@@ -757,7 +815,8 @@ __global__ __launch_bounds__(kEncBlock) void k_costs(const uint8_t* __restrict__
                                                      uint64_t count, uint32_t span,
                                                      uint64_t max_len,
                                                      const uint8_t* __restrict__ dirty,
-                                                     uint64_t* __restrict__ out, uint32_t chunk) {
+                                                     uint64_t* __restrict__ out,
+                                                     RangeSum* __restrict__ sums, uint32_t chunk) {
   const uint32_t lane = threadIdx.x & 63;
   const uint64_t waves = uint64_t(gridDim.x) * kEncWaves;
   for (uint64_t j0 = (uint64_t(blockIdx.x) * kEncWaves + (threadIdx.x >> 6)) * chunk;
@@ -769,8 +828,12 @@ __global__ __launch_bounds__(kEncBlock) void k_costs(const uint8_t* __restrict__
     while (todo) {
       const uint64_t j = j0 + uint64_t(__ffsll(static_cast<long long>(todo)) - 1);
       todo &= todo - 1;
-      const uint64_t c = range_cost_wave(col, dtype, starts[j], starts[j + span]);
-      if (lane == 0) out[j] = c;
+      RangeSum sum;
+      const uint64_t c = range_cost_wave(col, dtype, starts[j], starts[j + span], sum);
+      if (lane == 0) {
+        out[j] = c;
+        if (sums) sums[j] = sum;
+      }
     }
   }
 }
@@ -783,6 +846,7 @@ __global__ __launch_bounds__(kEncBlock) void k_costs_long(const uint8_t* __restr
                                                           uint64_t max_len,
                                                           const uint8_t* __restrict__ dirty,
                                                           uint64_t* __restrict__ out,
+                                                          RangeSum* __restrict__ sums,
                                                           uint32_t chunk) {
   __shared__ FitShared sh;
   __shared__ uint64_t todo_sh;
@@ -800,8 +864,12 @@ __global__ __launch_bounds__(kEncBlock) void k_costs_long(const uint8_t* __restr
     while (todo) {
       const uint64_t j = j0 + uint64_t(__ffsll(static_cast<long long>(todo)) - 1);
       todo &= todo - 1;
-      const uint64_t c = range_cost(sh, col, dtype, starts[j], starts[j + span]);
-      if (threadIdx.x == 0) out[j] = c;
+      RangeSum sum;
+      const uint64_t c = range_cost(sh, col, dtype, starts[j], starts[j + span], sum);
+      if (threadIdx.x == 0) {
+        out[j] = c;
+        if (sums) sums[j] = sum;
+      }
     }
     __syncthreads();  // todo_sh is rewritten by the next chunk
   }
@@ -821,9 +889,6 @@ __global__ __launch_bounds__(kEncBlock) void k_costs_long(const uint8_t* __restr
 // The pass keeps a bitmap of kept boundaries (bit 0 always set); the
 // partitions that absorbed others are sized once the pass is done.
 
-constexpr uint32_t kMergeChunkLog2 = 8;  // boundaries per speculative chunk
-constexpr uint64_t kMergeChunk = uint64_t(1) << kMergeChunkLog2;
-
 __device__ inline uint64_t shfl_up64(uint64_t x, int d) {
   return uint64_t(__shfl_up(static_cast<unsigned long long>(x), d, 64));
 }
@@ -834,15 +899,6 @@ __device__ inline uint64_t readlane64(uint64_t x, uint32_t k) {
   const uint32_t hi = uint32_t(__builtin_amdgcn_readlane(int(uint32_t(x >> 32)), int(k)));
   return (uint64_t(hi) << 32) | lo;
 }
-
-// Value summary of a range of the column: smallest and largest value, and
-// the sums of v and of t * v (t counted from the range's first position)
-// modulo 2^128: the least-squares slope needs no more (N is the same for
-// shifted values, and exact because |N| < 2^121).
-struct RangeSum {
-  uint64_t vmin, vmax;
-  U128 sy, sty;
-};
 
 // The summary of [x, z) from those of [x, y) and [y, z).
 __device__ inline RangeSum join(const RangeSum& a, const RangeSum& b, uint64_t a_len) {
@@ -867,32 +923,55 @@ struct MergeState {
 // so is the exact residual v_t - floor(theta1 * t), the ceiling of that real
 // number.  The encoder's residual takes the binary64 product, whose floor
 // exceeds the exact one by 1 exactly when the product rounds up onto an
-// integer (merge_walk checks for that).  A long run of merges then sizes
-// each union from the hulls and the values it adds, not from all its values.
+// integer (hull_ranges checks for that).  A long run of merges then sizes
+// each union from the hulls, not from its values.
 constexpr uint32_t kHullMax = 64;              // vertices per hull
-constexpr uint64_t kHullBuildMin = 256;        // shorter partitions are scanned whole
-constexpr uint64_t kHullBuildMax = 16384;      // values a hull is first built from
-constexpr uint64_t kHullAppendMax = 8192;      // values one step may append
-constexpr uint64_t kHullNewMax = 4096;         // new values a batch sizes by scanning
+constexpr uint64_t kHullBuildMin = 128;        // shorter partitions are scanned whole
+constexpr uint64_t kHullBuildNow = 2048;       // longer ones get hulls after kSoloMerges merges
+constexpr uint32_t kSoloMerges = 8;            // (a build costs about what 16 whole scans do)
+constexpr uint64_t kBatchNew = 1024;           // values a batch may add
+constexpr uint64_t kSoloMin = 256;             // longer neighbours: sized alone without hulls
+constexpr uint64_t kHullAppendMax = 8192;      // and longer than this with them
+constexpr uint64_t kDeadScanMax = 16384;       // longest partition a batch scans whole without hulls
+constexpr uint64_t kWide = uint64_t(1) << 61;  // value spread beyond which no line is fitted
 enum : uint32_t { kHullNone = 0, kHullValid = 1, kHullDead = 2 };
 
-struct ChainHull {  // hull 0: upper, hull 1: lower
-  uint32_t nu, nl, state, pad;
-  uint32_t t[2][kHullMax];
-  uint64_t x[2][kHullMax];
+struct ChainHull {  // side 0: upper, side 1: lower
+  uint32_t n[2], state, pad;
+  uint32_t t[2][kHullMax + 1];  // one entry of padding for the searches
+  uint64_t x[2][kHullMax + 1];
 };
 
-// A wavefront's LDS: the hulls and a window of values with a 16-value halo
-// on either side.
-constexpr uint32_t kHalo = 16;
-struct HullLds {
-  ChainHull h;
-  uint64_t stage[64 + 2 * kHalo];
+constexpr uint32_t kWalk = 256;                // threads of a walker, steps of a batch
+constexpr uint32_t kWalkWaves = kWalk / 64;
+constexpr uint32_t kHalo = 16;                 // farthest chord end of the first filter
+constexpr uint32_t kPeelCap = 640;             // points of a hull under construction
+constexpr uint32_t kStageVals = 1024;          // values staged with a window, when no more
+static_assert(kWalk == uint32_t(kEncBlock), "workgroup reductions");
+
+// A walker's LDS (one workgroup): the current partition's hulls and those of
+// the batch's longest union, the point lists they are built from, and the
+// sizes, summaries and values of the next kWalk partitions, loaded together
+// so that a batch waits for memory once per window.
+struct WalkLds {
+  ChainHull h[2];
+  uint32_t lt[2][2][kPeelCap];
+  uint64_t lx[2][2][kPeelCap];
+  uint64_t s[kWalk + 1], cost[kWalk], size[kWalk];
+  RangeSum psum[kWalk];
+  uint64_t vals[kStageVals];
+  double scan[kWalk];
+  RangeSum wave_sum[kWalkWaves];
+  uint64_t mask[3][kWalkWaves];
+  uint32_t count[2][kWalkWaves];  // survivors of each wavefront's block, per side
+  uint32_t n[2], cur[2];
+  StripShared strip;
+  uint64_t red[kEncWaves][4];     // workgroup reductions of fit.hpp
 };
 
-// The hulls' counts and state, identical in every lane of the wavefront.
+// The hulls' counts and state, identical in every thread of the walker.
 struct HullRegs {
-  uint32_t nu, nl, state;
+  uint32_t n[2], state;
 };
 
 __device__ inline void wave_lds_order() {
@@ -900,8 +979,12 @@ __device__ inline void wave_lds_order() {
   __builtin_amdgcn_wave_barrier();
 }
 
+__device__ inline uint32_t lanes_below(uint64_t mask) {
+  return __builtin_amdgcn_mbcnt_hi(uint32_t(mask >> 32), __builtin_amdgcn_mbcnt_lo(uint32_t(mask), 0));
+}
+
 // Sign of (b - a) x (c - a) for points with ta < tb < tc whose values lie
-// within 2^61 of each other.  kW = 64: within 2^43, so that with t < 2^20
+// within 2^61 of each other.  kW = 64: within 2^42, so that with t <= 2^20
 // each product fits in 64 bits; kW = 32: within 2^31, so that each factor
 // fits in 32 bits as well (one 32 x 32 -> 64 multiply).
 template <int kW = 128>
@@ -922,140 +1005,214 @@ __device__ inline int turn(uint32_t ta, uint64_t xa, uint32_t tb, uint64_t xb, u
   return l > r ? 1 : (l < r ? -1 : 0);
 }
 
-// Appends the points [u0, u1) of the partition beginning at column position
-// sa to both hulls; too many vertices mark them dead.  Each lane first tests
-// its point against chords through points of [0, u1) at distances 1..16 on
-// either side: a point on or below such a chord is no upper-hull vertex of
-// any set holding both ends, one on or above it no lower-hull vertex.  The
-// survivors then go through the monotone chain in order, lane 0 keeping the
-// upper hull and lane 1 the lower one side by side, each with its two last
-// vertices in registers.  Called by a whole wavefront, uniform arguments.
+// Drops points from the list of `side` (n points in buffer cur) until it is
+// a convex chain, by one wavefront.  A point on or below (upper hull; on or
+// above, lower) the chord of two others of the list on either side of it is
+// no vertex; a round tests every point against its neighbours 1, 2 and 4
+// places away at once, and a list that a round leaves alone has only strict
+// turns: it is the hull.  About five rounds on noise.
 template <int kW>
-__device__ inline void hull_append_t(const uint8_t* __restrict__ col, uint32_t dtype, uint64_t sa,
-                                     uint64_t u0, uint64_t u1, HullLds& w, HullRegs& hr) {
+__device__ __attribute__((always_inline)) inline void peel(WalkLds& w, uint32_t side, uint32_t& n,
+                                                           uint32_t& cur) {
   const uint32_t lane = threadIdx.x & 63;
-  const uint8_t* src = col + sa * dtype;
-  ChainHull& h = w.h;
-  const uint32_t side = lane & 1;  // lanes 0 and 1: the hull they keep
-  uint32_t n = side ? hr.nl : hr.nu;
-  uint32_t t1 = 0, t2 = 0;  // last and second-last vertex
-  uint64_t x1 = 0, x2 = 0;
-  if (lane < 2) {
-    if (n >= 1) { t1 = h.t[side][n - 1]; x1 = h.x[side][n - 1]; }
-    if (n >= 2) { t2 = h.t[side][n - 2]; x2 = h.x[side][n - 2]; }
-  }
-  bool over = false;
-  for (uint64_t b = u0; b < u1; b += 64) {
-    // positions b - kHalo .. b + 63 + kHalo that lie in [0, u1), staged once
-    for (uint32_t i = lane; i < 64 + 2 * kHalo; i += 64) {
-      if (b + i >= kHalo && b + i - kHalo < u1) w.stage[i] = load_value(src, dtype, b + i - kHalo);
+  while (n > 2) {
+    const uint32_t* T = w.lt[side][cur];
+    const uint64_t* X = w.lx[side][cur];
+    uint32_t* T2 = w.lt[side][cur ^ 1];
+    uint64_t* X2 = w.lx[side][cur ^ 1];
+    uint32_t out = 0;
+    for (uint32_t i0 = 0; i0 < n; i0 += 64) {
+      const uint32_t i = i0 + lane;
+      bool stays = i < n;
+      const uint32_t ic = stays ? i : n - 1;
+      // every neighbour loaded at once, out of range ones as the point itself
+      uint32_t ta[3], tc[3];
+      uint64_t xa[3], xc[3];
+      const uint32_t t = T[ic];
+      const uint64_t x = X[ic];
+#pragma unroll
+      for (uint32_t q = 0; q < 3; ++q) {
+        const uint32_t d = 1u << q;
+        const bool in = ic >= d && ic + d < n;
+        const uint32_t ia = in ? ic - d : ic, io = in ? ic + d : ic;
+        ta[q] = T[ia];
+        xa[q] = X[ia];
+        tc[q] = T[io];
+        xc[q] = X[io];
+      }
+#pragma unroll
+      for (uint32_t q = 0; q < 3; ++q) {
+        const int tr = turn<kW>(ta[q], xa[q], t, x, tc[q], xc[q]);
+        if (ta[q] != t && (side ? tr <= 0 : tr >= 0)) stays = false;
+      }
+      const uint64_t mask = __ballot(stays);
+      if (stays) {
+        const uint32_t o = out + lanes_below(mask);
+        T2[o] = t;
+        X2[o] = x;
+      }
+      out += uint32_t(__popcll(mask));
     }
     wave_lds_order();
-    const uint64_t t = b + lane;
-    const bool in = t < u1;
-    const uint64_t x = w.stage[kHalo + lane];  // used only where in
-    bool cu = in, cl = in;
-#pragma unroll
-    for (uint32_t ia = 0; ia < 5; ++ia) {
-      const uint32_t a = 1u << ia;
-      if (!in || t < a) break;
-      const uint64_t xa = w.stage[kHalo + lane - a];
-#pragma unroll
-      for (uint32_t ic = 0; ic < 5; ++ic) {
-        const uint32_t c = 1u << ic;
-        if (t + c >= u1) break;
-        const int tr = turn<kW>(0, xa, a, x, a + c, w.stage[kHalo + lane + c]);
-        if (tr >= 0) cu = false;
-        if (tr <= 0) cl = false;
-      }
-    }
-    wave_lds_order();  // every read of the window precedes the next block's
-    const uint64_t mu = __ballot(cu), ml = __ballot(cl);
-    uint64_t todo = mu | ml;
-    while (todo) {
-      const uint32_t q = uint32_t(__ffsll(static_cast<long long>(todo)) - 1);
-      todo &= todo - 1;
-      const uint64_t xq = readlane64(x, q);
-      const uint32_t tq = uint32_t(b + q);
-      const bool mine = lane < 2 && (((side ? ml : mu) >> q) & 1);
-      if (mine && !over) {
-        while (n >= 2) {
-          const int tr = turn<kW>(t2, x2, t1, x1, tq, xq);
-          if (side ? tr > 0 : tr < 0) break;  // a strict turn keeps the last vertex
-          --n;
-          t1 = t2;
-          x1 = x2;
-          if (n >= 2) {
-            t2 = h.t[side][n - 2];
-            x2 = h.x[side][n - 2];
-          }
-        }
-        if (n == kHullMax) {
-          over = true;
-        } else {
-          h.t[side][n] = tq;
-          h.x[side][n] = xq;
-          ++n;
-          t2 = t1;
-          x2 = x1;
-          t1 = tq;
-          x1 = xq;
-        }
-      }
-    }
-    if (__ballot(over)) break;
+    cur ^= 1;
+    if (out == n) break;
+    n = out;
   }
-  const uint32_t nu = uint32_t(__builtin_amdgcn_readlane(int(n), 0));
-  const uint32_t nl = uint32_t(__builtin_amdgcn_readlane(int(n), 1));
-  hr = __ballot(over) ? HullRegs{0, 0, kHullDead} : HullRegs{nu, nl, kHullValid};
-  wave_lds_order();  // the vertices are read by every lane next
 }
 
-// Values spread below 2^31 take the 32-bit turn test, below 2^43 the 64-bit one.
-__device__ inline void hull_append(const uint8_t* __restrict__ col, uint32_t dtype, uint64_t sa,
-                                   uint64_t u0, uint64_t u1, uint64_t spread, HullLds& w,
-                                   HullRegs& hr) {
-  if (spread < (uint64_t(1) << 31))
-    hull_append_t<32>(col, dtype, sa, u0, u1, w, hr);
-  else if (spread < (uint64_t(1) << 43))
-    hull_append_t<64>(col, dtype, sa, u0, u1, w, hr);
-  else
-    hull_append_t<128>(col, dtype, sa, u0, u1, w, hr);
+// Hull h[to] = hull h[from] (counts in hr; empty when hr is not valid) with
+// the points [u0, u1) of the partition beginning at column position sa
+// added, all later than its own.  read(t) is the value at position t < u1.
+// Each wavefront takes a block of 64 points and tests them against chords of
+// points at equal distances 1, 2 .. 16 on either side (about a quarter
+// stay); wavefronts 0 and 1 peel the upper and the lower list.  Returns the
+// counts; kHullDead when a hull has over kHullMax vertices.  Called by the
+// whole workgroup.
+template <int kW, class Read>
+__device__ __attribute__((always_inline)) inline HullRegs hull_extend_t(WalkLds& w, uint32_t from,
+                                                                        uint32_t to,
+                                                                        const HullRegs& hr,
+                                                                        uint64_t u0, uint64_t u1,
+                                                                        const Read& read) {
+  const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  uint32_t n[2] = {0, 0}, cur[2] = {0, 0};
+  if (hr.state == kHullValid) {
+#pragma unroll
+    for (uint32_t side = 0; side < 2; ++side) {
+      n[side] = hr.n[side];
+      if (threadIdx.x < n[side]) {
+        w.lt[side][0][threadIdx.x] = w.h[from].t[side][threadIdx.x];
+        w.lx[side][0][threadIdx.x] = w.h[from].x[side][threadIdx.x];
+      }
+    }
+  }
+  bool dead = false;
+  for (uint64_t b0 = u0; b0 < u1; b0 += kWalk) {
+    const uint64_t t = b0 + threadIdx.x;
+    const bool in = t < u1;
+    const uint64_t tc = in ? t : u1 - 1;
+    const uint64_t x = read(tc);
+    // all chord ends loaded at once, out of range ones as the point itself
+    uint64_t xa[5], xb[5];
+#pragma unroll
+    for (uint32_t q = 0; q < 5; ++q) {
+      const uint32_t d = 1u << q;
+      const bool both = tc >= d && tc + d < u1;
+      xa[q] = read(both ? tc - d : tc);
+      xb[q] = read(both ? tc + d : tc);
+    }
+    bool up = in, low = in;
+#pragma unroll
+    for (uint32_t q = 0; q < 5; ++q) {
+      const uint32_t d = 1u << q;
+      const int tr = turn<kW>(0, xa[q], d, x, 2 * d, xb[q]);
+      const bool both = tc >= d && tc + d < u1;
+      if (both && tr >= 0) up = false;
+      if (both && tr <= 0) low = false;
+    }
+    const uint64_t mu = __ballot(up), ml = __ballot(low);
+    if (lane == 0) {
+      w.count[0][wave] = uint32_t(__popcll(mu));
+      w.count[1][wave] = uint32_t(__popcll(ml));
+    }
+    __syncthreads();
+    uint32_t before[2] = {0, 0}, total[2] = {0, 0};
+#pragma unroll
+    for (uint32_t v = 0; v < kWalkWaves; ++v) {
+#pragma unroll
+      for (uint32_t side = 0; side < 2; ++side) {
+        const uint32_t c = w.count[side][v];
+        if (v < wave) before[side] += c;
+        total[side] += c;
+      }
+    }
+    if (up) {
+      const uint32_t o = n[0] + before[0] + lanes_below(mu);
+      w.lt[0][cur[0]][o] = uint32_t(t);
+      w.lx[0][cur[0]][o] = x;
+    }
+    if (low) {
+      const uint32_t o = n[1] + before[1] + lanes_below(ml);
+      w.lt[1][cur[1]][o] = uint32_t(t);
+      w.lx[1][cur[1]][o] = x;
+    }
+    n[0] += total[0];
+    n[1] += total[1];
+    __syncthreads();
+    // peeled at the end, and whenever the next blocks might not fit
+    if (b0 + kWalk >= u1 || n[0] > kPeelCap - kWalk || n[1] > kPeelCap - kWalk) {
+      if (wave < 2) {
+        uint32_t c = wave ? n[1] : n[0], buf = wave ? cur[1] : cur[0];
+        peel<kW>(w, wave, c, buf);
+        if (lane == 0) {
+          w.n[wave] = c;
+          w.cur[wave] = buf;
+        }
+      }
+      __syncthreads();
+#pragma unroll
+      for (uint32_t side = 0; side < 2; ++side) {
+        n[side] = w.n[side];
+        cur[side] = w.cur[side];
+      }
+      dead = n[0] > kPeelCap - kWalk || n[1] > kPeelCap - kWalk;
+      if (dead) break;
+    }
+  }
+  __syncthreads();  // every thread has read w.n
+  if (dead || n[0] > kHullMax || n[1] > kHullMax) return HullRegs{{0, 0}, kHullDead};
+#pragma unroll
+  for (uint32_t side = 0; side < 2; ++side) {
+    if (threadIdx.x < n[side]) {
+      w.h[to].t[side][threadIdx.x] = w.lt[side][cur[side]][threadIdx.x];
+      w.h[to].x[side][threadIdx.x] = w.lx[side][cur[side]][threadIdx.x];
+    }
+  }
+  __syncthreads();  // the vertices are read by every thread next
+  return HullRegs{{n[0], n[1]}, kHullValid};
+}
+
+// Values spread below 2^31 take the 32-bit turn test, below 2^42 the 64-bit one.
+template <class Read>
+__device__ __attribute__((always_inline)) inline HullRegs hull_extend(
+    WalkLds& w, uint32_t from, uint32_t to, const HullRegs& hr, uint64_t u0, uint64_t u1,
+    uint64_t spread, const Read& read) {
+  if (spread < (uint64_t(1) << 31)) return hull_extend_t<32>(w, from, to, hr, u0, u1, read);
+  if (spread < (uint64_t(1) << 42)) return hull_extend_t<64>(w, from, to, hr, u0, u1, read);
+  return hull_extend_t<128>(w, from, to, hr, u0, u1, read);
 }
 
 __device__ inline void hull_store(ChainHull* __restrict__ g, const ChainHull& h, const HullRegs& hr) {
-  const uint32_t lane = threadIdx.x & 63;
+  const uint32_t i = threadIdx.x;
   if (hr.state == kHullValid) {
-    if (lane < hr.nu) {
-      g->t[0][lane] = h.t[0][lane];
-      g->x[0][lane] = h.x[0][lane];
-    }
-    if (lane < hr.nl) {
-      g->t[1][lane] = h.t[1][lane];
-      g->x[1][lane] = h.x[1][lane];
+#pragma unroll
+    for (uint32_t side = 0; side < 2; ++side) {
+      if (i < hr.n[side]) {
+        g->t[side][i] = h.t[side][i];
+        g->x[side][i] = h.x[side][i];
+      }
     }
   }
-  if (lane == 0) {
-    g->nu = hr.nu;
-    g->nl = hr.nl;
+  if (i == 0) {
+    g->n[0] = hr.n[0];
+    g->n[1] = hr.n[1];
     g->state = hr.state;
   }
 }
 
 __device__ inline HullRegs hull_load(const ChainHull* __restrict__ g, ChainHull& h) {
-  const uint32_t lane = threadIdx.x & 63;
-  HullRegs hr{g->nu, g->nl, g->state};
+  const uint32_t i = threadIdx.x;
+  const HullRegs hr{{g->n[0], g->n[1]}, g->state};
   if (hr.state == kHullValid) {
-    if (lane < hr.nu) {
-      h.t[0][lane] = g->t[0][lane];
-      h.x[0][lane] = g->x[0][lane];
-    }
-    if (lane < hr.nl) {
-      h.t[1][lane] = g->t[1][lane];
-      h.x[1][lane] = g->x[1][lane];
+#pragma unroll
+    for (uint32_t side = 0; side < 2; ++side) {
+      if (i < hr.n[side]) {
+        h.t[side][i] = g->t[side][i];
+        h.x[side][i] = g->x[side][i];
+      }
     }
   }
-  wave_lds_order();
+  __syncthreads();
   return hr;
 }
 
@@ -1073,39 +1230,176 @@ __device__ inline int64_t vertex_residual(double th, uint32_t t, uint64_t x, uin
   return int64_t(x - vmin) - int64_t(fp) + (up ? 1 : 0);
 }
 
-__device__ inline void set_bits(unsigned long long* bits, uint64_t k, uint64_t mask) {
-  const uint64_t w = k >> 6, off = k & 63;
-  atomicOr(bits + w, static_cast<unsigned long long>(mask << off));
-  if (off && (mask >> (64 - off))) atomicOr(bits + w + 1, static_cast<unsigned long long>(mask >> (64 - off)));
+// Bounds of the largest and of the smallest residual the encoder would have
+// over the points of a hull, for this thread's slope.
+struct HullRange {
+  int64_t max_lo, max_hi, min_lo, min_hi;
+  __device__ uint32_t bits_lo() const {
+    return max_lo > min_hi ? bitlen64(uint64_t(max_lo) - uint64_t(min_hi)) : 0;
+  }
+  __device__ uint32_t bits_hi() const { return bitlen64(uint64_t(max_hi) - uint64_t(min_lo)); }
+  __device__ bool exact() const { return max_lo == max_hi && min_lo == min_hi; }
+};
+
+// The vertex of largest v - th t of an upper hull is the first whose next
+// edge is no steeper than th (a lower hull's smallest: no flatter), found by
+// binary search, the four searches side by side.  An edge (dt, dx) is
+// compared with th exactly: th dt = p + e with e the product's rounding
+// error, and dx - p is exact wherever it is as small as e.  Hulls 0 and 1 of
+// w.h have n0 and n1 vertices; pmax bounds every |product|, below 2^31.
+__device__ __attribute__((always_inline)) inline void hull_ranges(
+    const WalkLds& w, const uint32_t (&n0)[2], const uint32_t (&n1)[2], double th, double pmax,
+    uint64_t vmin, HullRange (&out)[2]) {
+  uint32_t lo[4] = {0, 0, 0, 0};
+  uint32_t hi[4] = {n0[0] - 1, n0[1] - 1, n1[0] - 1, n1[1] - 1};
+  const uint32_t most = max(max(hi[0], hi[1]), max(hi[2], hi[3]));
+  for (uint32_t span = most; span > 0; span >>= 1) {  // uniform: ends with every search done
+#pragma unroll
+    for (uint32_t q = 0; q < 4; ++q) {
+      const ChainHull& h = w.h[q >> 1];
+      const uint32_t side = q & 1, mid = (lo[q] + hi[q]) >> 1;
+      const uint32_t dt = h.t[side][mid + 1] - h.t[side][mid];
+      const int64_t dx = int64_t(h.x[side][mid + 1] - h.x[side][mid]);
+      const double p = __dmul_rn(th, double(dt));
+      const double e = __fma_rn(th, double(dt), -p);
+      const double d = double(dx) - p;
+      const bool right = side ? d < e : d > e;
+      if (lo[q] < hi[q]) {
+        if (right)
+          lo[q] = mid + 1;
+        else
+          hi[q] = mid;
+      }
+    }
+  }
+  // The exact residuals' largest, R, is the upper vertex's and the smallest,
+  // Q, the lower vertex's.  The encoder's largest is R when that product
+  // does not round up, else R or R - 1.  Its smallest is Q - 1 when the lower
+  // vertex's product rounds up; else Q unless another value reaching Q rounds
+  // up, which needs a product within half an ulp of pmax under an integer,
+  // where the vertex's own gap is at least as small (margin: two ulps of
+  // pmax, at least 2^-48 against the gap's own rounding).
+  const double margin = pmax >= 0x1p-3 ? fmax(ldexp(1.0, ilogb(pmax) - 51), 0x1p-48) : 0x1p-48;
+#pragma unroll
+  for (uint32_t b = 0; b < 2; ++b) {
+    const ChainHull& h = w.h[b];
+    const uint32_t iu = lo[2 * b], il = lo[2 * b + 1];
+    bool up, q_up;
+    double gap, q_gap;
+    const int64_t R = vertex_residual(th, h.t[0][iu], h.x[0][iu], vmin, up, gap);
+    const int64_t Q = vertex_residual(th, h.t[1][il], h.x[1][il], vmin, q_up, q_gap);
+    out[b].max_hi = R;
+    out[b].max_lo = up ? R - 1 : R;
+    out[b].min_hi = q_up ? Q - 1 : Q;
+    out[b].min_lo = q_up || q_gap < margin ? Q - 1 : Q;
+  }
 }
 
-__device__ inline void clear_bit(unsigned long long* bits, uint64_t k) {
-  atomicAnd(bits + (k >> 6), ~(1ull << (k & 63)));
+// Sets (clears) bits [k, k + f) of a bitmap, f <= kWalk: thread i takes the
+// i-th word that the run touches.
+__device__ inline void set_run(unsigned long long* bits, uint64_t k, uint64_t f) {
+  const uint64_t w = (k >> 6) + threadIdx.x;
+  if (f == 0 || w > (k + f - 1) >> 6) return;
+  const uint64_t lo = w << 6 < k ? k & 63 : 0;
+  const uint64_t end = k + f - (w << 6);
+  const uint64_t mask = (end >= 64 ? ~0ull : (1ull << end) - 1) & ~((1ull << lo) - 1);
+  atomicOr(bits + w, static_cast<unsigned long long>(mask));
+}
+
+__device__ inline void clear_run(unsigned long long* bits, uint64_t k, uint64_t f) {
+  const uint64_t w = (k >> 6) + threadIdx.x;
+  if (f == 0 || w > (k + f - 1) >> 6) return;
+  const uint64_t lo = w << 6 < k ? k & 63 : 0;
+  const uint64_t end = k + f - (w << 6);
+  const uint64_t mask = (end >= 64 ? ~0ull : (1ull << end) - 1) & ~((1ull << lo) - 1);
+  atomicAnd(bits + w, ~static_cast<unsigned long long>(mask));
+}
+
+// Residual range of v[0, len) of `src` for one slope, by the workgroup.
+__device__ __attribute__((always_inline)) inline void range_scan(
+    WalkLds& w, StripGroup<kEncBlock>& g, const uint8_t* src, uint32_t dtype, uint64_t len,
+    uint64_t vmin, uint64_t range, double th, int64_t& rmin, int64_t& rmax) {
+  constexpr uint32_t kR = 8;
+  rmin = INT64_MAX;
+  rmax = INT64_MIN;
+  // offsets and predictions below 2^50: differences exact in binary64
+  if (range < (uint64_t(1) << 32) && __dmul_rn(fabs(th), double(len)) < 0x1p50) {
+    double mx = -__builtin_inf(), mn = __builtin_inf();
+    for (uint64_t t0 = threadIdx.x; t0 < len; t0 += kWalk * kR) {
+      uint64_t x[kR];
+#pragma unroll
+      for (uint32_t k = 0; k < kR; ++k) {
+        const uint64_t t = t0 + kWalk * k;
+        x[k] = load_value(src, dtype, t < len ? t : len - 1);
+      }
+#pragma unroll
+      for (uint32_t k = 0; k < kR; ++k) {
+        const uint64_t t = t0 + kWalk * k;
+        const double tt = double(uint32_t(t < len ? t : len - 1));
+        const double r = double(uint32_t(x[k] - vmin)) - floor(__dmul_rn(th, tt));
+        mx = fmax(mx, r);
+        mn = fmin(mn, r);
+      }
+    }
+    g.maxmin(mx, mn);
+    rmin = int64_t(mn);
+    rmax = int64_t(mx);
+    return;
+  }
+  for (uint64_t t = threadIdx.x; t < len; t += kWalk) {
+    const int64_t rr = int64_t(load_value(src, dtype, t) - vmin) - predict(th, uint32_t(t));
+    rmin = rr < rmin ? rr : rmin;
+    rmax = rr > rmax ? rr : rmax;
+  }
+  block_minmax_i64(w, rmin, rmax);
+}
+
+__device__ inline uint64_t merged_size(uint64_t len, uint32_t bits) {
+  return kRecordBytes + 8 + 8 * ((len * bits + 63) >> 6);
+}
+
+// First thread whose flag is set, or kWalk; which = the mask slot (a slot is
+// used again only behind another slot's barrier).
+__device__ inline uint32_t first_of(WalkLds& w, uint32_t which, bool flag) {
+  const uint64_t mask = __ballot(flag);
+  if ((threadIdx.x & 63) == 0) w.mask[which][threadIdx.x >> 6] = mask;
+  __syncthreads();
+  uint32_t first = kWalk;
+#pragma unroll
+  for (int v = int(kWalkWaves) - 1; v >= 0; --v) {
+    const uint64_t m = w.mask[which][v];
+    if (m) first = uint32_t(v) * 64 + uint32_t(__ffsll(static_cast<long long>(m)) - 1);
+  }
+  return uint32_t(__builtin_amdgcn_readfirstlane(int(first)));
 }
 
 // Runs steps [kb, ke) from state st.  kFix = false: the bitmap holds zeros
 // there and the walk sets the kept bits.  kFix = true: the bits are another
 // run's, made from a different state; the walk rewrites them until it keeps
 // a boundary that run also kept (from there on both runs are the same) and
-// returns true at that point.  h / hr: the current partition's hulls, valid
-// when hr.state is kHullValid and a merge is pending.  Called by a whole
-// wavefront.
+// returns true at that point.  w.h[cur] / hr: the current partition's hulls,
+// valid when hr.state is kHullValid and a merge is pending.  Called by a
+// whole workgroup; state and decisions are the same in every thread.  The
+// walk only reads bits from step k on and only writes those before it.
 template <bool kFix>
-__device__ bool merge_walk(const uint8_t* __restrict__ col, uint32_t dtype,
-                           const uint64_t* __restrict__ s, const uint64_t* __restrict__ cost,
-                           const uint64_t* __restrict__ pair, const RangeSum* __restrict__ psum,
-                           uint64_t max_len, uint64_t kb, uint64_t ke, MergeState& st,
-                           unsigned long long* __restrict__ keep, HullLds& w, HullRegs& hr) {
-  const ChainHull& h = w.h;
-  const uint32_t lane = threadIdx.x & 63;
-  constexpr uint64_t kWide = uint64_t(1) << 61;  // value spread beyond which no line is fitted
+__device__ __attribute__((always_inline)) inline bool merge_walk(
+    const uint8_t* __restrict__ col, uint32_t dtype, const uint64_t* __restrict__ s,
+    const uint64_t* __restrict__ cost, const uint64_t* __restrict__ pair,
+    const RangeSum* __restrict__ psum, uint64_t max_len, uint64_t kb, uint64_t ke, MergeState& st,
+    unsigned long long* __restrict__ keep, WalkLds& w, HullRegs& hr, uint32_t& cur) {
+  const uint32_t tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  StripGroup<kEncBlock> group{&w.strip};
   uint64_t k = kb;
+  uint64_t w0 = 0, w1 = 0;  // partitions staged
+  uint64_t vb = 0, ve = 0;  // values staged (column positions)
+  uint64_t sa = s[st.a];
+  uint32_t solo = 0;        // merges sized one at a time since the last refusal
   while (k < ke) {
     if (st.a + 1 == k) {
-      // No merge pending: the next 64 steps are decided from the sizes
+      // No merge pending: the next kWalk steps are decided from the sizes
       // known in advance, each as if the steps before it kept their
       // boundary; the first merge (or meeting) ends the batch.
-      const uint64_t kk = k + lane;
+      const uint64_t kk = k + tid;
       const bool valid = kk < ke;
       bool merge = false, met = false;
       if (valid) {
@@ -1113,313 +1407,316 @@ __device__ bool merge_walk(const uint8_t* __restrict__ col, uint32_t dtype,
         merge = u != kNoMerge && u < cost[kk - 1] + cost[kk];
         if (kFix && !merge) met = bit_set(keep, kk);
       }
-      const uint64_t vmask = __ballot(valid), mmask = __ballot(merge),
-                     smask = kFix ? __ballot(met) : 0;
-      const int fm = mmask ? __ffsll(static_cast<long long>(mmask)) - 1 : 64;
-      const int fs = smask ? __ffsll(static_cast<long long>(smask)) - 1 : 64;
-      const int stop = fm < fs ? fm : fs;
-      const uint64_t kept = stop >= 64 ? vmask : vmask & ((1ull << stop) - 1);
-      if (lane == 0 && kept) set_bits(keep, k, kept);
-      if (fs < fm) return true;  // kFix: both runs keep boundary k + fs
-      if (fm == 64) {            // every valid step kept its boundary
-        const uint64_t last = uint64_t(63 - __clzll(static_cast<long long>(vmask)));
-        st.a = k + last;
+      const uint32_t steps = uint32_t(ke - k < kWalk ? ke - k : kWalk);
+      const uint32_t fm = first_of(w, 0, merge);
+      const uint32_t fs = kFix ? first_of(w, 1, met) : kWalk;
+      const uint32_t stop = min(min(fm, fs), steps);
+      set_run(keep, k, stop);
+      __syncthreads();               // the masks are read
+      if (fs < fm) return true;      // kFix: both runs keep boundary k + fs
+      if (fm == kWalk) {             // every valid step kept its boundary
+        st.a = k + steps - 1;
         st.cc = cost[st.a];
         st.sum = psum[st.a];
-        k += last + 1;
+        sa = s[st.a];
+        k += steps;
         continue;
       }
-      const uint64_t km = k + uint64_t(fm);
-      if (kFix && lane == 0) clear_bit(keep, km);
+      const uint64_t km = k + fm;
+      if (kFix) clear_run(keep, km, 1);
       st.a = km - 1;
       st.cc = pair[km - 1];
-      st.sum = join(psum[km - 1], psum[km], s[km] - s[km - 1]);
-      hr = HullRegs{0, 0, kHullNone};
+      sa = s[km - 1];
+      st.sum = join(psum[km - 1], psum[km], s[km] - sa);
+      hr = HullRegs{{0, 0}, kHullNone};
+      solo = 0;
       k = km + 1;
       continue;
     }
-    // The current partition absorbed others.  Lane l sizes its union with
-    // partitions k .. k+l: the union's sums and extremes from the
-    // partitions' summaries (a prefix across lanes), its slope from them,
-    // and its residual range from the current partition's hulls and one
-    // pass over the added values, every value broadcast to all lanes, each
-    // lane predicting with its own slope.  Without hulls the pass covers
-    // every value of the longest union, and the lanes taken are those
-    // whose union is at most about twice the current length, so a run that
-    // stops early wastes little of it.
-    const uint64_t sa = s[st.a];
-    const uint64_t lold = s[k] - sa;
-    if (hr.state == kHullNone && lold >= kHullBuildMin) {
-      if (lold <= kHullBuildMax && st.sum.vmax - st.sum.vmin < kWide) {
-        hr = HullRegs{0, 0, kHullValid};
-        hull_append(col, dtype, sa, 0, lold, st.sum.vmax - st.sum.vmin, w, hr);
+    // The current partition absorbed others.
+    if (k < w0 || k >= w1) {
+      w0 = k;
+      w1 = ke - k < kWalk ? ke : k + kWalk;
+      __syncthreads();  // every read of the old window is done
+      if (tid < w1 - w0) {
+        w.s[tid] = s[w0 + tid];
+        w.cost[tid] = cost[w0 + tid];
+        w.psum[tid] = psum[w0 + tid];
+      }
+      if (tid == 0) w.s[w1 - w0] = s[w1];
+      vb = s[w0];
+      ve = s[w1];
+      if (ve - vb <= kStageVals) {
+        for (uint64_t i = tid; i < ve - vb; i += kWalk) w.vals[i] = load_value(col, dtype, vb + i);
       } else {
-        hr.state = kHullDead;
+        ve = vb;
       }
+      __syncthreads();
     }
-    const bool via_hull = hr.state == kHullValid;
-    const uint64_t j = k + lane;
-    const uint64_t len0 = s[k + 1] - sa;
-    const uint64_t lcap = len0 + (len0 > 512 ? len0 : 512);
-    const uint64_t e_l = j < ke ? s[j + 1] : 0;
-    const bool act =
-        j < ke && (lane == 0 || (via_hull ? e_l - sa - lold <= kHullNewMax : e_l - sa <= lcap));
-    const uint32_t nact = uint32_t(__popcll(__ballot(act)));  // a prefix of the lanes
-    const uint64_t len_l = act ? e_l - sa : 0;
-    RangeSum u{~uint64_t(0), 0, U128{0, 0}, U128{0, 0}};
-    if (act) {
-      u = psum[j];
-      u.sty = add128(u.sty, mul128x64(u.sy, s[j] - sa));
-    }
-    // inclusive prefix over the lanes (the inactive ones add nothing)
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-      const uint64_t mn = shfl_up64(u.vmin, d), mx = shfl_up64(u.vmax, d);
-      const U128 y{shfl_up64(u.sy.lo, d), shfl_up64(u.sy.hi, d)};
-      const U128 ty{shfl_up64(u.sty.lo, d), shfl_up64(u.sty.hi, d)};
-      if (int(lane) >= d) {
-        u.vmin = mn < u.vmin ? mn : u.vmin;
-        u.vmax = mx > u.vmax ? mx : u.vmax;
-        u.sy = add128(u.sy, y);
-        u.sty = add128(u.sty, ty);
-      }
-    }
-    const uint64_t vmin = st.sum.vmin < u.vmin ? st.sum.vmin : u.vmin;
-    const uint64_t vmax = st.sum.vmax > u.vmax ? st.sum.vmax : u.vmax;
-    const uint64_t range = vmax - vmin;
-    const bool fits = act && len_l <= max_len;
-    const bool lin = fits && len_l > 1 && range < kWide;
-    double th = 0.0;
-    if (lin) th = ls_slope(len_l, add128(st.sum.sy, u.sy), add128(st.sum.sty, u.sty));
-    int64_t rmin = INT64_MAX, rmax = INT64_MIN;
-    const uint64_t lmax = readlane64(len_l, nact - 1);
-    const uint8_t* src = col + sa * dtype;
-    // 32 bits suffice when, on every lane fitting a line, the union's values
-    // lie within 2^31 of its minimum and every |prediction| is below 2^31
-    const bool narrow =
-        __ballot(lin && !(range < (uint64_t(1) << 31) &&
-                          __dmul_rn(fabs(th), double(len_l)) < 2147483648.0)) == 0;
-    // the values of [tb, lmax) staged 64 at a time in LDS, each read by
-    // every lane at once, every lane predicting with its own slope
-    auto scan = [&](uint64_t tb) {
-      for (uint64_t t0 = tb; t0 < lmax; t0 += 64) {
-        const uint64_t t = t0 + lane;
-        w.stage[lane] = load_value(src, dtype, t < lmax ? t : lmax - 1);
-        wave_lds_order();
-        const uint32_t cnt = lmax - t0 < 64 ? uint32_t(lmax - t0) : 64u;
-        if (narrow) {
-          const uint32_t vmin32 = uint32_t(vmin);
-          int32_t mn = INT32_MAX, mx = INT32_MIN;
-          for (uint32_t q = 0; q < cnt; ++q) {
-            const uint32_t tq = uint32_t(t0) + q;
-            const bool in = lin && tq < len_l;
-            const int32_t rr = int32_t(uint32_t(w.stage[q]) - vmin32) - predict32(th, in ? tq : 0);
-            mn = in ? min(mn, rr) : mn;
-            mx = in ? max(mx, rr) : mx;
-          }
-          rmin = mn < rmin ? mn : rmin;
-          rmax = mx > rmax ? mx : rmax;
-        } else {
-          for (uint32_t q = 0; q < cnt; ++q) {
-            const uint64_t tq = t0 + q;
-            if (lin && tq < len_l) {
-              const int64_t rr = int64_t(w.stage[q] - vmin) - predict(th, uint32_t(tq));
-              rmin = rr < rmin ? rr : rmin;
-              rmax = rr > rmax ? rr : rmax;
-            }
-          }
-        }
-        wave_lds_order();  // every read of the block precedes the next one's staging
-      }
+    // the value at position t of the current partition
+    const auto read = [&](uint64_t t) {
+      const uint64_t p = sa + t;
+      return p >= vb && p < ve ? w.vals[p - vb] : load_value(col, dtype, p);
     };
-    bool scan_all = !via_hull;
-    if (via_hull) {
-      scan(lold);  // the added values
-      bool unsure = false;
-      if (lin) {
-        const double pmax = __dmul_rn(fabs(th), double(len_l));  // bounds every |product|
-        if (!(pmax < 2147483648.0)) {
-          unsure = true;  // products too large for the rounding test below
+    const uint64_t lold = w.s[k - w0] - sa;
+    const uint64_t l0 = w.s[k - w0 + 1] - w.s[k - w0];
+    uint32_t f = 0;  // steps k .. k+f-1 merge
+    bool on = false;  // and the chain goes on
+    if (lold + l0 > max_len) {
+      // refused
+    } else if (l0 > kHullAppendMax ||
+               (hr.state == kHullNone && solo < kSoloMerges &&
+                (l0 > kSoloMin || lold > kHullBuildNow)) ||
+               (hr.state == kHullDead && (l0 > kSoloMin || lold > kDeadScanMax))) {
+      // One step, its union's residuals scanned by all threads, when the
+      // neighbour is long, or a long current partition has no hulls (yet).
+      const RangeSum u = join(st.sum, w.psum[k - w0], lold);
+      const uint64_t len = lold + l0, range = u.vmax - u.vmin;
+      uint32_t bits = bitlen64(range);
+      if (range < kWide) {
+        const double th = ls_slope(len, u.sy, u.sty);
+        int64_t rmin, rmax;
+        range_scan(w, group, col + sa * dtype, dtype, len, u.vmin, range, th, rmin, rmax);
+        bits = min(bits, bitlen64(uint64_t(rmax) - uint64_t(rmin)));
+      }
+      const uint64_t size = merged_size(len, bits);
+      if (size < st.cc + w.cost[k - w0]) {
+        f = 1;
+        on = true;
+        st.cc = size;
+        st.sum = u;
+        hr.state = kHullNone;  // built again when short neighbours follow
+        ++solo;
+      }
+    } else {
+      // Thread i sizes the union with partitions k .. k+i: the union's sums
+      // and extremes from the partitions' summaries (a prefix across
+      // threads), its slope from them, and its width from hulls: the union's
+      // points lie between the current partition's and those of the batch's
+      // longest union, so where the two hulls' residual ranges need the same
+      // number of bits, so does the union.  Otherwise (or without hulls) the
+      // added (or all) values are broadcast one by one to all threads, each
+      // predicting with its own slope; without hulls the unions taken are at
+      // most about twice the current length, so a run that stops early
+      // wastes little.
+      if (hr.state == kHullNone && lold >= kHullBuildMin) {
+        if (st.sum.vmax - st.sum.vmin < kWide) {
+          hr = hull_extend(w, cur, cur ^ 1, hr, 0, lold, st.sum.vmax - st.sum.vmin, read);
+          cur ^= 1;
         } else {
-          // Old values.  Exact residuals: the largest, R, is at an upper
-          // vertex and the smallest, Q, at a lower one.  The encoder's
-          // largest is R unless every value reaching R rounds up; its
-          // smallest is Q - 1 if some value reaching Q rounds up, which
-          // needs a product within half an ulp of pmax under an integer:
-          // ruled out when the lower vertices reaching Q, among them the
-          // one minimising v - theta1 * t, have a larger gap (margin: two
-          // ulps of pmax, at least 2^-48 against the gap's own rounding).
-          const double margin = pmax >= 0x1p-3 ? fmax(ldexp(1.0, ilogb(pmax) - 51), 0x1p-48)
-                                               : 0x1p-48;
-          int64_t R = INT64_MIN, Q = INT64_MAX;
-          bool r_exact = false, q_up = false, q_gap = true;
-          for (uint32_t i = 0; i < hr.nu; ++i) {
-            bool up;
-            double gap;
-            const int64_t rr = vertex_residual(th, h.t[0][i], h.x[0][i], vmin, up, gap);
-            if (rr > R) {
-              R = rr;
-              r_exact = !up;
-            } else if (rr == R) {
-              r_exact = r_exact || !up;
-            }
-          }
-          for (uint32_t i = 0; i < hr.nl; ++i) {
-            bool up;
-            double gap;
-            const int64_t rr = vertex_residual(th, h.t[1][i], h.x[1][i], vmin, up, gap);
-            const bool wide_gap = gap >= margin;
-            if (rr < Q) {
-              Q = rr;
-              q_up = up;
-              q_gap = wide_gap;
-            } else if (rr == Q) {
-              q_up = q_up || up;
-              q_gap = q_gap && wide_gap;
-            }
-          }
-          if (r_exact || rmax >= R) rmax = rmax > R ? rmax : R;
-          else unsure = true;
-          if (q_up) rmin = rmin < Q - 1 ? rmin : Q - 1;
-          else if (q_gap) rmin = rmin < Q ? rmin : Q;
-          else if (rmin > Q - 1) unsure = true;
+          hr.state = kHullDead;
         }
       }
-      scan_all = __ballot(unsure) != 0;
-      if (scan_all) {
-        rmin = INT64_MAX;
-        rmax = INT64_MIN;
+      const bool via_hull = hr.state == kHullValid;
+      const uint64_t j = k + tid;
+      const uint64_t len0 = lold + l0;
+      uint64_t lcap = via_hull ? lold + kBatchNew : len0 + (len0 > 512 ? len0 : 512);
+      if (lcap > max_len) lcap = max_len;
+      const uint64_t e_l = j < w1 ? w.s[j - w0 + 1] : 0;
+      const bool act = j < w1 && (tid == 0 || e_l - sa <= lcap);
+      RangeSum u{~uint64_t(0), 0, U128{0, 0}, U128{0, 0}};
+      if (act) {
+        u = w.psum[j - w0];
+        u.sty = add128(u.sty, mul128x64(u.sy, w.s[j - w0] - sa));
       }
-    }
-    if (scan_all) scan(0);
-    uint32_t bits = bitlen64(range);
-    if (lin) {
-      const uint32_t b_ls = bitlen64(uint64_t(rmax) - uint64_t(rmin));
-      if (b_ls < bits) bits = b_ls;
-    }
-    const uint64_t size = fits ? kRecordBytes + 8 + 8 * ((len_l * bits + 63) >> 6) : kNoMerge;
-    uint64_t prev = shfl_up64(size, 1);
-    if (lane == 0) prev = st.cc;
-    const bool merge = act && size != kNoMerge && size < prev + (act ? cost[j] : 0);
-    const uint64_t refuse = __ballot(act && !merge);
-    const uint32_t f = refuse ? uint32_t(__ffsll(static_cast<long long>(refuse)) - 1) : nact;
-    if (kFix && lane == 0 && f > 0) {  // steps k .. k+f-1 merged
-      for (uint32_t i = 0; i < f; ++i) clear_bit(keep, k + i);
-    }
-    if (f == nact) {  // the chain goes on past the batch
-      st.cc = readlane64(size, f - 1);
-      st.sum.vmin = readlane64(vmin, f - 1);
-      st.sum.vmax = readlane64(vmax, f - 1);
-      st.sum.sy = add128(st.sum.sy, U128{readlane64(u.sy.lo, f - 1), readlane64(u.sy.hi, f - 1)});
-      st.sum.sty = add128(st.sum.sty, U128{readlane64(u.sty.lo, f - 1), readlane64(u.sty.hi, f - 1)});
-      if (hr.state == kHullValid) {
-        const uint64_t lnew = s[k + f] - sa;
-        if (lnew - lold > kHullAppendMax || st.sum.vmax - st.sum.vmin >= kWide)
-          hr.state = kHullDead;
+      // inclusive prefix over the threads (the inactive ones, the last, add
+      // nothing), from the current partition's own summary on
+#pragma unroll
+      for (int d = 1; d < 64; d <<= 1) {
+        const uint64_t mn = shfl_up64(u.vmin, d), mx = shfl_up64(u.vmax, d);
+        const U128 y{shfl_up64(u.sy.lo, d), shfl_up64(u.sy.hi, d)};
+        const U128 ty{shfl_up64(u.sty.lo, d), shfl_up64(u.sty.hi, d)};
+        if (int(lane) >= d) {
+          u.vmin = mn < u.vmin ? mn : u.vmin;
+          u.vmax = mx > u.vmax ? mx : u.vmax;
+          u.sy = add128(u.sy, y);
+          u.sty = add128(u.sty, ty);
+        }
+      }
+      if (lane == 63) w.wave_sum[wave] = u;
+      const uint32_t nact = first_of(w, 0, !act);  // also orders wave_sum
+      RangeSum all = st.sum;  // summary of the longest union
+#pragma unroll
+      for (uint32_t v = 0; v < kWalkWaves; ++v) {
+        if (v == wave) u = join(all, u, 0);
+        all = join(all, w.wave_sum[v], 0);
+      }
+      const uint64_t len_l = act ? e_l - sa : 0;
+      const uint64_t lmax = w.s[k - w0 + nact] - sa;
+      const uint64_t spread = all.vmax - all.vmin;
+      const uint64_t vmin = u.vmin, range = u.vmax - u.vmin;
+      const bool lin = act && range < kWide;
+      double th = 0.0;
+      if (lin) th = ls_slope(len_l, u.sy, u.sty);
+      const double pmax = __dmul_rn(fabs(th), double(len_l));  // bounds every |product|
+      int64_t rmin = INT64_MAX, rmax = INT64_MIN;
+      uint32_t bits = bitlen64(range);
+      // the values of [tb, lmax) staged in LDS, each read by every thread at
+      // once, every thread predicting with its own slope; with narrow64 (in
+      // every thread) offsets and predictions below 2^50, exact in binary64
+      const auto scan = [&](uint64_t tb, bool narrow64) {
+        double mx = -__builtin_inf(), mn = __builtin_inf();
+        const double own = lin ? double(uint32_t(len_l)) : 0.0;
+        for (uint64_t t0 = tb; t0 < lmax; t0 += kWalk) {
+          const uint64_t t = t0 + tid;
+          const uint32_t cnt = lmax - t0 < kWalk ? uint32_t(lmax - t0) : kWalk;
+          __syncthreads();  // every read of the block before is done
+          const uint64_t x = t < lmax ? read(t) - all.vmin : 0;
+          // past the end: NaN, which maximum and minimum pass over
+          if (narrow64)
+            w.scan[tid] = t < lmax ? double(x) : __builtin_nan("");
+          else
+            w.scan[tid] = __longlong_as_double(static_cast<long long>(x));
+          __syncthreads();
+          if (narrow64) {
+            for (uint32_t q0 = 0; q0 < cnt; q0 += 8) {
+#pragma unroll
+              for (uint32_t q = 0; q < 8; ++q) {
+                const double tq = double(uint32_t(t0) + q0 + q);
+                const double r = w.scan[q0 + q] - floor(__dmul_rn(th, tq));
+                const double rr = tq < own ? r : __builtin_nan("");
+                mx = fmax(mx, rr);
+                mn = fmin(mn, rr);
+              }
+            }
+          } else {
+            for (uint32_t q = 0; q < cnt; ++q) {
+              const uint64_t tq = t0 + q;
+              if (lin && tq < len_l) {
+                const int64_t rr = int64_t(uint64_t(__double_as_longlong(w.scan[q]))) -
+                                   predict(th, uint32_t(tq));
+                rmin = rr < rmin ? rr : rmin;
+                rmax = rr > rmax ? rr : rmax;
+              }
+            }
+          }
+        }
+        if (narrow64 && mn <= mx) {
+          rmin = int64_t(mn);
+          rmax = int64_t(mx);
+        }
+        // counted from the thread's own smallest value
+        if (rmin <= rmax) {
+          rmin -= int64_t(vmin - all.vmin);
+          rmax -= int64_t(vmin - all.vmin);
+        }
+      };
+      // a batch of one: its slope (thread 0's) and a scan by all threads
+      const auto alone = [&](double own_th) {
+        if (tid == 0) w.scan[0] = own_th;
+        __syncthreads();
+        range_scan(w, group, col + sa * dtype, dtype, lmax, all.vmin, spread, w.scan[0], rmin, rmax);
+        __syncthreads();
+      };
+      HullRegs grown{{0, 0}, kHullDead};
+      if (via_hull) {
+        if (spread < kWide) grown = hull_extend(w, cur, cur ^ 1, hr, lold, lmax, spread, read);
+        const bool two = grown.state == kHullValid;
+        HullRange r[2];
+        if (cur == 0)
+          hull_ranges(w, hr.n, two ? grown.n : hr.n, th, pmax, vmin, r);
         else
-          hull_append(col, dtype, sa, lold, lnew, st.sum.vmax - st.sum.vmin, w, hr);
+          hull_ranges(w, two ? grown.n : hr.n, hr.n, th, pmax, vmin, r);
+        const HullRange own = cur == 0 ? r[0] : r[1], most = cur == 0 ? r[1] : r[0];
+        const bool small = pmax < 2147483648.0;
+        const uint32_t b_own = own.bits_lo();
+        const bool decided = small && (b_own >= bits || (two && b_own == most.bits_hi()));
+        if (first_of(w, 1, lin && !decided) == kWalk) {
+          if (lin && b_own < bits) bits = b_own;
+        } else {
+          const bool whole =
+              nact == 1 || first_of(w, 2, lin && !(small && own.exact())) != kWalk;
+          const bool narrow64 =
+              spread < (uint64_t(1) << 50) && first_of(w, 0, lin && !(pmax < 0x1p50)) == kWalk;
+          if (nact == 1)  // one slope: thread 0's
+            alone(th);
+          else
+            scan(whole ? 0 : lold, narrow64);
+          if (!whole && lin) {
+            rmin = own.min_lo < rmin ? own.min_lo : rmin;
+            rmax = own.max_hi > rmax ? own.max_hi : rmax;
+          }
+          if (lin) bits = min(bits, bitlen64(uint64_t(rmax) - uint64_t(rmin)));
+        }
+      } else {
+        const bool narrow64 =
+            spread < (uint64_t(1) << 50) && first_of(w, 1, lin && !(pmax < 0x1p50)) == kWalk;
+        scan(0, narrow64);
+        if (lin) bits = min(bits, bitlen64(uint64_t(rmax) - uint64_t(rmin)));
       }
+      const uint64_t size = act ? merged_size(len_l, bits) : kNoMerge;
+      w.size[tid] = size;
+      __syncthreads();
+      const uint64_t prev = tid == 0 ? st.cc : w.size[tid - 1];
+      const bool merge = act && size < prev + (act ? w.cost[j - w0] : 0);
+      f = min(first_of(w, 2, act && !merge), nact);
+      on = f == nact;
+      if (on) {  // the chain goes on past the batch
+        st.cc = w.size[f - 1];
+        st.sum = all;
+        if (via_hull) {
+          hr = grown;  // dead when it outgrew kHullMax vertices
+          cur ^= 1;
+        }
+      }
+      __syncthreads();  // sizes and masks are read
+    }
+    if (kFix) clear_run(keep, k, f);
+    if (on) {
       k += f;
       continue;
     }
     // step k+f refuses: boundary k+f is kept and partition k+f is current
     const uint64_t kk = k + f;
+    // (one thread reads the bit: another's read might follow the write below)
     bool met = false;
-    if (lane == 0) {
-      if (kFix) met = bit_set(keep, kk);
-      if (!met) set_bits(keep, kk, 1);
+    if (kFix) {
+      met = first_of(w, 1, tid == 0 && bit_set(keep, kk)) == 0;
+      __syncthreads();  // the mask is read
     }
-    met = __ballot(met) != 0;
+    if (!met) set_run(keep, kk, 1);
     st.a = kk;
-    st.cc = cost[kk];
-    st.sum = psum[kk];
-    hr = HullRegs{0, 0, kHullNone};
+    st.cc = w.cost[kk - w0];
+    st.sum = w.psum[kk - w0];
+    sa = w.s[kk - w0];
+    hr = HullRegs{{0, 0}, kHullNone};
+    solo = 0;
     k = kk + 1;
     if (met) return true;
   }
   return false;
 }
 
-
-// psum[j] = the summary of partition j, j < m: one lane per partition of at
-// most 64 values, the wavefront together for the longer ones of its 64.
-__global__ __launch_bounds__(kEncBlock) void k_part_sums(const uint8_t* __restrict__ col,
-                                                        uint32_t dtype,
-                                                        const uint64_t* __restrict__ s,
-                                                        uint64_t m, RangeSum* __restrict__ psum) {
-  const uint32_t lane = threadIdx.x & 63;
-  const uint64_t waves = uint64_t(gridDim.x) * kEncWaves;
-  for (uint64_t j0 = (uint64_t(blockIdx.x) * kEncWaves + (threadIdx.x >> 6)) * 64; j0 < m;
-       j0 += waves * 64) {
-    const uint64_t j = j0 + lane;
-    uint64_t a = 0, e = 0;
-    if (j < m) {
-      a = s[j];
-      e = s[j + 1];
-    }
-    const bool shortp = j < m && e - a <= 64;
-    if (shortp) {
-      RangeSum r{~uint64_t(0), 0, U128{0, 0}, U128{0, 0}};
-      for (uint64_t t = 0; t < e - a; ++t) {
-        const uint64_t x = load_value(col, dtype, a + t);
-        r.vmin = x < r.vmin ? x : r.vmin;
-        r.vmax = x > r.vmax ? x : r.vmax;
-        r.sy = add128(r.sy, U128{x, 0});
-        r.sty = add128(r.sty, mul64x64(t, x));
-      }
-      psum[j] = r;
-    }
-    uint64_t todo = __ballot(j < m && !shortp);
-    while (todo) {
-      const uint32_t l = uint32_t(__ffsll(static_cast<long long>(todo)) - 1);
-      todo &= todo - 1;
-      const uint64_t la = readlane64(a, l), le = readlane64(e, l);
-      RangeSum r{~uint64_t(0), 0, U128{0, 0}, U128{0, 0}};
-      for (uint64_t t = lane; t < le - la; t += 64) {
-        const uint64_t x = load_value(col, dtype, la + t);
-        r.vmin = x < r.vmin ? x : r.vmin;
-        r.vmax = x > r.vmax ? x : r.vmax;
-        r.sy = add128(r.sy, U128{x, 0});
-        r.sty = add128(r.sty, mul64x64(t, x));
-      }
-      wave_minmax_u64(r.vmin, r.vmax);
-      wave_sum_u128x2(r.sy, r.sty);
-      if (lane == 0) psum[j0 + l] = r;
-    }
-  }
-}
-
-
-// Speculative pass: one wavefront per chunk of kMergeChunk boundaries,
+// Speculative pass: one workgroup per chunk of 2^chunk_log2 boundaries,
 // scanned as if its first boundary were kept (chunk 0 from the true start);
 // each chunk's end state and hulls go to out and hulls, and seen[q] records
 // the entry state the chunk was walked from.
-__global__ __launch_bounds__(kEncBlock) void k_merge_spec(
+__global__ __launch_bounds__(kWalk) void k_merge_spec(
     const uint8_t* __restrict__ col, uint32_t dtype, const uint64_t* __restrict__ s,
     const uint64_t* __restrict__ cost, const uint64_t* __restrict__ pair,
-    const RangeSum* __restrict__ psum, uint64_t m, uint64_t max_len,
+    const RangeSum* __restrict__ psum, uint64_t m, uint64_t max_len, uint32_t chunk_log2,
     unsigned long long* __restrict__ keep, MergeState* __restrict__ out,
     ChainHull* __restrict__ hulls, uint64_t* __restrict__ seen) {
-  __shared__ HullLds lds[kEncWaves];
-  const uint32_t wv = threadIdx.x >> 6;
-  const uint64_t q = uint64_t(blockIdx.x) * kEncWaves + wv;
-  const uint64_t k0 = q << kMergeChunkLog2;
+  __shared__ WalkLds lds;
+  const uint64_t q = blockIdx.x;
+  const uint64_t k0 = q << chunk_log2, chunk = uint64_t(1) << chunk_log2;
   if (k0 >= m) return;
-  const uint64_t ke = m - k0 < kMergeChunk ? m : k0 + kMergeChunk;
+  const uint64_t ke = m - k0 < chunk ? m : k0 + chunk;
   MergeState st;
   uint64_t kb = k0;
   if (q == 0) {
-    if ((threadIdx.x & 63) == 0) set_bits(keep, 0, 1);
+    set_run(keep, 0, 1);
     st = MergeState{0, cost[0], psum[0]};
     kb = 1;
   } else {
     st = MergeState{k0 - 1, cost[k0 - 1], psum[k0 - 1]};
-    if ((threadIdx.x & 63) == 0) seen[q] = k0 - 1;
+    if (threadIdx.x == 0) seen[q] = k0 - 1;
   }
-  HullRegs hr{0, 0, kHullNone};
-  merge_walk<false>(col, dtype, s, cost, pair, psum, max_len, kb, ke, st, keep, lds[wv], hr);
-  if ((threadIdx.x & 63) == 0) out[q] = st;
-  hull_store(hulls + q, lds[wv].h, hr);
+  HullRegs hr{{0, 0}, kHullNone};
+  uint32_t cur = 0;
+  merge_walk<false>(col, dtype, s, cost, pair, psum, max_len, kb, ke, st, keep, lds, hr, cur);
+  if (threadIdx.x == 0) out[q] = st;
+  hull_store(hulls + q, lds.h[cur], hr);
 }
 
 // Fix-up rounds.  out[q] is the end state (hulls[q] its hulls) of the run
@@ -1428,89 +1725,103 @@ __global__ __launch_bounds__(kEncBlock) void k_merge_spec(
 // differs from seen: from that state, rewriting the chunk's bits until it
 // keeps a boundary the recorded run also kept (from there on that run is
 // right, and so is its end state) or reaches the chunk's end (its end state
-// is the new out[q]).  The neighbours, of the other parity, do not run in
-// the same round.  Chunk 0 begins where the column does, so after round r
-// (parities 1, 0, 1, ...) at least chunks 0..r are right; rounds repeat
-// until two in a row walk nothing.
-__global__ __launch_bounds__(kEncBlock) void k_merge_round(
+// is the new out[q], and chunk q + 1, of the other parity, is looked at in
+// the next round).  The neighbours, of the other parity, do not run in the
+// same round.  Rounds 0 and 1 look at every odd and every even chunk, the
+// later ones at the list the round before them left in lists[r & 1], of
+// todo[0] entries; todo[1] counts the next round's.  Chunk 0 begins where
+// the column does, so after round r at least chunks 0..r+1 are right; rounds
+// end when one leaves an empty list.
+__global__ __launch_bounds__(kWalk) void k_merge_round(
     const uint8_t* __restrict__ col, uint32_t dtype, const uint64_t* __restrict__ s,
     const uint64_t* __restrict__ cost, const uint64_t* __restrict__ pair,
-    const RangeSum* __restrict__ psum, uint64_t m, uint64_t max_len,
+    const RangeSum* __restrict__ psum, uint64_t m, uint64_t max_len, uint32_t chunk_log2,
     unsigned long long* __restrict__ keep, MergeState* __restrict__ out,
-    ChainHull* __restrict__ hulls, uint64_t* __restrict__ seen, uint64_t nchunks,
-    uint32_t parity, unsigned long long* __restrict__ walks) {
-  __shared__ HullLds lds[kEncWaves];
-  const uint32_t wv = threadIdx.x >> 6;
-  const uint64_t q = 2 * (uint64_t(blockIdx.x) * kEncWaves + wv) + parity;
-  if (q == 0 || q >= nchunks) return;
-  MergeState st = out[q - 1];
-  if (st.a == seen[q]) return;
-  const uint64_t kb = q << kMergeChunkLog2;
-  const uint64_t ke = m - kb < kMergeChunk ? m : kb + kMergeChunk;
-  HullRegs hr{0, 0, kHullNone};
-  if (st.a + 1 < kb) hr = hull_load(hulls + (q - 1), lds[wv].h);
-  const bool met =
-      merge_walk<true>(col, dtype, s, cost, pair, psum, max_len, kb, ke, st, keep, lds[wv], hr);
-  if ((threadIdx.x & 63) == 0) {
-    seen[q] = out[q - 1].a;
-    if (!met) out[q] = st;
-    atomicAdd(walks, 1ull);
+    ChainHull* __restrict__ hulls, uint64_t* __restrict__ seen, uint64_t nchunks, uint64_t round,
+    uint32_t* __restrict__ lists, uint32_t* __restrict__ todo) {
+  __shared__ WalkLds lds;
+  const uint32_t* list = lists + (round & 1) * nchunks;
+  uint32_t* next = lists + ((round + 1) & 1) * nchunks;
+  const uint64_t count = round < 2 ? (nchunks + 1) / 2 : todo[0];
+  for (uint64_t i = blockIdx.x; i < count; i += gridDim.x) {
+    const uint64_t q = round < 2 ? 2 * i + (round == 0 ? 1 : 0) : list[i];
+    if (q == 0 || q >= nchunks) continue;
+    MergeState st = out[q - 1];
+    const uint64_t from = st.a;
+    if (from == seen[q]) continue;
+    __syncthreads();  // seen[q] is read by every thread before it is written
+    const uint64_t kb = q << chunk_log2, chunk = uint64_t(1) << chunk_log2;
+    const uint64_t ke = m - kb < chunk ? m : kb + chunk;
+    HullRegs hr{{0, 0}, kHullNone};
+    uint32_t cur = 0;
+    if (from + 1 < kb) hr = hull_load(hulls + (q - 1), lds.h[0]);
+    const bool met = merge_walk<true>(col, dtype, s, cost, pair, psum, max_len, kb, ke, st, keep,
+                                      lds, hr, cur);
+    if (threadIdx.x == 0) {
+      seen[q] = from;
+      if (!met) {
+        out[q] = st;
+        if (q + 1 < nchunks) next[atomicAdd(todo + 1, 1u)] = uint32_t(q + 1);
+      }
+    }
+    if (!met) hull_store(hulls + q, lds.h[cur], hr);
+    __syncthreads();  // the walker's LDS is free
   }
-  if (!met) hull_store(hulls + q, lds[wv].h, hr);
 }
 
 // ---- compaction after a pass --------------------------------------------------------
 
-__device__ inline uint32_t kept_bit(const unsigned long long* keep, uint64_t k, uint64_t m) {
-  return k < m && ((keep[k >> 6] >> (k & 63)) & 1ull) ? 1u : 0u;
+constexpr uint32_t kKeepWords = 64;  // bitmap words per workgroup
+
+// Word w of the bitmap of kept boundaries, bits from m on clear.
+__device__ inline uint64_t kept_word(const unsigned long long* keep, uint64_t w, uint64_t m) {
+  if (w * 64 >= m) return 0;
+  const uint64_t x = keep[w];
+  return m - w * 64 < 64 ? x & ((1ull << (m - w * 64)) - 1) : x;
 }
 
-// Kept boundaries in words [blockIdx * 1024, +1024) of the bitmap.
-__global__ __launch_bounds__(kScanBlock) void k_keep_count(const unsigned long long* __restrict__ keep,
-                                                           uint64_t m, uint64_t* __restrict__ counts) {
-  const uint64_t nwords = (m + 63) / 64;
-  const uint64_t w0 = uint64_t(blockIdx.x) * kItemsPerBlock + threadIdx.x * 4;
-  uint32_t c = 0;
+// Kept boundaries in the workgroup's words.
+__global__ __launch_bounds__(64) void k_keep_count(const unsigned long long* __restrict__ keep,
+                                                   uint64_t m, uint64_t* __restrict__ counts) {
+  uint32_t c = uint32_t(__popcll(kept_word(keep, uint64_t(blockIdx.x) * kKeepWords + threadIdx.x, m)));
 #pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    const uint64_t w = w0 + q;
-    if (w < nwords) {
-      uint64_t x = keep[w];
-      if ((w + 1) * 64 > m) x &= (m & 63) ? ((1ull << (m & 63)) - 1) : ~0ull;
-      c += uint32_t(__popcll(x));
-    }
-  }
-  uint32_t total;
-  block_exclusive_scan(c, &total);
-  if (threadIdx.x == 0) counts[blockIdx.x] = total;
+  for (int d = 32; d > 0; d >>= 1) c += uint32_t(__shfl_xor(int(c), d, 64));
+  if (threadIdx.x == 0) counts[blockIdx.x] = c;
 }
 
-// Copies the kept starts to their new places with their sizes (a
-// partition that absorbed others is sized afterwards), whether it absorbed
-// others, and its old index.
+// Copies the kept starts to their new places with their sizes and summaries
+// (a partition that absorbed others is sized afterwards), whether it
+// absorbed others, and its old index.  A lane per boundary, so that a
+// word's partitions are read and written side by side.
 __global__ __launch_bounds__(kScanBlock) void k_keep_emit(
     const unsigned long long* __restrict__ keep, uint64_t m, const uint64_t* __restrict__ offsets,
     const uint64_t* __restrict__ starts, const uint64_t* __restrict__ cost,
-    uint64_t* __restrict__ starts_out, uint64_t* __restrict__ cost_out,
+    const RangeSum* __restrict__ psum, uint64_t* __restrict__ starts_out,
+    uint64_t* __restrict__ cost_out, RangeSum* __restrict__ psum_out,
     uint8_t* __restrict__ changed_out, uint64_t* __restrict__ old_out) {
-  const uint64_t w0 = uint64_t(blockIdx.x) * kItemsPerBlock + threadIdx.x * 4;
-  uint32_t c = 0;
+  constexpr uint32_t kPer = kKeepWords / (kScanBlock / 64);  // words per wavefront
+  const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const uint64_t w0 = uint64_t(blockIdx.x) * kKeepWords;
+  // kept boundaries before this wavefront's words
+  uint32_t c = lane < wave * kPer ? uint32_t(__popcll(kept_word(keep, w0 + lane, m))) : 0;
 #pragma unroll
-  for (int q = 0; q < 4; ++q)
-    for (uint64_t k = (w0 + q) * 64; k < (w0 + q + 1) * 64 && k < m; ++k) c += kept_bit(keep, k, m);
-  uint32_t total;
-  uint64_t out = offsets[blockIdx.x] + block_exclusive_scan(c, &total);
-#pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    for (uint64_t k = (w0 + q) * 64; k < (w0 + q + 1) * 64 && k < m; ++k) {
-      if (!kept_bit(keep, k, m)) continue;
-      const bool absorbed = k + 1 < m && !kept_bit(keep, k + 1, m);
-      starts_out[out] = starts[k];
-      cost_out[out] = cost[k];
-      changed_out[out] = absorbed ? 1 : 0;
-      old_out[out] = k;
-      ++out;
+  for (int d = 32; d > 0; d >>= 1) c += uint32_t(__shfl_xor(int(c), d, 64));
+  uint64_t out = offsets[blockIdx.x] + c;
+  for (uint32_t q = 0; q < kPer; ++q) {
+    const uint64_t w = w0 + wave * kPer + q;
+    const uint64_t x = kept_word(keep, w, m);
+    const uint64_t k = w * 64 + lane;
+    if ((x >> lane) & 1) {
+      const uint64_t o = out + uint64_t(__popcll(x & ((1ull << lane) - 1)));
+      const uint64_t after = lane < 63 ? x >> (lane + 1) : kept_word(keep, w + 1, m);
+      const bool absorbed = k + 1 < m && !(after & 1);
+      starts_out[o] = starts[k];
+      cost_out[o] = cost[k];
+      if (!absorbed) psum_out[o] = psum[k];
+      changed_out[o] = absorbed ? 1 : 0;
+      old_out[o] = k;
     }
+    out += uint64_t(__popcll(x));
   }
 }
 
@@ -1548,6 +1859,30 @@ struct Buffers {
     return true;
   }
 };
+
+constexpr uint64_t kRoundGroup = 16;  // fix-up rounds launched between checks
+constexpr uint64_t kRoundGrid = 1024;  // workgroups of a round that works off a list
+
+// Boundaries per speculative chunk of a merge pass over m partitions of n
+// values.  A run of merges crosses one chunk per round and every chunk is
+// walked again in each round until its run is the right one, so long chunks
+// save work (256 boundaries made a thousand walkers re-walk 20,000 chunks 93
+// times each), as long as there is a walker for every CU: about a thousand
+// chunks of 1024 (four batches, 40 us: below, a round costs its launch) to
+// 4096 boundaries.  Partitions that are sized one at a time (kSoloMin) take
+// as long each as a batch of short ones: 16 per chunk.
+uint32_t chunk_log2(uint64_t m, uint64_t n) {
+  if (n / m > leco::kSoloMin) return 4;
+  uint32_t c = 10;
+  while (c < 12 && (m >> c) > 1024) ++c;
+  return c;
+}
+
+// The most chunks a pass over at most m partitions of n values has.
+uint64_t chunks_bound(uint64_t m, uint64_t n) {
+  const uint64_t few = n / leco::kSoloMin;  // partitions longer than kSoloMin on average
+  return ((m < few ? m : few) >> 4) + (m >> 10) + 2;
+}
 
 leco_status pfail(leco_ctx* ctx, leco_status st, const char* msg) {
   ctx->last_error = msg;
@@ -1661,21 +1996,22 @@ leco_status leco_partition(leco_ctx* ctx, const void* col_dev, uint64_t n, leco_
   uint64_t *starts = nullptr, *starts2 = nullptr, *cost = nullptr, *cost2 = nullptr,
            *pair = nullptr, *pair2 = nullptr, *old = nullptr, *keep_counts = nullptr;
   uint8_t *changed = nullptr, *dirty = nullptr;
-  unsigned long long *keep = nullptr, *walks = nullptr;
+  unsigned long long* keep = nullptr;
+  uint32_t *todo = nullptr, *lists = nullptr;
   leco::MergeState* mout = nullptr;
   leco::ChainHull* hulls = nullptr;
-  leco::RangeSum* psum = nullptr;
+  leco::RangeSum *psum = nullptr, *psum2 = nullptr;
   uint64_t* seen = nullptr;
-  constexpr int kRoundGroup = 8;  // fix-up rounds launched between checks
   const uint64_t kwords = (m + 63) / 64;
-  const uint64_t nbk = (kwords + leco::kItemsPerBlock - 1) / leco::kItemsPerBlock;
-  const uint64_t nchunks0 = (m + leco::kMergeChunk - 1) / leco::kMergeChunk;
+  const uint64_t nbk = (kwords + leco::kKeepWords - 1) / leco::kKeepWords;
+  const uint64_t nchunks0 = chunks_bound(m, n);
   if (!buf.alloc(&starts, m + 1) || !buf.alloc(&starts2, m + 1) || !buf.alloc(&cost, m) ||
       !buf.alloc(&cost2, m) || !buf.alloc(&pair, m) || !buf.alloc(&pair2, m) ||
       !buf.alloc(&old, m) || !buf.alloc(&changed, m) || !buf.alloc(&dirty, m) ||
       !buf.alloc(&keep, kwords) || !buf.alloc(&keep_counts, nbk) ||
       !buf.alloc(&mout, nchunks0) || !buf.alloc(&hulls, nchunks0) || !buf.alloc(&psum, m) ||
-      !buf.alloc(&seen, nchunks0) || !buf.alloc(&walks, kRoundGroup))
+      !buf.alloc(&psum2, m) || !buf.alloc(&seen, nchunks0) || !buf.alloc(&lists, 2 * nchunks0) ||
+      !buf.alloc(&todo, kRoundGroup + 1))
     return pfail(ctx, LECO_ENOMEM, "partition: partition arrays");
   hipLaunchKernelGGL(leco::k_bitmap_emit, dim3(uint32_t(nb)), dim3(leco::kScanBlock), 0, stream,
                      reinterpret_cast<const uint64_t*>(bitmap), nwords, counts, starts);
@@ -1685,12 +2021,12 @@ leco_status leco_partition(leco_ctx* ctx, const void* col_dev, uint64_t n, leco_
   // merge passes
   const uint64_t grid_cap = uint64_t(ctx->num_cus) * 16;
   auto costs = [&](const uint64_t* s, uint64_t count, uint32_t span, const uint8_t* dirty,
-                   uint64_t* out) {
+                   uint64_t* out, leco::RangeSum* sums) {
     if (count == 0) return hipSuccess;
     const uint64_t gs = (count + leco::kEncBlock - 1) / leco::kEncBlock;
     hipLaunchKernelGGL(leco::k_costs_short, dim3(uint32_t(gs < grid_cap ? gs : grid_cap)),
                        dim3(leco::kEncBlock), 0, stream, col, w, s, count, span, prm->max_len,
-                       dirty, out);
+                       dirty, out, sums);
     hipError_t e0 = hipGetLastError();
     if (e0 != hipSuccess) return e0;
     // chunks of ranges: at least one per resident wavefront (k_costs) or
@@ -1704,72 +2040,71 @@ leco_status leco_partition(leco_ctx* ctx, const void* col_dev, uint64_t n, leco_
     const uint64_t gw = (chunks_w + leco::kEncWaves - 1) / leco::kEncWaves;
     hipLaunchKernelGGL(leco::k_costs, dim3(uint32_t(gw < grid_cap ? gw : grid_cap)),
                        dim3(leco::kEncBlock), 0, stream, col, w, s, count, span, prm->max_len,
-                       dirty, out, cw);
+                       dirty, out, sums, cw);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     const uint32_t cl = chunk_for(grid_cap);
     const uint64_t chunks_l = (count + cl - 1) / cl;
     const uint64_t gl = chunks_l < grid_cap ? chunks_l : grid_cap;
     hipLaunchKernelGGL(leco::k_costs_long, dim3(uint32_t(gl)), dim3(leco::kEncBlock), 0, stream,
-                       col, w, s, count, span, prm->max_len, dirty, out, cl);
+                       col, w, s, count, span, prm->max_len, dirty, out, sums, cl);
     return hipGetLastError();
   };
-  P_TRY(costs(starts, m, 1, nullptr, cost));
-  if (m >= 2) P_TRY(costs(starts, m - 1, 2, nullptr, pair));
+  P_TRY(costs(starts, m, 1, nullptr, cost, psum));
+  if (m >= 2) P_TRY(costs(starts, m - 1, 2, nullptr, pair, nullptr));
   for (uint64_t pass = 0; prm->max_passes == 0 || pass < prm->max_passes; ++pass) {
     if (m < 2) break;
     const uint64_t words = (m + 63) / 64;
-    const uint64_t nchunks = (m + leco::kMergeChunk - 1) / leco::kMergeChunk;
+    const uint32_t clog2 = chunk_log2(m, n);
+    const uint64_t nchunks = ((m - 1) >> clog2) + 1;
     P_TRY(hipMemsetAsync(keep, 0, 8 * words, stream));
-    const uint64_t gsum = (m + 64 * leco::kEncWaves - 1) / (64 * leco::kEncWaves);
-    hipLaunchKernelGGL(leco::k_part_sums, dim3(uint32_t(gsum < grid_cap ? gsum : grid_cap)),
-                       dim3(leco::kEncBlock), 0, stream, col, w, starts, m, psum);
+    hipLaunchKernelGGL(leco::k_merge_spec, dim3(uint32_t(nchunks)), dim3(leco::kWalk), 0, stream, col, w,
+                       starts, cost, pair, psum, m, prm->max_len, clog2, keep, mout, hulls, seen);
     P_TRY(hipGetLastError());
-    const uint32_t gch = uint32_t((nchunks + leco::kEncWaves - 1) / leco::kEncWaves);
-    hipLaunchKernelGGL(leco::k_merge_spec, dim3(gch), dim3(leco::kEncBlock), 0, stream, col, w,
-                       starts, cost, pair, psum, m, prm->max_len, keep, mout, hulls, seen);
-    P_TRY(hipGetLastError());
-    // fix-up rounds, parities 1, 0, 1, ..., until two in a row walk nothing;
-    // chunk r is right after round r, so nchunks rounds always suffice
-    const uint64_t half = (nchunks + 1) / 2;
-    const uint32_t ghalf = uint32_t((half + leco::kEncWaves - 1) / leco::kEncWaves);
-    for (uint64_t r0 = 0; nchunks > 1 && r0 < nchunks + 2 * kRoundGroup; r0 += kRoundGroup) {
-      P_TRY(hipMemsetAsync(walks, 0, 8 * kRoundGroup, stream));
-      for (int i = 0; i < kRoundGroup; ++i) {
-        hipLaunchKernelGGL(leco::k_merge_round, dim3(ghalf), dim3(leco::kEncBlock), 0, stream, col,
-                           w, starts, cost, pair, psum, m, prm->max_len, keep, mout, hulls, seen,
-                           nchunks, uint32_t((r0 + i + 1) & 1), walks + i);
+    // fix-up rounds until one leaves an empty list: chunk r is right after
+    // round r, so nchunks rounds always suffice
+    uint32_t left = 1;
+    for (uint64_t r0 = 0; nchunks > 1 && left && r0 < nchunks + 2; r0 += kRoundGroup) {
+      // todo[i] counts the entries of round r0 + i; the last one carries over
+      if (r0) P_TRY(hipMemcpyAsync(todo, todo + kRoundGroup, 4, hipMemcpyDeviceToDevice, stream));
+      P_TRY(hipMemsetAsync(todo + (r0 ? 1 : 0), 0, 4 * (kRoundGroup + (r0 ? 0 : 1)), stream));
+      for (uint64_t i = 0; i < kRoundGroup; ++i) {
+        const uint64_t r = r0 + i, all = (nchunks + 1) / 2;
+        const uint64_t g = r < 2 ? all : all < kRoundGrid ? all : kRoundGrid;
+        hipLaunchKernelGGL(leco::k_merge_round, dim3(uint32_t(g)), dim3(leco::kWalk), 0, stream, col, w,
+                           starts, cost, pair, psum, m, prm->max_len, clog2, keep, mout, hulls,
+                           seen, nchunks, r, lists, todo + i);
         P_TRY(hipGetLastError());
       }
-      unsigned long long nwalk[kRoundGroup];
-      P_TRY(hipMemcpyAsync(nwalk, walks, 8 * kRoundGroup, hipMemcpyDeviceToHost, stream));
+      P_TRY(hipMemcpyAsync(&left, todo + kRoundGroup, 4, hipMemcpyDeviceToHost, stream));
       P_TRY(hipStreamSynchronize(stream));
-      if (nwalk[kRoundGroup - 2] == 0 && nwalk[kRoundGroup - 1] == 0) break;
     }
-    const uint64_t blocks = (words + leco::kItemsPerBlock - 1) / leco::kItemsPerBlock;
-    hipLaunchKernelGGL(leco::k_keep_count, dim3(uint32_t(blocks)), dim3(leco::kScanBlock), 0,
-                       stream, keep, m, keep_counts);
+    const uint64_t blocks = (words + leco::kKeepWords - 1) / leco::kKeepWords;
+    hipLaunchKernelGGL(leco::k_keep_count, dim3(uint32_t(blocks)), dim3(64), 0, stream, keep, m,
+                       keep_counts);
     P_TRY(hipGetLastError());
     uint64_t m2 = 0;
     P_TRY(scan_counts(keep_counts, blocks, &m2, stream));
     if (m2 == m) break;  // the pass merged nothing
     hipLaunchKernelGGL(leco::k_keep_emit, dim3(uint32_t(blocks)), dim3(leco::kScanBlock), 0,
-                       stream, keep, m, keep_counts, starts, cost, starts2, cost2, changed, old);
+                       stream, keep, m, keep_counts, starts, cost, psum, starts2, cost2, psum2,
+                       changed, old);
     P_TRY(hipGetLastError());
     P_TRY(hipMemcpyAsync(starts2 + m2, &n, 8, hipMemcpyHostToDevice, stream));
-    // sizes of the partitions that absorbed others
-    P_TRY(costs(starts2, m2, 1, changed, cost2));
+    // sizes and summaries of the partitions that absorbed others
+    P_TRY(costs(starts2, m2, 1, changed, cost2, psum2));
     if (m2 >= 2) {
       // pair sizes for the next pass: reused, or sized where a merge happened
       hipLaunchKernelGGL(leco::k_pair_reuse, dim3(uint32_t((m2 - 1 + 255) / 256)), dim3(256), 0,
                          stream, m2, changed, old, pair, pair2, dirty);
       P_TRY(hipGetLastError());
-      P_TRY(costs(starts2, m2 - 1, 2, dirty, pair2));
+      P_TRY(costs(starts2, m2 - 1, 2, dirty, pair2, nullptr));
     }
     P_TRY(hipStreamSynchronize(stream));  // &n stays valid until the copy is done
     std::swap(starts, starts2);
     std::swap(cost, cost2);
     std::swap(pair, pair2);
+    std::swap(psum, psum2);
     m = m2;
   }
   *m_out = m;
