@@ -245,7 +245,8 @@ __device__ inline U128 join_split(U128 p) {
 }
 
 // Range of the least-squares residuals of kN register-held values, value k
-// at position t0 + k * kStride (positions from len on ignored).  When small
+// at position t0 + k * kStride (positions from len on ignored), over the
+// wavefront.  When small
 // (values below vmin + 2^30, every |floor(theta1 t)| below 2^30, the same
 // in every lane) each residual fits int32 and the range is taken in 32-bit
 // operations; otherwise in 64-bit ones with the full prediction.
@@ -264,8 +265,8 @@ __device__ __attribute__((always_inline)) inline void residual_range_regs(
         mx = rr > mx ? rr : mx;
       }
     }
-    rmin = mn;
-    rmax = mx;
+    rmin = wave_min(mn);
+    rmax = wave_max(mx);
   } else {
     rmin = INT64_MAX;
     rmax = INT64_MIN;
@@ -278,6 +279,7 @@ __device__ __attribute__((always_inline)) inline void residual_range_regs(
         rmax = rr > rmax ? rr : rmax;
       }
     }
+    wave_minmax_i64(rmin, rmax);
   }
 }
 
@@ -303,8 +305,7 @@ __device__ __attribute__((always_inline)) inline Model fit_wave_regs(const W (&v
     lo = v[k] < lo ? v[k] : lo;
     hi = v[k] > hi ? v[k] : hi;
   }
-  uint64_t vmin = lo, vmax = hi;
-  wave_minmax_u64(vmin, vmax);
+  const uint64_t vmin = wave_min(lo), vmax = wave_max(hi);
   const uint64_t range = vmax - vmin;
   Model md{vmin, vmin, 0.0, bitlen64(range), false, 0, range};
   if (len > 1 && !force_constant && range < (uint64_t(1) << 61)) {
@@ -331,7 +332,6 @@ __device__ __attribute__((always_inline)) inline Model fit_wave_regs(const W (&v
     const bool small = narrow && __dmul_rn(fabs(th), double(len)) < 1073741824.0;
     int64_t rmin, rmax;
     residual_range_regs<kR, 64>(v, lane, len, vmin, th, small, rmin, rmax);
-    wave_minmax_i64(rmin, rmax);
     choose_model(md, th, rmin, rmax);
   }
   return md;
@@ -370,6 +370,24 @@ __global__ __launch_bounds__(kEncBlock, kR == 16 ? 5 : 1) void k_fit_wave(const 
                        ? fit_wave<kR>(reinterpret_cast<const uint64_t*>(c.col) + start, len, c.force_constant)
                        : fit_wave<kR>(reinterpret_cast<const uint32_t*>(c.col) + start, len, c.force_constant);
   if (lane == 0) store_model(scr, P, md, len);
+}
+
+// Every thread receives the workgroup's min and max of int32 values.
+__device__ inline void block_minmax_i32(FitShared& sh, int32_t& mn, int32_t& mx) {
+  mn = wave_min(mn);
+  mx = wave_max(mx);
+  const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  if (lane == 0) {
+    sh.red[wave][0] = uint64_t(uint32_t(mn));
+    sh.red[wave][1] = uint64_t(uint32_t(mx));
+  }
+  __syncthreads();
+#pragma unroll
+  for (int w = 0; w < kEncWaves; ++w) {
+    mn = min(mn, int32_t(uint32_t(sh.red[w][0])));
+    mx = max(mx, int32_t(uint32_t(sh.red[w][1])));
+  }
+  __syncthreads();
 }
 
 // ---- fit: one workgroup per partition ----------------------------------------------
@@ -444,8 +462,9 @@ __device__ __attribute__((always_inline)) inline Model fit_block(FitShared& sh, 
         rmin = rr < rmin ? rr : rmin;
         rmax = rr > rmax ? rr : rmax;
       }
+      wave_minmax_i64(rmin, rmax);
     }
-    block_minmax_i64(sh, rmin, rmax);
+    block_join_i64(sh, rmin, rmax);
     choose_model(md, th, rmin, rmax);
   }
   return md;
@@ -682,6 +701,25 @@ __device__ inline double i128_to_double(__int128 x) {
   return i128_to_f64(U128{uint64_t(x), uint64_t(static_cast<unsigned __int128>(x) >> 64)});
 }
 
+// The norms sum g_k(t)^2 over t < n have closed forms (the Gram
+// polynomials' squared norms, exact integers): (n-1)n(n+1)/3,
+// (n-2)...(n+2)/5 and (n-3)...(n+3)/7, below 2^84 for n <= 4096.  Each is
+// a run of 3, 5 or 7 consecutive integers, one of which the divisor
+// divides: that factor is divided first, so no 128-bit division is needed.
+__device__ inline __int128 gram_norm(int64_t n, int64_t half, int64_t d) {
+  __int128 q = 1;
+  bool divided = false;
+  for (int64_t f = n - half; f <= n + half; ++f) {
+    int64_t x = f;
+    if (!divided && x % d == 0) {
+      x /= d;
+      divided = true;
+    }
+    q *= x;
+  }
+  return q;
+}
+
 // The degree-2 and degree-3 least-squares polynomials of a partition of
 // 3 <= n <= 4096 values of range below 2^50, in the Gram basis:
 // c_k = fl(S_k) / fl(Q_k), S_k = sum y_t g_k(t) exact in int128 and
@@ -734,25 +772,7 @@ __device__ __attribute__((always_inline)) inline void poly_stage(
   const __int128 S1 = 2 * m1 - a * m0;
   const __int128 S2 = 6 * m2 - 6 * a * m1 + e2 * m0;
   const __int128 S3 = 20 * m3 - 30 * a * m2 + k3 * m1 - e3 * m0;
-  // The norms sum g_k(t)^2 over t < n have closed forms (the Gram
-  // polynomials' squared norms, exact integers): (n-1)n(n+1)/3,
-  // (n-2)...(n+2)/5 and (n-3)...(n+3)/7, below 2^84 for n <= 4096.  Each is
-  // a run of 3, 5 or 7 consecutive integers, one of which the divisor
-  // divides: that factor is divided first, so no 128-bit division is needed.
-  auto norm = [](int64_t nv, int64_t half, int64_t d) {
-    __int128 q = 1;
-    bool divided = false;
-    for (int64_t f = nv - half; f <= nv + half; ++f) {
-      int64_t x = f;
-      if (!divided && x % d == 0) {
-        x /= d;
-        divided = true;
-      }
-      q *= x;
-    }
-    return q;
-  };
-  const __int128 Q1 = norm(N, 1, 3), Q2 = norm(N, 2, 5), Q3 = norm(N, 3, 7);
+  const __int128 Q1 = gram_norm(N, 1, 3), Q2 = gram_norm(N, 2, 5), Q3 = gram_norm(N, 3, 7);
   double c[3];
   const __int128 Sk[3] = {S1, S2, S3}, Q[3] = {Q1, Q2, Q3};
 #pragma unroll
@@ -803,16 +823,220 @@ __device__ inline unsigned __int128 from_u128(U128 x) {
   return (static_cast<unsigned __int128>(x.hi) << 64) | x.lo;
 }
 
-// The least-squares model of fit_block, then the polynomial stage, by the
-// whole workgroup.
+// Partitions whose range is below this take the narrow polynomial fit.
+constexpr uint64_t kPolyNarrowRange = uint64_t(1) << 28;
+
+// An integer below 2^52 held in binary64.
+__device__ inline uint64_t f64_to_u64(double x) {
+  return uint64_t(__double_as_longlong(x + 4503599627370496.0)) & ((uint64_t(1) << 52) - 1);
+}
+
+// The nearest int32 of an integer or infinity (v_cvt_i32_f64 saturates).
+__device__ inline int32_t f64_to_i32(double x) {
+  return static_cast<int32_t>(fmin(fmax(x, -2147483648.0), 2147483647.0));
+}
+
+__device__ inline uint64_t uniform64(uint64_t x) {
+  const uint32_t lo = uint32_t(__builtin_amdgcn_readfirstlane(int(uint32_t(x))));
+  const uint32_t hi = uint32_t(__builtin_amdgcn_readfirstlane(int(uint32_t(x >> 32))));
+  return (uint64_t(hi) << 32) | lo;
+}
+
+// The line and both polynomials of a partition of 3 <= n <= kT kR values of
+// range below kPolyNarrowRange, in one pass for the sums and one for the
+// residuals, by a group of kT threads; value k of thread tid, at position tid
+// + kT k, is the offset y[k] (0 from n on).  The same exact sums,
+// slopes, predictions and choice as fit_wave / fit_block and poly_stage:
+//   sums       the T_i of poly_stage reach 2^28 (0^3 + ... + 15^3) < 2^42,
+//              exact in binary64; the line's sums are M_0 and M_1; M_0 .. M_2 fit 64 bits (2^28 2^36), M_3
+//              takes 128;
+//   residuals  y and every |floor| are below 2^52, so their differences and
+//              extremes are exact in binary64, line, degree 2 and degree 3
+//              side by side (25 instructions a value).
+// Bound by vector issue: 1260 vector instructions a wavefront of 1000 values,
+// 205 of the kernel's 270 us for 1e8.  Against integer sums and residuals in
+// three passes, encode of 1e8 values: two sines u32 L 1000 575 -> 427 us,
+// sorted keys u64 L 1000 590 -> 440, cubic blocks u64 L 2000 568 -> 484 and
+// L 4096 (a workgroup each) 692 -> 458.
+template <int kT, int kR, class Group>
+__device__ __attribute__((always_inline)) inline Model fit_poly_narrow(
+    const uint32_t (&y0)[kR], uint32_t tid, uint32_t n, uint64_t vmin, uint64_t range, Group& group,
+    uint32_t& kind, double& c2_out, double& c3_out) {
+  constexpr int kC = kR < 16 ? kR : 16;  // registers per chunk, as in poly_stage
+  static_assert(kR % kC == 0, "whole chunks");
+  using u128 = unsigned __int128;
+  uint64_t M0 = 0, M1 = 0, M2 = 0;
+  u128 M3 = 0;
+#pragma unroll
+  for (int h = 0; h < kR / kC; ++h) {
+    // A_i = sum_j y_j C(j + i, i), by running sums from the last value down:
+    // four additions a value and no constants
+    double A0 = 0.0, A1 = 0.0, A2 = 0.0, A3 = 0.0;
+#pragma unroll
+    for (int j = kC - 1; j >= 0; --j) {
+      A0 += double(y0[h * kC + j]);
+      A1 += A0;
+      A2 += A1;
+      A3 += A2;
+    }
+    const uint64_t T0 = f64_to_u64(A0), T1 = f64_to_u64(A1 - A0),
+                   T2 = f64_to_u64(2.0 * A2 - 3.0 * A1 + A0),
+                   T3 = f64_to_u64(6.0 * A3 - 12.0 * A2 + 7.0 * A1 - A0);
+    const uint64_t u = tid + uint64_t(h) * kC * kT, S = kT;
+    M0 += T0;
+    M1 += T0 * u + T1 * S;
+    M2 += T0 * (u * u) + T1 * (2 * u * S) + T2 * (S * S);
+    M3 += u128(T0) * (u * u * u) + u128(T1) * (3 * u * u * S) + u128(T2 * (3 * u * S * S)) +
+          u128(T3) * (S * S * S);
+  }
+  group.sum(M0, M1, M2, M3);
+  const int64_t N = n, a = N - 1;
+  const int64_t k3 = 12 * N * N - 30 * N + 22, e2 = a * (N - 2), e3 = a * (N - 2) * (N - 3);
+  // S1 < 2^54 and |S2| < 2^28 n^3 / 4 < 2^62 (the Gram polynomial of degree 2
+  // is n^2 times a Legendre-like one) in 64-bit arithmetic modulo 2^64
+  const int64_t S1 = int64_t(2 * M1 - uint64_t(a) * M0);
+  const int64_t S2 = int64_t(6 * M2 - uint64_t(6 * a) * M1 + uint64_t(e2) * M0);
+  const __int128 S3 = 20 * __int128(M3) - 30 * a * __int128(M2) + k3 * __int128(M1) - e3 * __int128(M0);
+  // the norms of gram_norm: n (n^2 - 1) / 3, n (n^2 - 1)(n^2 - 4) / 5 < 2^60
+  // and that product times (n^2 - 9) / 7, of which 7 divides one factor
+  const uint64_t n2 = uint64_t(N) * uint64_t(N), w1 = uint64_t(N) * (n2 - 1), w2 = w1 * (n2 - 4);
+  const bool in_w2 = w2 % 7 == 0;
+  const __int128 Q3 = n < 4 ? 0
+                            : __int128(u128(in_w2 ? w2 / 7 : w2) * (in_w2 ? n2 - 9 : (n2 - 9) / 7));
+  double c[3];
+  c[0] = i128_to_double(S1) / u64_to_f64(w1 / 3);
+  c[1] = i128_to_double(S2) / u64_to_f64(w2 / 5);
+  c[2] = Q3 != 0 ? i128_to_double(S3) / i128_to_double(Q3) : 0.0;
+#pragma unroll
+  for (int k = 0; k < 3; ++k)
+    if (c[k] == 0.0) c[k] = 0.0;  // +0.0, never -0.0
+  const double th = ls_slope(n, U128{M0, 0}, U128{M1, 0});
+  // an infinity stays only in threads without values: far outside int32
+  double mx[3], mn[3];
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    mx[k] = -__builtin_inf();
+    mn[k] = __builtin_inf();
+  }
+  GramWalk gw;
+  gw.start(tid, n, kT);
+  double td = double(tid);
+#pragma unroll
+  for (int k = 0; k < kR; ++k) {
+    // converted again, not kept in twice the registers since the sums
+    uint32_t yk = y0[k];
+    asm volatile("" : "+v"(yk));
+    // past the end (of the partition's last rounds): NaN, which maximum and
+    // minimum pass over
+    double y = double(yk);
+    if (uint32_t(kT * (k + 1)) > n) y = tid + kT * k < n ? y : __builtin_nan("");
+    const double s2 = __dadd_rn(__dmul_rn(c[0], gw.g1), __dmul_rn(c[1], gw.g2));
+    const double s3 = __dadd_rn(s2, __dmul_rn(c[2], gw.g3));
+    const double r[3] = {y - floor(__dmul_rn(th, td)), y - floor(s2), y - floor(s3)};
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+      mx[q] = fmax(mx[q], r[q]);
+      mn[q] = fmin(mn[q], r[q]);
+    }
+    gw.next();
+    td += double(kT);
+  }
+  // Residuals are below 2^31 in magnitude (y < 2^28; a least-squares
+  // prediction, without its constant term, is below five times that), so
+  // they are reduced as int32; the conversion saturates infinities.
+  int32_t hi[3], lo[3];
+#pragma unroll
+  for (int q = 0; q < 3; ++q) {
+    hi[q] = f64_to_i32(mx[q]);
+    lo[q] = f64_to_i32(mn[q]);
+    group.maxmin(hi[q], lo[q]);
+  }
+  Model md{vmin, vmin, 0.0, bitlen64(range), false, 0, range};
+  choose_model(md, th, lo[0], hi[0]);
+  kind = 0;
+  c2_out = c3_out = 0.0;
+#pragma unroll
+  for (int deg = 2; deg <= 3; ++deg) {
+    if (deg == 3 && n < 4) break;
+    const int64_t rmin = lo[deg - 1], rmax = hi[deg - 1];
+    const uint32_t b = bitlen64(uint64_t(rmax) - uint64_t(rmin));
+    if (b < md.bits) {
+      md.linear = true;
+      md.theta1 = c[0];
+      md.base = md.vmin + uint64_t(rmin);
+      md.bits = b;
+      md.rmin = rmin;
+      kind = 1;
+      c2_out = c[1];
+      c3_out = deg == 3 ? c[2] : 0.0;
+    }
+  }
+  return md;
+}
+
+// The group's reductions for fit_poly_narrow.
+struct PolyWave {
+  // m3 < 2^76 in two halves of 40 bits, which 64 lanes cannot overflow
+  __device__ void sum(uint64_t& m0, uint64_t& m1, uint64_t& m2, unsigned __int128& m3) {
+    m0 = wave_sum_u64(m0);
+    m1 = wave_sum_u64(m1);
+    m2 = wave_sum_u64(m2);
+    const uint64_t lo = wave_sum_u64(uint64_t(m3) & ((uint64_t(1) << 40) - 1));
+    m3 = (static_cast<unsigned __int128>(wave_sum_u64(uint64_t(m3 >> 40))) << 40) + lo;
+  }
+  __device__ void maxmin(int32_t& mx, int32_t& mn) {
+    mx = wave_max(mx);
+    mn = wave_min(mn);
+  }
+};
+
+struct PolyBlock {
+  FitShared& fs;
+  __device__ void sum(uint64_t& m0, uint64_t& m1, uint64_t& m2, unsigned __int128& m3) {
+    block_sum_u64x2(fs, m0, m1);
+    U128 x = to_u128(m3), z{m2, 0};
+    block_sum_u128x2(fs, x, z);
+    m0 = uniform64(m0);  // every wavefront's, for the scalar unit
+    m1 = uniform64(m1);
+    m2 = uniform64(z.lo);
+    m3 = (static_cast<unsigned __int128>(uniform64(x.hi)) << 64) | uniform64(x.lo);
+  }
+  __device__ void maxmin(int32_t& mx, int32_t& mn) { block_minmax_i32(fs, mn, mx); }
+};
+
+// The least-squares line and the polynomials, by the whole workgroup: in
+// binary64 for narrow partitions, else the model of fit_block and then
+// poly_stage.
 template <class T>
 __device__ __attribute__((always_inline)) inline Model fit_poly(FitShared& fs, const T* src, uint64_t len, bool force_constant,
                                  uint32_t& kind, double& c2_out, double& c3_out) {
-  Model md = fit_block(fs, src, len, force_constant);
+  const uint32_t tid = threadIdx.x;
   kind = 0;
   c2_out = c3_out = 0.0;
+  if (!force_constant && len >= 3 && len <= kEncRegLen) {
+    T v[kEncRegs];
+#pragma unroll
+    for (int k = 0; k < kEncRegs; ++k) v[k] = T(load_clamped(src, tid + k * kEncBlock, len));
+    T lo = v[0], hi = v[0];
+#pragma unroll
+    for (int k = 1; k < kEncRegs; ++k) {
+      lo = v[k] < lo ? v[k] : lo;
+      hi = v[k] > hi ? v[k] : hi;
+    }
+    uint64_t vmin = lo, vmax = hi;
+    block_minmax_u64(fs, vmin, vmax);
+    if (vmax - vmin < kPolyNarrowRange) {
+      uint32_t y[kEncRegs];
+#pragma unroll
+      for (int k = 0; k < kEncRegs; ++k)
+        y[k] = tid + k * kEncBlock < len ? uint32_t(v[k]) - uint32_t(vmin) : 0u;
+      PolyBlock g{fs};
+      return fit_poly_narrow<kEncBlock, kEncRegs>(y, tid, uint32_t(len), vmin, vmax - vmin, g, kind,
+                                                  c2_out, c3_out);
+    }
+  }
+  Model md = fit_block(fs, src, len, force_constant);
   if (force_constant || len < 3 || len > kPolyMaxLen || md.range >= kPolyMaxRange) return md;
-  const uint32_t tid = threadIdx.x;
   uint64_t y[kEncRegs];
 #pragma unroll
   for (int k = 0; k < kEncRegs; ++k) y[k] = load_clamped(src, tid + k * kEncBlock, len) - md.vmin;
@@ -833,17 +1057,37 @@ __device__ __attribute__((always_inline)) inline Model fit_poly(FitShared& fs, c
   return md;
 }
 
-// The same by one wavefront, for partitions of at most 64 kR values: the
-// model of fit_wave, then the polynomial stage with wavefront reductions (no
+// The same by one wavefront, for partitions of at most 64 kR values (no
 // barrier).
 template <int kR, class T>
 __device__ __attribute__((always_inline)) inline Model fit_poly_wave(const T* src, uint64_t len, bool force_constant,
                                       uint32_t& kind, double& c2_out, double& c3_out) {
-  Model md = fit_wave<kR>(src, len, force_constant);
+  const uint32_t lane = threadIdx.x & 63;
   kind = 0;
   c2_out = c3_out = 0.0;
+  T v[kR];
+#pragma unroll
+  for (int k = 0; k < kR; ++k) v[k] = T(load_clamped(src, lane + 64 * k, len));
+  if (!force_constant && len >= 3) {
+    T lo = v[0], hi = v[0];
+#pragma unroll
+    for (int k = 1; k < kR; ++k) {
+      lo = v[k] < lo ? v[k] : lo;
+      hi = v[k] > hi ? v[k] : hi;
+    }
+    const uint64_t vmin = wave_min(lo), vmax = wave_max(hi);
+    if (vmax - vmin < kPolyNarrowRange) {
+      uint32_t y[kR];
+#pragma unroll
+      for (int k = 0; k < kR; ++k)
+        y[k] = lane + 64 * k < len ? uint32_t(v[k]) - uint32_t(vmin) : 0u;
+      PolyWave g;
+      return fit_poly_narrow<64, kR>(y, lane, uint32_t(len), vmin, vmax - vmin, g, kind, c2_out,
+                                     c3_out);
+    }
+  }
+  Model md = fit_wave<kR>(src, len, force_constant);
   if (force_constant || len < 3 || md.range >= kPolyMaxRange) return md;
-  const uint32_t lane = threadIdx.x & 63;
   uint64_t y[kR];
 #pragma unroll
   for (int k = 0; k < kR; ++k) y[k] = load_clamped(src, lane + 64 * k, len) - md.vmin;
@@ -893,10 +1137,10 @@ __global__ __launch_bounds__(kEncBlock) void k_fit_poly(const EncColumn* __restr
   }
 }
 
-// Held to four waves per SIMD at 16 values per lane and three at 32 (128
-// and 168 VGPRs instead of 139 and 181, some spilled): polynomial encode
-// of 1e8 u32 two-sine values 0.67 -> 0.61 ms, of 2e8 u64 cubic blocks
-// 1.26 -> 1.17 ms.
+// Held to four waves per SIMD at 16 values per lane and three at 32: the
+// narrow fit takes 84 and 134 VGPRs by itself, the wide one beside it 127 and
+// 168 (some spilled).  Held to five and four, encode of 1e8 two-sine values
+// 455 -> 515 us, of cubic blocks 470 -> 575.
 template <int kR>
 __global__ __launch_bounds__(kEncBlock, kR == 16 ? 4 : 3) void k_fit_poly_wave(const EncColumn* __restrict__ cols,
                                                             uint64_t ncols, EncColumn single,
@@ -1192,27 +1436,6 @@ __device__ inline uint64_t lb_exclusive(const uint64_t* st, uint64_t first, uint
   return acc;
 }
 
-// Every thread receives the workgroup's min and max of int32 values.
-__device__ inline void block_minmax_i32(FitShared& sh, int32_t& mn, int32_t& mx) {
-#pragma unroll
-  for (int m = 32; m > 0; m >>= 1) {
-    mn = min(mn, __shfl_xor(mn, m, 64));
-    mx = max(mx, __shfl_xor(mx, m, 64));
-  }
-  const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  if (lane == 0) {
-    sh.red[wave][0] = uint64_t(uint32_t(mn));
-    sh.red[wave][1] = uint64_t(uint32_t(mx));
-  }
-  __syncthreads();
-#pragma unroll
-  for (int w = 0; w < kEncWaves; ++w) {
-    mn = min(mn, int32_t(uint32_t(sh.red[w][0])));
-    mx = max(mx, int32_t(uint32_t(sh.red[w][1])));
-  }
-  __syncthreads();
-}
-
 // The model of a partition held in registers as described above.  When
 // the residuals v - vmin - floor(theta1 t) fit int32 (`small`), r32 keeps
 // them for the packing.
@@ -1316,19 +1539,19 @@ __device__ __attribute__((always_inline)) inline void encode_fused_part(
   uint64_t v[kEncRegs];
   const bool full = len == kEncRegLen;  // no load clamped, no position masked
   if (c.dtype == 8) {
-    const auto src = global_ptr(reinterpret_cast<const uint64_t*>(c.col) + start);
+    const uint64_t* src = reinterpret_cast<const uint64_t*>(c.col) + start;
     if (full) {
 #pragma unroll
-      for (int k = 0; k < kEncRegs; ++k) v[k] = src[t0 + 64 * k];
+      for (int k = 0; k < kEncRegs; ++k) v[k] = global_ptr(src)[t0 + 64 * k];
     } else {
 #pragma unroll
       for (int k = 0; k < kEncRegs; ++k) v[k] = load_clamped(src, t0 + 64 * k, len);
     }
   } else {
-    const auto src = global_ptr(reinterpret_cast<const uint32_t*>(c.col) + start);
+    const uint32_t* src = reinterpret_cast<const uint32_t*>(c.col) + start;
     if (full) {
 #pragma unroll
-      for (int k = 0; k < kEncRegs; ++k) v[k] = src[t0 + 64 * k];
+      for (int k = 0; k < kEncRegs; ++k) v[k] = global_ptr(src)[t0 + 64 * k];
     } else {
 #pragma unroll
       for (int k = 0; k < kEncRegs; ++k) v[k] = load_clamped(src, t0 + 64 * k, len);

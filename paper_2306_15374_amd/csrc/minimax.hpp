@@ -115,54 +115,15 @@ __device__ __host__ constexpr uint64_t strip_f64_range(uint32_t log2s) {
 
 // ---- group reductions of a (largest, smallest) pair -------------------------------
 
-template <int kCtrl, int kRowMask>
-__device__ inline double dpp_f64(double x) {
-  const uint64_t b = uint64_t(__double_as_longlong(x));
-  const int lo = int(uint32_t(b)), hi = int(uint32_t(b >> 32));
-  const uint32_t l = uint32_t(__builtin_amdgcn_update_dpp(lo, lo, kCtrl, kRowMask, 0xf, false));
-  const uint32_t h = uint32_t(__builtin_amdgcn_update_dpp(hi, hi, kCtrl, kRowMask, 0xf, false));
-  return __longlong_as_double(static_cast<long long>((uint64_t(h) << 32) | l));
-}
-
-template <int kCtrl, int kRowMask>
-__device__ inline void dpp_step(double& mx, double& mn) {
-  mx = fmax(mx, dpp_f64<kCtrl, kRowMask>(mx));
-  mn = fmin(mn, dpp_f64<kCtrl, kRowMask>(mn));
-}
-
-__device__ inline double lane63(double x) {
-  const uint64_t b = uint64_t(__double_as_longlong(x));
-  const uint32_t lo = uint32_t(__builtin_amdgcn_readlane(int(uint32_t(b)), 63));
-  const uint32_t hi = uint32_t(__builtin_amdgcn_readlane(int(uint32_t(b >> 32)), 63));
-  return __longlong_as_double(static_cast<long long>((uint64_t(hi) << 32) | lo));
-}
-
-// Largest mx and smallest mn of a wavefront, by lane permutations within the
-// vector unit: pairs, quads, half rows and rows of 16, then across rows.
+// Largest mx and smallest mn of a wavefront (maxNum / minNum: NaN passes).
 __device__ inline void wave_maxmin(double& mx, double& mn) {
-  dpp_step<0xB1, 0xf>(mx, mn);   // quad_perm [1,0,3,2]
-  dpp_step<0x4E, 0xf>(mx, mn);   // quad_perm [2,3,0,1]
-  dpp_step<0x141, 0xf>(mx, mn);  // row_half_mirror
-  dpp_step<0x140, 0xf>(mx, mn);  // row_mirror
-  dpp_step<0x142, 0xa>(mx, mn);  // row_bcast15 into rows 1 and 3
-  dpp_step<0x143, 0xc>(mx, mn);  // row_bcast31 into rows 2 and 3
-  mx = lane63(mx);
-  mn = lane63(mn);
-}
-
-__device__ inline __int128 shfl_xor128(__int128 x, int m) {
-  const uint64_t lo = shfl_xor64(uint64_t(x), m);
-  const uint64_t hi = shfl_xor64(uint64_t(static_cast<unsigned __int128>(x) >> 64), m);
-  return __int128((static_cast<unsigned __int128>(hi) << 64) | lo);
+  mx = wave_reduce<true>(mx, [](double a, double b) { return fmax(a, b); });
+  mn = wave_reduce<true>(mn, [](double a, double b) { return fmin(a, b); });
 }
 
 __device__ inline void wave_maxmin(__int128& mx, __int128& mn) {
-#pragma unroll
-  for (int m = 32; m > 0; m >>= 1) {
-    const __int128 a = shfl_xor128(mx, m), b = shfl_xor128(mn, m);
-    mx = a > mx ? a : mx;
-    mn = b < mn ? b : mn;
-  }
+  mx = wave_max(mx);
+  mn = wave_min(mn);
 }
 
 // LDS of a workgroup's reductions, in two halves used in turn: one barrier
