@@ -39,6 +39,7 @@ struct BatchSink {
   // polynomial predictions by forward differences (decode_range_poly) only
   // when storing alone, for the same reason
   static constexpr bool kGramWalk = kStore && !kFilter;
+  static constexpr bool kAlign = kStore && !kFilter;
   OutT* out;
   FilterSink f;
   __device__ bool visit_segment(const Part& p, uint32_t t0, uint32_t t1) {

@@ -167,6 +167,21 @@ __device__ inline void decode_values(const Part& p, uint32_t c0, uint32_t c1, in
   }
 }
 
+// Decodes the n < kWave values from t = c0 on, whatever the width and slope.
+template <class Sink>
+__device__ inline void decode_few(const Part& p, uint32_t c0, uint32_t n, int64_t qoff,
+                                  const uint32_t* stage, Sink& sink) {
+  const uint32_t lane = lane_id(), b = p.bits, t = c0 + lane;
+  if (lane >= n) return;
+  uint64_t u = 0;
+  if (b != 0) {
+    const uint32_t q = uint32_t(qoff + int64_t(b) * t);
+    u = b <= 32 ? uint64_t(extract32(stage, q, b == 32 ? ~0u : (1u << b) - 1))
+                : extract64(stage, q, b >= 64 ? ~0u : (1u << (b - 32)) - 1);
+  }
+  sink.put(p.start + t, p.base + uint64_t(predict(p.theta1, t)) + u);
+}
+
 // Decodes the piece [g0, g0 + span) whose records are in `table` and whose
 // residual words are staged, 64 consecutive values per round whatever the
 // partition boundaries: bit x of `starts` marks a partition start at g0 + x
@@ -418,7 +433,17 @@ __device__ bool decode_tile(const uint8_t* __restrict__ blob, const Header& h, u
           const int64_t qoff = int32_t(__builtin_amdgcn_readfirstlane(r.qoff));
           const uint64_t s0 = g0 > p.start ? g0 : p.start;
           const uint64_t s1 = ge < p.start + p.len ? ge : p.start + p.len;
-          decode_values(p, uint32_t(s0 - p.start), uint32_t(s1 - p.start), qoff, stage, sink);
+          // the values before the next multiple of kWave on their own, so
+          // that the rounds after them write whole cache lines (1e8 u32 values
+          // at L = 1000: 115 -> 94 us, L = 333: 147 -> 112; L = 1024 80)
+          uint64_t c = s0;
+          if (Sink::kAlign && (uint32_t(s0) & (kWave - 1))) {
+            c = (s0 | (kWave - 1)) + 1;
+            if (c > s1) c = s1;
+            decode_few(p, uint32_t(s0 - p.start), uint32_t(c - s0), qoff, stage, sink);
+            if (c == s1) continue;
+          }
+          decode_values(p, uint32_t(c - p.start), uint32_t(s1 - p.start), qoff, stage, sink);
         }
       }
       wave_sync();
@@ -484,6 +509,7 @@ struct StoreSink {
   static constexpr bool kWholeTile = true;
   static constexpr bool kFlat = kFlatRuns;
   static constexpr bool kGramWalk = true;
+  static constexpr bool kAlign = true;
   OutT* out;
   uint64_t origin;
   __device__ bool visit_segment(const Part&, uint32_t, uint32_t) { return true; }
@@ -659,6 +685,7 @@ struct FilterSink {
   static constexpr bool kWholeTile = false;  // may skip segments by their model bounds
   static constexpr bool kFlat = false;
   static constexpr bool kGramWalk = false;
+  static constexpr bool kAlign = false;
   uint64_t lo, hi;
   uint64_t sum_lo, sum_hi, count;
   int prune;
