@@ -283,10 +283,25 @@ hipError_t launch_decode(leco_ctx* ctx, const void* blob, uint64_t blob_bytes, v
   const uint64_t e = all ? out_cap : end;
   // the total count is not known on the host: out_cap (decode_all) or end
   // (range) stands in for it
-  const uint32_t tl = pick_tile_log2(ctx->tune, blob_bytes, e);
+  uint32_t tl = pick_tile_log2(ctx->tune, blob_bytes, e);
   if (!all && e <= begin) return hipSuccess;
   // decode_all always launches, so an empty output still checks n <= 0
-  const uint64_t tiles = e <= begin ? 1 : ((e - 1) >> tl) - (begin >> tl) + 1;
+  const auto tiles_of = [&](uint32_t l) { return e <= begin ? 1 : ((e - 1) >> l) - (begin >> l) + 1; };
+  if (ctx->tune.tile_log2 == 0) {
+    // Few workgroups: the largest tile that gives every CU three of them,
+    // down to 2^11 values.  decode_all of 1e6 values took 9.0 us in 61 tiles
+    // (constant runs 13.7) and takes 7.2, the rate of launches, in 489; 1e7
+    // values 18.7 in 610 and 17.7 (runs 14.7) in 1220; 4e6 values 9.4 in 976,
+    // but 10.7 in 1953, at about 3 ns for each workgroup more.
+    while (tl > 11 && tiles_of(tl) < uint64_t(3) * ctx->num_cus) --tl;
+    // Many: no tile below 2^10, which holds its words whatever their width
+    // (the estimate counts records too, and for a range near the start of a
+    // long column all of its bytes): 2e7 values in partitions of 2 took
+    // 129 us and take 103.  A single partition per value wants the small
+    // tiles as long as they fit the chip: 2e5 values 7.3 us, 8.9 in 2^10.
+    while (tl < 10 && tiles_of(tl) > uint64_t(8) * ctx->num_cus) ++tl;
+  }
+  const uint64_t tiles = tiles_of(tl);
   const uint64_t cap = uint64_t(ctx->num_cus) * ctx->tune.decode_blocks_per_cu;
   uint64_t grid = (cap == 0 || tiles < cap) ? tiles : cap;
   if (ctx->tune.xcd_remap) grid = (grid + 7) & ~uint64_t(7);
