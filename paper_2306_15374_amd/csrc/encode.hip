@@ -143,7 +143,7 @@ __device__ inline void finish_column(const EncColumn& c, uint64_t total_words, i
   const bool variable = c.fixed_len == 0;
   const uint64_t meta_end = kHeaderBytes + kRecordBytes * c.m + (variable ? 8 * (c.m + 1) : 0);
   if (variable) reinterpret_cast<uint64_t*>(c.blob + kHeaderBytes + kRecordBytes * c.m)[c.m] = c.n;
-  // padding around the coefficient section, which k_records fills
+  // padding around the coefficient section, which k_layout fills
   const uint64_t coef = c.regressor == 2 ? align16(meta_end) : c.words_off;
   const uint64_t coef_end = c.regressor == 2 ? coef + 16 * c.m : c.words_off;
   for (uint64_t i = meta_end; i < coef; ++i) c.blob[i] = 0;
@@ -1172,12 +1172,13 @@ __global__ __launch_bounds__(kEncBlock, kR == 16 ? 4 : 3) void k_fit_poly_wave(c
   }
 }
 
-// ---- scan: word offsets ------------------------------------------------------------
+// ---- layout: word offsets and records -----------------------------------------------
 
-// Exclusive prefix sum of x over the workgroup's threads; *total receives
-// the workgroup sum.
-__device__ inline uint64_t block_exclusive_scan_u64(uint64_t x, uint64_t* total) {
-  __shared__ uint64_t wsum[kEncWaves];
+// Exclusive prefix sum of x over a workgroup of 64 W threads, with the
+// workgroup's sum in *total.  wsum[W] is shared; a barrier has to lie between
+// two calls.
+template <int W>
+__device__ inline uint64_t block_exclusive_scan_u64(uint64_t* wsum, uint64_t x, uint64_t* total) {
   const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   uint64_t inc = x;
 #pragma unroll
@@ -1189,92 +1190,143 @@ __device__ inline uint64_t block_exclusive_scan_u64(uint64_t x, uint64_t* total)
   __syncthreads();
   uint64_t before = 0, all = 0;
 #pragma unroll
-  for (int w = 0; w < kEncWaves; ++w) {
+  for (int w = 0; w < W; ++w) {
     if (w < int(wave)) before += wsum[w];
     all += wsum[w];
   }
-  __syncthreads();
   *total = all;
   return before + inc - x;
 }
 
 // bsum[g] = word count of partitions [g * 1024, (g + 1) * 1024).
 __global__ __launch_bounds__(kEncBlock) void k_scan_sums(EncScratch scr, uint64_t nparts) {
-  const uint64_t p0 = uint64_t(blockIdx.x) * kScanItems + threadIdx.x * 4;
+  __shared__ uint64_t wsum[kEncWaves];
+  const uint64_t p0 = uint64_t(blockIdx.x) * kScanItems + threadIdx.x;
   uint64_t x = 0;
 #pragma unroll
-  for (int q = 0; q < 4; ++q)
+  for (uint32_t q = 0; q < kScanItems; q += kEncBlock)
     if (p0 + q < nparts) x += scr.nwords[p0 + q];
   uint64_t total;
-  block_exclusive_scan_u64(x, &total);
+  block_exclusive_scan_u64<kEncWaves>(wsum, x, &total);
   if (threadIdx.x == 0) scr.bsum[blockIdx.x] = total;
 }
 
 // Exclusive prefix of bsum[0, ng) in place, by one workgroup.
-__global__ __launch_bounds__(kEncBlock) void k_scan_top(EncScratch scr, uint64_t ng) {
+__global__ __launch_bounds__(kScanItems) void k_scan_top(EncScratch scr, uint64_t ng) {
+  __shared__ uint64_t wsum[kScanItems / 64];
   uint64_t carry = 0;
-  for (uint64_t g0 = 0; g0 < ng; g0 += kEncBlock) {
+  for (uint64_t g0 = 0; g0 < ng; g0 += kScanItems) {
     const uint64_t g = g0 + threadIdx.x;
     const uint64_t x = g < ng ? scr.bsum[g] : 0;
     uint64_t total;
-    const uint64_t ex = block_exclusive_scan_u64(x, &total);
+    const uint64_t ex = block_exclusive_scan_u64<kScanItems / 64>(wsum, x, &total);
+    __syncthreads();
     if (g < ng) scr.bsum[g] = carry + ex;
     carry += total;
   }
 }
 
-// woff[P] = exclusive prefix of the word counts over all partitions of the
-// launch (a column's offsets are relative to its first partition's).
-__global__ __launch_bounds__(kEncBlock) void k_scan_apply(EncScratch scr, uint64_t nparts) {
-  const uint64_t p0 = uint64_t(blockIdx.x) * kScanItems + threadIdx.x * 4;
-  uint64_t x[4], sum = 0;
-#pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    x[q] = p0 + q < nparts ? scr.nwords[p0 + q] : 0;
-    sum += x[q];
-  }
-  uint64_t total;
-  uint64_t run = scr.bsum[blockIdx.x] + block_exclusive_scan_u64(sum, &total);
-#pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    if (p0 + q < nparts) scr.woff[p0 + q] = run;
-    run += x[q];
-  }
-}
+// What k_layout knows of the word counts before its workgroup's partitions.
+constexpr uint32_t kLayoutCounts = 0;  // nothing: it sums the counts themselves
+constexpr uint32_t kLayoutSums = 1;    // bsum holds the sums of k_scan_sums
+constexpr uint32_t kLayoutPrefix = 2;  // bsum holds their prefixes (k_scan_top)
+constexpr uint64_t kLayoutDirect = 32;
+constexpr uint64_t kLayoutGroups = 4096;
 
-// Records and starts; the last partition of a column also writes the
-// header and the padding.
-__global__ __launch_bounds__(kEncBlock) void k_records(const EncColumn* __restrict__ cols,
-                                                      uint64_t ncols, EncColumn single,
-                                                      uint64_t nparts, EncScratch scr, int* err) {
-  const uint64_t P = uint64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (P >= nparts) return;
-  const EncColumn c = column_of(cols, ncols, single, P);
-  const uint64_t j = P - c.part_base;
-  const uint64_t word_off = scr.woff[P] - scr.woff[c.part_base];
-  const uint64_t rec = kHeaderBytes + kRecordBytes * j;
-  if (rec + kRecordBytes <= c.cap) {
-    uint64_t* r = reinterpret_cast<uint64_t*>(c.blob + rec);
-    r[0] = scr.base[P];
-    r[1] = scr.theta[P];
-    r[2] = word_off;
-    r[3] = uint64_t(scr.bits[P]) | (c.regressor == 2 ? uint64_t(scr.kind[P]) << 8 : 0);
+// Word offsets within each column, records, starts and headers, one
+// workgroup per kScanItems partitions; the workgroups together also write the
+// blobs of empty columns, which have no partition.  Below 1e6 partitions
+// latency is all there is here (about 5 us for each launch of such kernels),
+// so the launches count: the prefixes, their application, the records and the
+// empty columns were five kernels and are this one, after at most two that
+// sum the counts.  1e6 values: polynomial 29.7 us, now 19.5, 1e7 in
+// least-squares partitions of 1024 42 and 35.5.  The words that the column
+// of the workgroup's first partition has before it come from the sums of
+// whole groups, less what the column's first group holds of columns before
+// it; columns that start further on start at 0.  A thread per partition
+// while the workgroups fit the chip; more workgroups of 256 threads, which
+// take fewer registers: for 1e7 partitions 154 us, 226 with 1024 threads.
+template <uint32_t kThreads>
+__global__ __launch_bounds__(kThreads) void k_layout(const EncColumn* __restrict__ cols,
+                                                    uint64_t ncols, EncColumn single,
+                                                    uint64_t nparts, EncScratch scr,
+                                                    uint32_t mode, int* err) {
+  constexpr uint32_t kPer = kScanItems / kThreads;
+  __shared__ uint64_t prefix[kScanItems];
+  __shared__ uint64_t wsum[2][kThreads / 64];
+  const uint64_t stride = uint64_t(gridDim.x) * kThreads;
+  for (uint64_t i = uint64_t(blockIdx.x) * kThreads + threadIdx.x; i < ncols; i += stride) {
+    const EncColumn& e = cols ? cols[i] : single;
+    if (e.m == 0) finish_column(e, 0, err);  // also writes starts[0] = 0 of a variable column
   }
-  if (c.fixed_len == 0) {
-    const uint64_t so = kHeaderBytes + kRecordBytes * c.m + 8 * j;
-    if (so + 8 <= c.cap) *reinterpret_cast<uint64_t*>(c.blob + so) = c.starts[j];
+  const uint64_t g = blockIdx.x, p0 = g * kScanItems;
+  if (p0 >= nparts) return;
+  uint64_t nw[kPer], sum = 0;
+#pragma unroll
+  for (uint32_t q = 0; q < kPer; ++q) {
+    const uint64_t P = p0 + kPer * threadIdx.x + q;
+    nw[q] = P < nparts ? scr.nwords[P] : 0;
+    sum += nw[q];
   }
-  if (c.regressor == 2) {  // (c2, c3), zero for a line or constant
-    const uint64_t meta_end =
-        kHeaderBytes + kRecordBytes * c.m + (c.fixed_len == 0 ? 8 * (c.m + 1) : 0);
-    const uint64_t co = align16(meta_end) + 16 * j;
-    if (co + 16 <= c.cap) {
-      uint64_t* q = reinterpret_cast<uint64_t*>(c.blob + co);
-      q[0] = scr.kind[P] ? scr.c2[P] : 0;
-      q[1] = scr.kind[P] ? scr.c3[P] : 0;
+  // words of the first column's partitions before p0
+  uint64_t before = 0;
+  const uint64_t first = column_of(cols, ncols, single, p0).part_base;
+  const uint64_t gf = first / kScanItems;
+  if (first < p0) {
+    if (mode == kLayoutCounts) {
+      for (uint64_t q = first + threadIdx.x; q < p0; q += kThreads) before += scr.nwords[q];
+    } else {
+      if (mode == kLayoutSums)
+        for (uint64_t q = gf + threadIdx.x; q < g; q += kThreads) before += scr.bsum[q];
+      else if (threadIdx.x == 0)
+        before = scr.bsum[g] - scr.bsum[gf];
+      for (uint64_t q = gf * kScanItems + threadIdx.x; q < first; q += kThreads)
+        before -= scr.nwords[q];
     }
   }
-  if (j + 1 == c.m) finish_column(c, word_off + scr.nwords[P], err);
+  uint64_t carry, total;
+  block_exclusive_scan_u64<kThreads / 64>(wsum[0], before, &carry);
+  uint64_t run = block_exclusive_scan_u64<kThreads / 64>(wsum[1], sum, &total);
+#pragma unroll
+  for (uint32_t q = 0; q < kPer; ++q) {
+    prefix[kPer * threadIdx.x + q] = run;
+    run += nw[q];
+  }
+  __syncthreads();
+  for (uint32_t q = 0; q < kPer; ++q) {
+    const uint32_t at = q * kThreads + threadIdx.x;
+    const uint64_t P = p0 + at;
+    if (P >= nparts) break;
+    const EncColumn c = column_of(cols, ncols, single, P);
+    const uint64_t j = P - c.part_base;
+    const uint64_t word_off =
+        c.part_base < p0 ? carry + prefix[at] : prefix[at] - prefix[c.part_base - p0];
+    scr.woff[P] = word_off;
+    const uint64_t rec = kHeaderBytes + kRecordBytes * j;
+    if (rec + kRecordBytes <= c.cap) {
+      const uint64_t base = scr.base[P], theta = scr.theta[P];
+      uint4* r = reinterpret_cast<uint4*>(c.blob + rec);
+      r[0] = make_uint4(uint32_t(base), uint32_t(base >> 32), uint32_t(theta),
+                        uint32_t(theta >> 32));
+      r[1] = make_uint4(uint32_t(word_off), uint32_t(word_off >> 32),
+                        scr.bits[P] | (c.regressor == 2 ? scr.kind[P] << 8 : 0), 0);
+    }
+    if (c.fixed_len == 0) {
+      const uint64_t so = kHeaderBytes + kRecordBytes * c.m + 8 * j;
+      if (so + 8 <= c.cap) *reinterpret_cast<uint64_t*>(c.blob + so) = c.starts[j];
+    }
+    if (c.regressor == 2) {  // (c2, c3), zero for a line or constant
+      const uint64_t meta_end =
+          kHeaderBytes + kRecordBytes * c.m + (c.fixed_len == 0 ? 8 * (c.m + 1) : 0);
+      const uint64_t co = align16(meta_end) + 16 * j;
+      if (co + 16 <= c.cap) {
+        uint64_t* k = reinterpret_cast<uint64_t*>(c.blob + co);
+        k[0] = scr.kind[P] ? scr.c2[P] : 0;
+        k[1] = scr.kind[P] ? scr.c3[P] : 0;
+      }
+    }
+    if (j + 1 == c.m) finish_column(c, word_off + scr.nwords[P], err);
+  }
 }
 
 // ---- pack ----------------------------------------------------------------------------
@@ -1343,7 +1395,7 @@ __global__ __launch_bounds__(kEncBlock) __attribute__((amdgpu_waves_per_eu(5))) 
   const EncColumn c = column_of(cols, ncols, single, P);
   uint64_t start, len;
   part_bounds(c, P - c.part_base, start, len);
-  const uint64_t w0 = 2 * (meta_load(scr.woff, P) - meta_load(scr.woff, c.part_base));
+  const uint64_t w0 = 2 * meta_load(scr.woff, P);
   uint32_t* gw32 = reinterpret_cast<uint32_t*>(c.blob + c.words_off) + w0;
   const uint64_t cap_w32 = c.cap > c.words_off ? (c.cap - c.words_off) / 4 : 0;
   const uint64_t nwords32 = 2 * ((len * b + 63) >> 6);
@@ -1645,7 +1697,7 @@ __device__ __attribute__((always_inline)) inline void encode_fused_part(
 
 // Before a one-pass encode: the look-back states (scr.woff) and the ticket
 // (scr.bsum[0]) start at 0, and every empty column's blob is written whole
-// (as k_encode_prepare does; one launch instead of two).
+// (one launch instead of two).
 __global__ void k_fused_prepare(const EncColumn* __restrict__ cols, uint64_t ncols,
                                 EncColumn single, EncScratch scr, uint64_t nparts, int* err) {
   const uint64_t stride = uint64_t(gridDim.x) * blockDim.x;
@@ -1767,18 +1819,6 @@ __global__ __launch_bounds__(kEncBlock) void k_encode_fused_wave(
   }
 }
 
-// Writes the complete blob of every empty column (no partitions, so no
-// other kernel sees it).
-__global__ void k_encode_prepare(const EncColumn* __restrict__ cols, uint64_t ncols,
-                                 EncColumn single, int* err) {
-  const uint64_t stride = uint64_t(gridDim.x) * blockDim.x;
-  for (uint64_t i = uint64_t(blockIdx.x) * blockDim.x + threadIdx.x; i < ncols; i += stride) {
-    const EncColumn& c = cols ? cols[i] : single;
-    if (c.m != 0) continue;
-    finish_column(c, 0, err);  // also writes starts[0] = 0 of a variable column
-  }
-}
-
 uint64_t encode_scratch_bytes(uint64_t nparts) {
   const uint64_t k = nparts ? nparts : 1;
   const uint64_t ng = (k + kScanItems - 1) / kScanItems;
@@ -1879,20 +1919,34 @@ hipError_t launch_encode_columns(leco_ctx* ctx, const EncColumn* cols_dev, uint6
                          cols_dev, ncols, single, nparts, scr, ctx->err_dev);
     return hipGetLastError();
   }
-  const uint64_t cg = (ncols + 255) / 256;
-  hipLaunchKernelGGL(k_encode_prepare, dim3(uint32_t(cg < 4096 ? cg : 4096)), dim3(256), 0,
-                     stream, cols_dev, ncols, single, ctx->err_dev);
-  if (nparts == 0) return hipGetLastError();
-  const hipError_t e = launch_fit_columns(ctx, cols_dev, ncols, single, nparts, max_len, regs,
-                                          scr, stream);
-  if (e != hipSuccess) return e;
+  if (nparts != 0) {
+    const hipError_t e = launch_fit_columns(ctx, cols_dev, ncols, single, nparts, max_len, regs,
+                                            scr, stream);
+    if (e != hipSuccess) return e;
+  }
   const bool wave = max_len <= kWaveEncMax && ctx->tune.encode_wave;  // pack only
   const uint64_t ng = (nparts + kScanItems - 1) / kScanItems;
-  hipLaunchKernelGGL(k_scan_sums, dim3(uint32_t(ng)), dim3(kEncBlock), 0, stream, scr, nparts);
-  hipLaunchKernelGGL(k_scan_top, dim3(1), dim3(kEncBlock), 0, stream, scr, ng);
-  hipLaunchKernelGGL(k_scan_apply, dim3(uint32_t(ng)), dim3(kEncBlock), 0, stream, scr, nparts);
-  hipLaunchKernelGGL(k_records, dim3(uint32_t((nparts + 255) / 256)), dim3(256), 0, stream,
-                     cols_dev, ncols, single, nparts, scr, ctx->err_dev);
+  // Every workgroup of k_layout sums what lies before it: the counts of up to
+  // kLayoutDirect groups (256 KB at most, about 2 us) in less time than the
+  // launch that sums them first (5 us), the sums of up to kLayoutGroups
+  // groups (32 KB at most) in less than the launch that scans those.
+  const uint32_t mode = ng <= kLayoutDirect   ? kLayoutCounts
+                        : ng <= kLayoutGroups ? kLayoutSums
+                                              : kLayoutPrefix;
+  if (mode != kLayoutCounts)
+    hipLaunchKernelGGL(k_scan_sums, dim3(uint32_t(ng)), dim3(kEncBlock), 0, stream, scr, nparts);
+  if (mode == kLayoutPrefix)
+    hipLaunchKernelGGL(k_scan_top, dim3(1), dim3(kScanItems), 0, stream, scr, ng);
+  uint64_t lg = (ncols + kEncBlock - 1) / kEncBlock;
+  lg = lg < 1 ? 1 : (lg > 1024 ? 1024 : lg);
+  lg = ng > lg ? ng : lg;
+  if (lg <= 2 * uint64_t(ctx->num_cus))
+    hipLaunchKernelGGL(k_layout<kScanItems>, dim3(uint32_t(lg)), dim3(kScanItems), 0, stream,
+                       cols_dev, ncols, single, nparts, scr, mode, ctx->err_dev);
+  else
+    hipLaunchKernelGGL(k_layout<kEncBlock>, dim3(uint32_t(lg)), dim3(kEncBlock), 0, stream,
+                       cols_dev, ncols, single, nparts, scr, mode, ctx->err_dev);
+  if (nparts == 0) return hipGetLastError();
   if (wave)
     hipLaunchKernelGGL(k_pack<true>, dim3(uint32_t(pw)), dim3(kEncBlock), 0, stream, cols_dev,
                        ncols, single, nparts, scr);
