@@ -34,6 +34,7 @@ constexpr int kEncRegs = 16;                           // values per thread in r
 constexpr uint32_t kEncRegLen = kEncBlock * kEncRegs;  // 4096
 constexpr uint32_t kWaveEncMax = uint32_t(kWaveEncodeMax);
 constexpr int kWaveRegs = int(kWaveEncMax / 64);      // values per lane, one wavefront
+constexpr int kShortRegs = 2;                         // the fewest
 constexpr uint64_t kNarrowRange = 1ull << 30;
 constexpr uint32_t kScanItems = 1024;                  // word counts per scan workgroup
 
@@ -149,6 +150,31 @@ __device__ inline void finish_column(const EncColumn& c, uint64_t total_words, i
   for (uint64_t i = meta_end; i < coef; ++i) c.blob[i] = 0;
   for (uint64_t i = coef_end; i < c.words_off; ++i) c.blob[i] = 0;
   for (uint64_t i = c.words_off + 8 * total_words; i < size; ++i) c.blob[i] = 0;
+}
+
+// Record j of a column, its start (variable partitions) and its coefficients
+// (polynomial columns; zero for a line or constant), as far as the capacity
+// reaches.
+__device__ inline void write_record(const EncColumn& c, uint64_t j, uint64_t base, uint64_t theta,
+                                    uint64_t word_off, uint32_t bits, uint32_t kind, uint64_t c2,
+                                    uint64_t c3) {
+  const uint64_t rec = kHeaderBytes + kRecordBytes * j;
+  if (rec + kRecordBytes <= c.cap) {
+    uint4* r = reinterpret_cast<uint4*>(c.blob + rec);
+    r[0] = make_uint4(uint32_t(base), uint32_t(base >> 32), uint32_t(theta), uint32_t(theta >> 32));
+    r[1] = make_uint4(uint32_t(word_off), uint32_t(word_off >> 32), bits | kind << 8, 0);
+  }
+  const uint64_t starts = kHeaderBytes + kRecordBytes * c.m;
+  if (c.fixed_len == 0 && starts + 8 * j + 8 <= c.cap)
+    *reinterpret_cast<uint64_t*>(c.blob + starts + 8 * j) = c.starts[j];
+  if (c.regressor == 2) {
+    const uint64_t co = align16(starts + (c.fixed_len == 0 ? 8 * (c.m + 1) : 0)) + 16 * j;
+    if (co + 16 <= c.cap) {
+      uint64_t* q = reinterpret_cast<uint64_t*>(c.blob + co);
+      q[0] = kind ? c2 : 0;
+      q[1] = kind ? c3 : 0;
+    }
+  }
 }
 
 // Writes the fitted model of partition P.
@@ -347,7 +373,25 @@ __device__ __attribute__((always_inline)) inline Model fit_wave(const T* src, ui
   return fit_wave_regs<kR>(v, len, force_constant);
 }
 
-// At 16 values per lane, held to five waves per SIMD (90 VGPRs instead of
+// Calls f with the smallest number of values per lane, kMin to kR halving,
+// that holds a partition of len values: every loop of a fit runs over all of
+// them, so at 16 a partition of 128 values paid for 1024 (encode of 5e7 u32
+// values in such partitions: least squares 540 us, now 356, minimax 1020 and
+// 660, polynomial 1153 and 744, with the packing's smaller last batch).
+template <int kN>
+struct Lanes {
+  static constexpr int n = kN;
+};
+
+template <int kR, int kMin, class F>
+__device__ __attribute__((always_inline)) inline auto by_length(uint64_t len, const F& f) {
+  if constexpr (kR > kMin) {
+    if (len <= 32 * kR) return by_length<kR / 2, kMin>(len, f);
+  }
+  return f(Lanes<kR>{});
+}
+
+// At 16 values per lane, held to five waves per SIMD (82 VGPRs instead of
 // 104): 2% faster on u64 columns.
 template <int kR>
 __global__ __launch_bounds__(kEncBlock, kR == 16 ? 5 : 1) void k_fit_wave(const EncColumn* __restrict__ cols,
@@ -366,9 +410,11 @@ __global__ __launch_bounds__(kEncBlock, kR == 16 ? 5 : 1) void k_fit_wave(const 
     if (lane == 0) raise(err, kErrDevice);
     return;
   }
-  const Model md = c.dtype == 8
-                       ? fit_wave<kR>(reinterpret_cast<const uint64_t*>(c.col) + start, len, c.force_constant)
-                       : fit_wave<kR>(reinterpret_cast<const uint32_t*>(c.col) + start, len, c.force_constant);
+  const Model md = by_length<kR, kShortRegs>(len, [&](auto r) __attribute__((always_inline)) {
+    return c.dtype == 8
+               ? fit_wave<r.n>(reinterpret_cast<const uint64_t*>(c.col) + start, len, c.force_constant)
+               : fit_wave<r.n>(reinterpret_cast<const uint32_t*>(c.col) + start, len, c.force_constant);
+  });
   if (lane == 0) store_model(scr, P, md, len);
 }
 
@@ -535,7 +581,7 @@ template <int kR, class T>
 __device__ __attribute__((always_inline)) inline Model fit_minimax_wave(const T* src, uint64_t len,
                                                                         bool force_constant,
                                                                         bool minimax, int* err) {
-  constexpr uint32_t kLog2S = kR == 16 ? 10 : 11;
+  constexpr uint32_t kLog2S = kR <= 16 ? 10 : 11;
   const uint32_t lane = threadIdx.x & 63;
   T v[kR];
 #pragma unroll
@@ -686,12 +732,13 @@ __global__ __launch_bounds__(kEncBlock, kR == 16 ? 4 : 2) void k_fit_minimax_wav
     return;
   }
   const bool minimax = c.regressor == 1;
-  const Model md =
-      c.dtype == 8
-          ? fit_minimax_wave<kR>(reinterpret_cast<const uint64_t*>(c.col) + start, len,
-                                 c.force_constant, minimax, err)
-          : fit_minimax_wave<kR>(reinterpret_cast<const uint32_t*>(c.col) + start, len,
-                                 c.force_constant, minimax, err);
+  const Model md = by_length<kR, kShortRegs>(len, [&](auto r) __attribute__((always_inline)) {
+    return c.dtype == 8
+               ? fit_minimax_wave<r.n>(reinterpret_cast<const uint64_t*>(c.col) + start, len,
+                                       c.force_constant, minimax, err)
+               : fit_minimax_wave<r.n>(reinterpret_cast<const uint32_t*>(c.col) + start, len,
+                                       c.force_constant, minimax, err);
+  });
   if (lane == 0) store_model(scr, P, md, len);
 }
 
@@ -1160,12 +1207,13 @@ __global__ __launch_bounds__(kEncBlock, kR == 16 ? 4 : 3) void k_fit_poly_wave(c
   }
   uint32_t kind;
   double c2, c3;
-  const Model md =
-      c.dtype == 8
-          ? fit_poly_wave<kR>(reinterpret_cast<const uint64_t*>(c.col) + start, len,
-                              c.force_constant, kind, c2, c3)
-          : fit_poly_wave<kR>(reinterpret_cast<const uint32_t*>(c.col) + start, len,
-                              c.force_constant, kind, c2, c3);
+  const Model md = by_length<kR, kShortRegs>(len, [&](auto r) __attribute__((always_inline)) {
+    return c.dtype == 8
+               ? fit_poly_wave<r.n>(reinterpret_cast<const uint64_t*>(c.col) + start, len,
+                                    c.force_constant, kind, c2, c3)
+               : fit_poly_wave<r.n>(reinterpret_cast<const uint32_t*>(c.col) + start, len,
+                                    c.force_constant, kind, c2, c3);
+  });
   if (lane == 0) {
     store_model(scr, P, md, len);
     store_poly(scr, P, kind, c2, c3);
@@ -1302,29 +1350,9 @@ __global__ __launch_bounds__(kThreads) void k_layout(const EncColumn* __restrict
     const uint64_t word_off =
         c.part_base < p0 ? carry + prefix[at] : prefix[at] - prefix[c.part_base - p0];
     scr.woff[P] = word_off;
-    const uint64_t rec = kHeaderBytes + kRecordBytes * j;
-    if (rec + kRecordBytes <= c.cap) {
-      const uint64_t base = scr.base[P], theta = scr.theta[P];
-      uint4* r = reinterpret_cast<uint4*>(c.blob + rec);
-      r[0] = make_uint4(uint32_t(base), uint32_t(base >> 32), uint32_t(theta),
-                        uint32_t(theta >> 32));
-      r[1] = make_uint4(uint32_t(word_off), uint32_t(word_off >> 32),
-                        scr.bits[P] | (c.regressor == 2 ? scr.kind[P] << 8 : 0), 0);
-    }
-    if (c.fixed_len == 0) {
-      const uint64_t so = kHeaderBytes + kRecordBytes * c.m + 8 * j;
-      if (so + 8 <= c.cap) *reinterpret_cast<uint64_t*>(c.blob + so) = c.starts[j];
-    }
-    if (c.regressor == 2) {  // (c2, c3), zero for a line or constant
-      const uint64_t meta_end =
-          kHeaderBytes + kRecordBytes * c.m + (c.fixed_len == 0 ? 8 * (c.m + 1) : 0);
-      const uint64_t co = align16(meta_end) + 16 * j;
-      if (co + 16 <= c.cap) {
-        uint64_t* k = reinterpret_cast<uint64_t*>(c.blob + co);
-        k[0] = scr.kind[P] ? scr.c2[P] : 0;
-        k[1] = scr.kind[P] ? scr.c3[P] : 0;
-      }
-    }
+    const bool poly = c.regressor == 2;
+    write_record(c, j, scr.base[P], scr.theta[P], word_off, scr.bits[P], poly ? scr.kind[P] : 0,
+                 poly ? scr.c2[P] : 0, poly ? scr.c3[P] : 0);
     if (j + 1 == c.m) finish_column(c, word_off + scr.nwords[P], err);
   }
 }
@@ -1343,39 +1371,56 @@ constexpr uint32_t kPackBatch = 8;  // rounds of 64 residuals per batch
 // stored as one contiguous run; words at or beyond `limit` (the span's end,
 // or the blob's capacity) are not stored.  Called by one wavefront.  A
 // polynomial partition (kind 1) predicts with poly_predict(theta1, c2, c3).
+template <uint32_t kBatch, class T>
+__device__ __attribute__((always_inline)) inline void pack_batch(
+    const T* src, uint64_t len, uint64_t base, double theta1, bool fits32, uint32_t kind, double c2,
+    double c3, uint32_t b, __attribute__((address_space(1))) uint32_t* gdst, uint64_t limit,
+    uint64_t k0, uint32_t nr, uint32_t* w32) {
+  const uint32_t lane = threadIdx.x & 63;
+  uint64_t u[kBatch];
+#pragma unroll
+  for (uint32_t r = 0; r < kBatch; ++r) u[r] = load_clamped(src, uint32_t(64 * (k0 + r) + lane), len);
+#pragma unroll
+  for (uint32_t r = 0; r < kBatch; ++r) {
+    const uint32_t t = uint32_t(64 * (k0 + r) + lane);
+    const uint64_t p = kind ? uint64_t(poly_predict(theta1, c2, c3, t, uint32_t(len)))
+                            : fits32 ? uint64_t(int64_t(predict32(theta1, t)))
+                                     : uint64_t(predict(theta1, t));
+    u[r] = t < len ? (u[r] - base) - p : 0;
+  }
+  const uint32_t nw = 2 * b * nr;  // <= 1024
+  for (uint32_t q = lane; q < nw; q += 64) w32[q] = 0;
+  wave_fence();
+#pragma unroll
+  for (uint32_t r = 0; r < kBatch; ++r)
+    if (r < nr) or_bits(w32, (64 * r + lane) * b, b, u[r]);
+  wave_fence();
+  const uint64_t first = 2 * b * k0;
+  const uint64_t count = first >= limit ? 0 : (limit - first < nw ? limit - first : nw);
+  for (uint32_t q = lane; q < count; q += 64) gdst[first + q] = w32[q];
+  wave_fence();
+}
+
 template <class T>
 __device__ __attribute__((always_inline)) inline void pack_rounds(const T* src, uint64_t len, uint64_t base, double theta1,
                                    uint32_t kind, double c2, double c3, uint32_t b,
                                    uint32_t* gw32, uint64_t limit, uint64_t k_begin,
                                    uint64_t k_end, uint32_t* w32) {
-  const uint32_t lane = threadIdx.x & 63;
   const bool fits32 = prediction_fits_i32(theta1, len);
   const auto gdst = global_ptr(gw32);
-  for (uint64_t k0 = k_begin; k0 < k_end; k0 += kPackBatch) {
-    const uint32_t nr = uint32_t(k_end - k0 < kPackBatch ? k_end - k0 : kPackBatch);
-    uint64_t u[kPackBatch];
-#pragma unroll
-    for (uint32_t r = 0; r < kPackBatch; ++r) u[r] = load_clamped(src, uint32_t(64 * (k0 + r) + lane), len);
-#pragma unroll
-    for (uint32_t r = 0; r < kPackBatch; ++r) {
-      const uint32_t t = uint32_t(64 * (k0 + r) + lane);
-      const uint64_t p = kind ? uint64_t(poly_predict(theta1, c2, c3, t, uint32_t(len)))
-                              : fits32 ? uint64_t(int64_t(predict32(theta1, t)))
-                                       : uint64_t(predict(theta1, t));
-      u[r] = t < len ? (u[r] - base) - p : 0;
-    }
-    const uint32_t nw = 2 * b * nr;  // <= 1024
-    for (uint32_t q = lane; q < nw; q += 64) w32[q] = 0;
-    wave_fence();
-#pragma unroll
-    for (uint32_t r = 0; r < kPackBatch; ++r)
-      if (r < nr) or_bits(w32, (64 * r + lane) * b, b, u[r]);
-    wave_fence();
-    const uint64_t first = 2 * b * k0;
-    const uint64_t count = first >= limit ? 0 : (limit - first < nw ? limit - first : nw);
-    for (uint32_t q = lane; q < count; q += 64) gdst[first + q] = w32[q];
-    wave_fence();
-  }
+  uint64_t k0 = k_begin;
+  for (; k0 + kPackBatch / 2 < k_end; k0 += kPackBatch)
+    pack_batch<kPackBatch>(src, len, base, theta1, fits32, kind, c2, c3, b, gdst, limit, k0,
+                           uint32_t(k_end - k0 < kPackBatch ? k_end - k0 : kPackBatch), w32);
+  if (k0 >= k_end) return;
+  // the rest, in the smallest batch that holds it
+  const uint32_t nr = uint32_t(k_end - k0);
+  if (nr > 2)
+    pack_batch<4>(src, len, base, theta1, fits32, kind, c2, c3, b, gdst, limit, k0, nr, w32);
+  else if (nr == 2)
+    pack_batch<2>(src, len, base, theta1, fits32, kind, c2, c3, b, gdst, limit, k0, nr, w32);
+  else
+    pack_batch<1>(src, len, base, theta1, fits32, kind, c2, c3, b, gdst, limit, k0, nr, w32);
 }
 
 // One wavefront per partition (kWave, four per workgroup), or one workgroup
@@ -1725,61 +1770,35 @@ __global__ __launch_bounds__(kEncBlock) __attribute__((amdgpu_waves_per_eu(4))) 
   encode_fused_part(sh, c, P, scr, err);
 }
 
-// The one-pass encoder for partitions of at most 64 kR values: one
-// wavefront per partition, no workgroup barrier after the ticket.  Values in
-// registers, model by wavefront shuffles, word count published, residuals
-// packed in the wavefront's LDS slice, look-back, record and words written.
-template <int kR>
-__global__ __launch_bounds__(kEncBlock) void k_encode_fused_wave(
-    const EncColumn* __restrict__ cols, uint64_t ncols, EncColumn single, uint64_t nparts,
-    EncScratch scr, int* err) {
-  __shared__ uint32_t words[kEncWaves][2 * 64 * kR];
-  __shared__ uint64_t ticket;
+// Partition P of k_encode_fused_wave, of at most 64 kN values.
+template <int kN>
+__device__ __attribute__((always_inline)) inline void encode_fused_wave(
+    const EncColumn& c, uint64_t P, uint64_t j, uint64_t start, uint64_t len,
+    const EncScratch& scr, uint32_t* w32, int* err) {
   const uint32_t lane = threadIdx.x & 63;
-  const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  // one ticket per workgroup, whose waves take partitions 4 ticket ..
-  // 4 ticket + 3 (a ticket per wavefront, 2e6 device-scope atomics on one
-  // word for 2e9 values, doubled the time of such a launch)
-  if (threadIdx.x == 0)
-    ticket = atomicAdd(reinterpret_cast<unsigned long long*>(scr.bsum), 1ull);
-  __syncthreads();
-  const uint64_t tk = ticket;
-  const uint64_t P = kEncWaves * ((uint64_t(uint32_t(__builtin_amdgcn_readfirstlane(int(uint32_t(tk >> 32))))) << 32) |
-                                  uint32_t(__builtin_amdgcn_readfirstlane(int(uint32_t(tk))))) +
-                     wave;
-  if (P >= nparts) return;
-  const EncColumn c = column_of(cols, ncols, single, P);
-  uint64_t start, len;
-  const uint64_t j = P - c.part_base;
-  part_bounds(c, j, start, len);
-  if (len > 64 * kR) {  // the host sends such launches to the two passes
-    if (lane == 0) raise(err, kErrDevice);
-    return;
-  }
-  uint64_t v[kR];
+  uint64_t v[kN];
   if (c.dtype == 8) {
     const uint64_t* src = reinterpret_cast<const uint64_t*>(c.col) + start;
 #pragma unroll
-    for (int k = 0; k < kR; ++k) v[k] = load_clamped(src, lane + 64 * k, len);
+    for (int k = 0; k < kN; ++k) v[k] = load_clamped(src, lane + 64 * k, len);
   } else {
     const uint32_t* src = reinterpret_cast<const uint32_t*>(c.col) + start;
 #pragma unroll
-    for (int k = 0; k < kR; ++k) v[k] = load_clamped(src, lane + 64 * k, len);
+    for (int k = 0; k < kN; ++k) v[k] = load_clamped(src, lane + 64 * k, len);
   }
-  const Model md = fit_wave_regs<kR>(v, len, c.force_constant != 0);
+  const Model md = fit_wave_regs<kN>(v, len, c.force_constant != 0);
   const uint64_t nw = (len * md.bits + 63) >> 6;
   uint64_t* st = scr.woff;
   if (lane == 0) lb_publish(st, P, (j == 0 ? kLbInclusive : kLbCount) | nw);
   const uint32_t b = md.bits;
   const uint32_t nr = uint32_t((len + 63) / 64);
   const uint32_t nwb = 2 * b * nr;
-  uint32_t* w32 = words[wave];
   if (nwb) {
     for (uint32_t q = lane; q < nwb; q += 64) w32[q] = 0;
     wave_fence();
     const bool fits32 = prediction_fits_i32(md.theta1, len);
 #pragma unroll
-    for (int k = 0; k < kR; ++k) {
+    for (int k = 0; k < kN; ++k) {
       const uint32_t t = lane + 64 * k;
       const uint64_t p = !md.linear ? 0
                          : fits32   ? uint64_t(int64_t(predict32(md.theta1, t)))
@@ -1817,6 +1836,42 @@ __global__ __launch_bounds__(kEncBlock) void k_encode_fused_wave(
     const uint64_t count = limit < nwb ? limit : nwb;
     for (uint32_t q = lane; q < count; q += 64) gdst[q] = w32[q];
   }
+}
+
+// The one-pass encoder for partitions of at most 64 kR values: one
+// wavefront per partition, no workgroup barrier after the ticket.  Values in
+// registers, model by wavefront shuffles, word count published, residuals
+// packed in the wavefront's LDS slice, look-back, record and words written.
+template <int kR>
+__global__ __launch_bounds__(kEncBlock) void k_encode_fused_wave(
+    const EncColumn* __restrict__ cols, uint64_t ncols, EncColumn single, uint64_t nparts,
+    EncScratch scr, int* err) {
+  __shared__ uint32_t words[kEncWaves][2 * 64 * kR];
+  __shared__ uint64_t ticket;
+  const uint32_t lane = threadIdx.x & 63;
+  const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  // one ticket per workgroup, whose waves take partitions 4 ticket ..
+  // 4 ticket + 3 (a ticket per wavefront, 2e6 device-scope atomics on one
+  // word for 2e9 values, doubled the time of such a launch)
+  if (threadIdx.x == 0)
+    ticket = atomicAdd(reinterpret_cast<unsigned long long*>(scr.bsum), 1ull);
+  __syncthreads();
+  const uint64_t tk = ticket;
+  const uint64_t P = kEncWaves * ((uint64_t(uint32_t(__builtin_amdgcn_readfirstlane(int(uint32_t(tk >> 32))))) << 32) |
+                                  uint32_t(__builtin_amdgcn_readfirstlane(int(uint32_t(tk))))) +
+                     wave;
+  if (P >= nparts) return;
+  const EncColumn c = column_of(cols, ncols, single, P);
+  uint64_t start, len;
+  const uint64_t j = P - c.part_base;
+  part_bounds(c, j, start, len);
+  if (len > 64 * kR) {  // the host sends such launches to the two passes
+    if (lane == 0) raise(err, kErrDevice);
+    return;
+  }
+  by_length<kR, kShortRegs>(len, [&](auto r) __attribute__((always_inline)) {
+    encode_fused_wave<r.n>(c, P, j, start, len, scr, words[wave], err);
+  });
 }
 
 uint64_t encode_scratch_bytes(uint64_t nparts) {
