@@ -5,13 +5,14 @@
 //   C = (len + 1) * D~new - len * D~old,  D~ = bitlen(max d - min d)
 // over the partition's first differences d, stays within tau * S_M, and
 // the partition holds fewer than max_len values.  The column is cut into
-// 2^14-value sub-chunks that are first split speculatively in parallel, as
-// if a partition began at each one's start.  One wavefront per 2^20-value
-// segment then walks the segment's sub-chunks in order from the true state,
-// each until the true run starts a partition where the speculative run did
-// (from there on the two runs are the same), rewriting the starts it
-// passes; a last wavefront does the same across segments, from the end
-// state of each segment to the next.  The wavefront walks 64 candidates at a
+// 2^11-value sub-chunks that are first split speculatively in parallel, as
+// if a partition began at each one's start, and then again from the state
+// that its left neighbour ended in, until this run starts a partition where
+// the first one did (from there on the two runs are the same), rewriting the
+// starts it passes.  Where a sub-chunk holds no such place, one wavefront per
+// 2^20-value segment walks the next ones on from its end; a last wavefront
+// does the same across segments, from the end state of each segment to the
+// next.  The wavefront walks 64 candidates at a
 // time (see greedy_walk).  This reproduces the sequential greedy exactly.
 // Optionally the split also honours starting partitions (section 3.2.2,
 // selecting good starting positions): runs of smallest second-order delta,
@@ -38,9 +39,10 @@
 // latency of the batches along its longest run: 256 steps in about 8 us.  With
 // one wavefront, 64 steps a batch, every added value broadcast to all lanes
 // and the hulls kept by a serial chain it was 60 us for 64, and short chunks
-// re-walked most of the column in every round: 512 -> 64 ms (in order: hulls
+// re-walked most of the column in every round: 512 -> 48 ms (in order: hulls
 // by parallel peeling, unions sized by bounds of two hulls, 4096-boundary
-// chunks and a workgroup per walker), sorted normal samples 30 -> 16 ms.
+// chunks and a workgroup per walker; then the split's look-ahead), sorted
+// normal samples 30 -> 7 ms.
 #include <math.h>
 
 #include <utility>
@@ -54,8 +56,9 @@
 namespace leco {
 
 constexpr uint32_t kSegLog2 = 20;
-constexpr uint32_t kSubLog2 = 14;  // speculative split sub-chunks of a segment
+constexpr uint32_t kSubLog2 = 11;  // speculative split sub-chunks of a segment
 constexpr uint32_t kSplitWindow = 1024;  // values staged in LDS per window
+constexpr uint32_t kSplitAhead = 16;      // values one lane tries in a row (split_ahead)
 constexpr uint32_t kScanBlock = 256;
 constexpr uint32_t kItemsPerBlock = 1024;  // bitmap words or flags per scan block
 constexpr uint64_t kNoMerge = ~uint64_t(0);
@@ -148,6 +151,40 @@ __device__ inline bool bit_set(unsigned long long* bitmap, uint64_t j) {
   return (word >> (j & 63)) & 1ull;
 }
 
+// The greedy from 64 partition starts at once: lane l takes v[p - 1 + l] as a
+// partition's first value and tries up to kSplitAhead values after it, so
+// that each knows where the next partition would begin, if it is that near
+// (0: not known).  win[0] is v[p - 1]; candidates end before b.
+template <class K>
+__device__ inline uint32_t split_ahead(const uint64_t* win, uint64_t p, uint64_t b, double thr,
+                                       uint64_t max_len) {
+  const uint32_t lane = threadIdx.x & 63;
+  // tries 1 .. reach stay before b; of a partition of max_len values the
+  // next one begins without the cost test
+  const uint64_t after = b - (p - 1);
+  const uint32_t reach = after <= lane + 1 ? 0 : uint32_t(after - lane - 1 < kSplitAhead ? after - lane - 1 : kSplitAhead);
+  const uint32_t cap = uint32_t(max_len < kSplitAhead + 1 ? max_len : kSplitAhead + 1);
+  uint32_t next = 0;
+  int32_t w_old = 0;
+  uint64_t prev = win[reach ? lane : 0];  // lanes past b read nothing past it
+  K mn = make_key(static_cast<K*>(nullptr), 0, 0), mx = mn;
+#pragma unroll 2
+  for (uint32_t k = 1; k <= kSplitAhead; ++k) {
+    const bool on = next == 0 && k <= reach;
+    if (__ballot(on) == 0) break;
+    const uint64_t v = win[on ? lane + k : 0];
+    const K d = make_key(static_cast<K*>(nullptr), v, prev);
+    prev = v;
+    if (k == 1 || key_less(d, mn)) mn = d;
+    if (k == 1 || key_less(mx, d)) mx = d;
+    const int32_t w_new = int32_t(key_span_bits(mn, mx));
+    const int32_t cost = int32_t(k + 1) * w_new - int32_t(k) * w_old;
+    w_old = w_new;
+    if (on && !(k < cap && double(cost) <= thr)) next = k;
+  }
+  return next;
+}
+
 // Runs the greedy over candidates [p, b) from state st, 64 candidates per
 // step: lane l assumes the values before its own are all included, takes
 // the inclusive prefix min / max of the first differences over the lanes
@@ -158,6 +195,13 @@ __device__ inline bool bit_set(unsigned long long* bitmap, uint64_t j) {
 // [p, b) are a speculative run's, made from a different state; the walk
 // rewrites them until it starts a partition where the speculative run also
 // did (from there on both runs are the same), returning true at that point.
+//
+// Where partitions are short that is a step of about 1 us for each, the
+// latency of its scans.  So after a partition of at most kSplitAhead values,
+// and at the walk's start, the lanes run the greedy from 64 starts in a row
+// (split_ahead) and the partitions are read off as a chain of them, as far as
+// it is known: a 2^14-value sub-chunk of normal samples, in partitions of two
+// or three, took 5.8 ms and takes 0.78, one of 2^11 0.10.
 //
 // forced and inside (both null, or both bitmaps over the column): bit j of
 // forced set means a partition begins at j (the first value of a starting
@@ -180,8 +224,9 @@ __device__ bool greedy_walk(const uint8_t* __restrict__ col, uint32_t dtype, uin
   uint32_t w_old = st.w_old;
   uint64_t base = 0, wend = 0;  // the window holds v[base - 1, wend)
   bool synced = false;
+  bool ahead = forced == nullptr;
   while (p < b) {
-    const uint64_t need = p + 64 < b ? p + 64 : b;
+    const uint64_t need = p + 64 + kSplitAhead < b ? p + 64 + kSplitAhead : b;
     if (wend < need) {
       __syncthreads();  // every lane is done with the old window
       base = p;
@@ -189,6 +234,67 @@ __device__ bool greedy_walk(const uint8_t* __restrict__ col, uint32_t dtype, uin
       for (uint64_t k = lane; k <= wend - base; k += 64)
         win[k] = load_value(col, dtype, base - 1 + k);
       __syncthreads();
+    }
+    if (ahead && !have) {  // v[i] = v[p - 1] is the partition's only value yet
+      const uint32_t next = split_ahead<K>(win + (p - base), p, b, thr, max_len);
+      // bit x of (found1, found0): a partition begins at p + x
+      uint64_t found0 = 0, found1 = 0;
+      uint32_t at = 0;  // of the last one found: p - 1 + at
+      while (at < 64) {
+        const uint32_t k = uint32_t(__builtin_amdgcn_readlane(int(next), int(at)));
+        if (k == 0) break;
+        at += k;
+        if (at <= 64)
+          found0 |= 1ull << (at - 1);
+        else
+          found1 |= 1ull << (at - 65);
+      }
+      ahead = at >= 64;
+      if (at != 0) {
+        // words of the bitmap that hold bits p .. p + at - 1: three at most
+        const uint32_t sh = uint32_t(p & 63);
+        const auto word_of = [&](uint64_t m0, uint64_t m1) {
+          return lane == 0   ? m0 << sh
+                 : lane == 1 ? (sh ? m0 >> (64 - sh) : 0) | m1 << sh
+                             : (sh ? m1 >> (64 - sh) : 0);
+        };
+        unsigned long long* word = bitmap + (p >> 6) + lane;
+        uint64_t range0 = at >= 64 ? ~0ull : (1ull << at) - 1;
+        uint64_t range1 = at > 64 ? (1ull << (at - 64)) - 1 : 0;
+        if (kFix) {
+          // the first start of both runs, if any, ends the walk
+          uint64_t both = 0;
+          if (lane < 3 && word_of(range0, range1) != 0)
+            both = word_of(found0, found1) &
+                   __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          const uint64_t hit = __ballot(both != 0);
+          if (hit != 0) {
+            const int w = __ffsll(static_cast<long long>(hit)) - 1;
+            const uint64_t bits = uint64_t(__shfl(static_cast<unsigned long long>(both), w, 64));
+            const uint64_t js = (((p >> 6) + uint64_t(w)) << 6) + uint64_t(__ffsll(static_cast<long long>(bits)) - 1);
+            at = uint32_t(js - p) + 1;
+            // up to js, whose bit is set
+            range0 = at > 64 ? ~0ull : (1ull << (at - 1)) - 1;
+            range1 = at > 64 ? (1ull << (at - 65)) - 1 : 0;
+            found0 &= range0;
+            found1 &= range1;
+            synced = true;
+          }
+          if (lane < 3) {
+            const uint64_t gone = word_of(range0 & ~found0, range1 & ~found1);
+            if (gone) atomicAnd(word, ~gone);
+          }
+        }
+        if (lane < 3) {
+          const uint64_t put = word_of(found0, found1);
+          if (put) atomicOr(word, put);
+        }
+        i = p - 1 + at;
+        w_old = 0;
+        p += at;
+        if (synced) break;
+        continue;
+      }
     }
     const uint64_t j = p + lane;
     const bool valid = j < b;
@@ -239,6 +345,7 @@ __device__ bool greedy_walk(const uint8_t* __restrict__ col, uint32_t dtype, uin
       } else if (lane == 0) {
         mark(bitmap, js);
       }
+      ahead = forced == nullptr && js - i <= kSplitAhead;
       i = js;
       have = false;
       w_old = 0;
@@ -305,15 +412,45 @@ __device__ bool walk_subchunks(const uint8_t* col, uint32_t dtype, uint64_t n, d
   return false;
 }
 
-// Fix-up within segments: one workgroup per 2^20-value segment walks its
-// sub-chunks 1.. in order, each from the state the previous one ends in,
-// until its starts meet the speculative ones; the segment's end state (as
-// if a partition began at the segment start) goes to seg_states.
+// Every sub-chunk but a segment's first again, from the speculative end
+// state of the one before it, until it meets its own speculative starts.
+// met[q]: it did, so that it ends as the speculative run does (if the one
+// before it did too); else ends[q] is its end state.  Partitions are short
+// enough to meet in nearly all columns, and one wavefront that walked a
+// segment's sub-chunks in order took 6 us for each.
+__global__ __launch_bounds__(64) void k_split_meet(const uint8_t* __restrict__ col,
+                                                   uint32_t dtype, uint64_t n, double thr,
+                                                   uint64_t max_len,
+                                                   unsigned long long* __restrict__ bitmap,
+                                                   const SplitState* __restrict__ states,
+                                                   SplitState* __restrict__ ends,
+                                                   uint8_t* __restrict__ met,
+                                                   const uint64_t* __restrict__ forced,
+                                                   const uint64_t* __restrict__ inside) {
+  __shared__ uint64_t win[kSplitWindow + 1];
+  constexpr uint64_t kSubs = uint64_t(1) << (kSegLog2 - kSubLog2);
+  const uint64_t q = blockIdx.x;
+  if (q << kSubLog2 >= n) return;
+  bool same = true;
+  if (q % kSubs != 0) {
+    SplitState st = states[q - 1];
+    same = walk_subchunks(col, dtype, n, thr, max_len, q, q + 1, st, win, bitmap, forced, inside);
+    if (!same && threadIdx.x == 0) ends[q] = st;
+  }
+  if (threadIdx.x == 0) met[q] = same ? 1 : 0;
+}
+
+// Fix-up within segments: one workgroup per 2^20-value segment walks on from
+// each sub-chunk that did not meet its speculative starts, until a later one
+// does; the segment's end state (as if a partition began at the segment
+// start) goes to seg_states.
 __global__ __launch_bounds__(64) void k_split_fix(const uint8_t* __restrict__ col,
                                                   uint32_t dtype, uint64_t n, double thr,
                                                   uint64_t max_len,
                                                   unsigned long long* __restrict__ bitmap,
                                                   const SplitState* __restrict__ states,
+                                                  const SplitState* __restrict__ ends,
+                                                  const uint8_t* __restrict__ met,
                                                   SplitState* __restrict__ seg_states,
                                                   const uint64_t* __restrict__ forced,
                                                   const uint64_t* __restrict__ inside) {
@@ -324,11 +461,26 @@ __global__ __launch_bounds__(64) void k_split_fix(const uint8_t* __restrict__ co
   const uint64_t q0 = uint64_t(blockIdx.x) * kSubs;
   const uint64_t nsub = (n + (uint64_t(1) << kSubLog2) - 1) >> kSubLog2;
   const uint64_t q_end = q0 + kSubs < nsub ? q0 + kSubs : nsub;
-  SplitState st = states[q0];
-  for (uint64_t q = q0 + 1; q < q_end; ++q) {
-    // a meeting makes the rest of sub-chunk q the speculative run's
-    if (walk_subchunks(col, dtype, n, thr, max_len, q, q + 1, st, win, bitmap, forced, inside))
-      st = states[q];
+  SplitState st = states[q_end - 1];
+  for (uint64_t q = q0 + 1; q < q_end;) {
+    const uint64_t at = q + threadIdx.x;
+    const uint64_t apart = __ballot(at < q_end && met[at < q_end ? at : q] == 0);
+    if (apart == 0) {
+      q += 64;
+      continue;
+    }
+    q += uint64_t(__ffsll(static_cast<long long>(apart)) - 1);
+    st = ends[q++];
+    while (q < q_end) {
+      // meeting the starts there, the rest of q is the run recorded for it:
+      // the speculative one if that met, else the one that ends[q] ends
+      if (walk_subchunks(col, dtype, n, thr, max_len, q, q + 1, st, win, bitmap, forced, inside)) {
+        st = met[q] ? states[q_end - 1] : ends[q];
+        if (met[q++]) break;
+      } else {
+        ++q;
+      }
+    }
   }
   if (threadIdx.x == 0) seg_states[blockIdx.x] = st;
 }
@@ -1845,17 +1997,30 @@ __global__ void k_pair_reuse(uint64_t m, const uint8_t* __restrict__ changed,
 namespace {
 
 // Device buffers of one call, freed on every exit path.
+// Device arrays of one call, of one allocation for each commit.
 struct Buffers {
+  std::vector<std::pair<void**, size_t>> wanted;
   std::vector<void*> ptrs;
   ~Buffers() {
     for (void* p : ptrs) (void)hipFree(p);
   }
   template <class T>
-  bool alloc(T** p, uint64_t count) {
+  void add(T** p, uint64_t count) {
+    static_assert(alignof(T) <= 256, "arrays begin at multiples of 256 bytes");
+    wanted.emplace_back(reinterpret_cast<void**>(p), ((count ? count : 1) * sizeof(T) + 255) / 256 * 256);
+  }
+  bool commit() {
+    size_t total = 0;
+    for (const auto& w : wanted) total += w.second;
     void* q = nullptr;
-    if (hipMalloc(&q, count ? count * sizeof(T) : sizeof(T)) != hipSuccess) return false;
+    if (hipMalloc(&q, total) != hipSuccess) return false;
     ptrs.push_back(q);
-    *p = static_cast<T*>(q);
+    char* at = static_cast<char*>(q);
+    for (const auto& w : wanted) {
+      *w.first = at;
+      at += w.second;
+    }
+    wanted.clear();
     return true;
   }
 };
@@ -1946,23 +2111,32 @@ leco_status leco_partition(leco_ctx* ctx, const void* col_dev, uint64_t n, leco_
   // split: bitmap of partition starts
   const uint64_t nwords = (n + 63) / 64;
   const uint64_t nseg = (n + (uint64_t(1) << leco::kSegLog2) - 1) >> leco::kSegLog2;
-  unsigned long long* bitmap = nullptr;
-  if (!buf.alloc(&bitmap, nwords)) return pfail(ctx, LECO_ENOMEM, "partition: bitmap");
-  P_TRY(hipMemsetAsync(bitmap, 0, 8 * nwords, stream));
   const uint64_t nsub = (n + (uint64_t(1) << leco::kSubLog2) - 1) >> leco::kSubLog2;
-  leco::SplitState *states = nullptr, *seg_states = nullptr;
-  if (!buf.alloc(&states, nsub) || !buf.alloc(&seg_states, nseg))
-    return pfail(ctx, LECO_ENOMEM, "partition: split states");
+  const uint64_t nb = (nwords + leco::kItemsPerBlock - 1) / leco::kItemsPerBlock;
+  unsigned long long* bitmap = nullptr;
+  leco::SplitState *states = nullptr, *ends = nullptr, *seg_states = nullptr;
+  uint8_t* met = nullptr;
+  uint64_t* counts = nullptr;
+  buf.add(&bitmap, nwords);
+  buf.add(&states, nsub);
+  buf.add(&ends, nsub);
+  buf.add(&met, nsub);
+  buf.add(&seg_states, nseg);
+  buf.add(&counts, nb);
   // starting partitions: bitmaps of their first and later values
-  uint64_t *first = nullptr, *inside = nullptr;
+  uint64_t *first = nullptr, *inside = nullptr, *partial = nullptr, *best = nullptr;
+  const uint64_t gd_cap = uint64_t(ctx->num_cus) * 8;
+  const uint64_t gd0 = (n + leco::kScanBlock - 1) / leco::kScanBlock;
+  const uint64_t gd = gd0 < gd_cap ? gd0 : gd_cap;
   if (prm->start_positions) {
-    const uint64_t cap = uint64_t(ctx->num_cus) * 8;
-    const uint64_t gd0 = (n + leco::kScanBlock - 1) / leco::kScanBlock;
-    const uint64_t gd = gd0 < cap ? gd0 : cap;
-    uint64_t *partial = nullptr, *best = nullptr;
-    if (!buf.alloc(&first, nwords) || !buf.alloc(&inside, nwords) ||
-        !buf.alloc(&partial, 2 * gd) || !buf.alloc(&best, 2))
-      return pfail(ctx, LECO_ENOMEM, "partition: starting partitions");
+    buf.add(&first, nwords);
+    buf.add(&inside, nwords);
+    buf.add(&partial, 2 * gd);
+    buf.add(&best, 2);
+  }
+  if (!buf.commit()) return pfail(ctx, LECO_ENOMEM, "partition: split arrays");
+  P_TRY(hipMemsetAsync(bitmap, 0, 8 * nwords, stream));
+  if (prm->start_positions) {
     hipLaunchKernelGGL(leco::k_dd_min, dim3(uint32_t(gd)), dim3(leco::kScanBlock), 0, stream, col,
                        w, n, partial);
     P_TRY(hipGetLastError());
@@ -1975,8 +2149,11 @@ leco_status leco_partition(leco_ctx* ctx, const void* col_dev, uint64_t n, leco_
   hipLaunchKernelGGL(leco::k_split_spec, dim3(uint32_t(nsub)), dim3(64), 0, stream, col, w, n,
                      thr, prm->max_len, bitmap, states, first, inside);
   P_TRY(hipGetLastError());
+  hipLaunchKernelGGL(leco::k_split_meet, dim3(uint32_t(nsub)), dim3(64), 0, stream, col, w, n, thr,
+                     prm->max_len, bitmap, states, ends, met, first, inside);
+  P_TRY(hipGetLastError());
   hipLaunchKernelGGL(leco::k_split_fix, dim3(uint32_t(nseg)), dim3(64), 0, stream, col, w, n, thr,
-                     prm->max_len, bitmap, states, seg_states, first, inside);
+                     prm->max_len, bitmap, states, ends, met, seg_states, first, inside);
   P_TRY(hipGetLastError());
   if (nseg > 1) {
     hipLaunchKernelGGL(leco::k_split_join, dim3(1), dim3(64), 0, stream, col, w, n, thr,
@@ -1985,9 +2162,6 @@ leco_status leco_partition(leco_ctx* ctx, const void* col_dev, uint64_t n, leco_
   }
 
   // starts from the bitmap
-  const uint64_t nb = (nwords + leco::kItemsPerBlock - 1) / leco::kItemsPerBlock;
-  uint64_t* counts = nullptr;
-  if (!buf.alloc(&counts, nb)) return pfail(ctx, LECO_ENOMEM, "partition: counts");
   hipLaunchKernelGGL(leco::k_bitmap_count, dim3(uint32_t(nb)), dim3(leco::kScanBlock), 0, stream,
                      reinterpret_cast<const uint64_t*>(bitmap), nwords, counts);
   P_TRY(hipGetLastError());
@@ -2005,14 +2179,21 @@ leco_status leco_partition(leco_ctx* ctx, const void* col_dev, uint64_t n, leco_
   const uint64_t kwords = (m + 63) / 64;
   const uint64_t nbk = (kwords + leco::kKeepWords - 1) / leco::kKeepWords;
   const uint64_t nchunks0 = chunks_bound(m, n);
-  if (!buf.alloc(&starts, m + 1) || !buf.alloc(&starts2, m + 1) || !buf.alloc(&cost, m) ||
-      !buf.alloc(&cost2, m) || !buf.alloc(&pair, m) || !buf.alloc(&pair2, m) ||
-      !buf.alloc(&old, m) || !buf.alloc(&changed, m) || !buf.alloc(&dirty, m) ||
-      !buf.alloc(&keep, kwords) || !buf.alloc(&keep_counts, nbk) ||
-      !buf.alloc(&mout, nchunks0) || !buf.alloc(&hulls, nchunks0) || !buf.alloc(&psum, m) ||
-      !buf.alloc(&psum2, m) || !buf.alloc(&seen, nchunks0) || !buf.alloc(&lists, 2 * nchunks0) ||
-      !buf.alloc(&todo, kRoundGroup + 1))
-    return pfail(ctx, LECO_ENOMEM, "partition: partition arrays");
+  buf.add(&starts, m + 1);
+  buf.add(&starts2, m + 1);
+  for (uint64_t** p : {&cost, &cost2, &pair, &pair2, &old}) buf.add(p, m);
+  buf.add(&changed, m);
+  buf.add(&dirty, m);
+  buf.add(&keep, kwords);
+  buf.add(&keep_counts, nbk);
+  buf.add(&mout, nchunks0);
+  buf.add(&hulls, nchunks0);
+  buf.add(&psum, m);
+  buf.add(&psum2, m);
+  buf.add(&seen, nchunks0);
+  buf.add(&lists, 2 * nchunks0);
+  buf.add(&todo, kRoundGroup + 1);
+  if (!buf.commit()) return pfail(ctx, LECO_ENOMEM, "partition: partition arrays");
   hipLaunchKernelGGL(leco::k_bitmap_emit, dim3(uint32_t(nb)), dim3(leco::kScanBlock), 0, stream,
                      reinterpret_cast<const uint64_t*>(bitmap), nwords, counts, starts);
   P_TRY(hipGetLastError());
