@@ -347,7 +347,7 @@ __device__ __attribute__((always_inline)) inline Model fit_wave_regs(const W (&v
         sty += uint64_t(t) * y;
       }
       wave_sum_u64x2(sy, sty);
-      th = ls_slope(len, U128{sy, 0}, U128{sty, 0});
+      th = ls_slope_narrow(len, sy, sty);
     } else {
       U128 s, st;
       split_sums_regs<kR, 64>(v, lane, len, vmin, s, st);
@@ -484,7 +484,7 @@ __device__ __attribute__((always_inline)) inline Model fit_block(FitShared& sh, 
         sty += uint64_t(t) * y;
       }
       block_sum_u64x2(sh, sy, sty);
-      th = block_slope(sh, len, U128{sy, 0}, U128{sty, 0});
+      th = block_slope_narrow(sh, len, sy, sty);
       small = __dmul_rn(fabs(th), double(len)) < 1073741824.0;
     } else {
       if (in_regs) {
@@ -957,7 +957,7 @@ __device__ __attribute__((always_inline)) inline Model fit_poly_narrow(
 #pragma unroll
   for (int k = 0; k < 3; ++k)
     if (c[k] == 0.0) c[k] = 0.0;  // +0.0, never -0.0
-  const double th = ls_slope(n, U128{M0, 0}, U128{M1, 0});
+  const double th = ls_slope_narrow(n, M0, M1);
   // an infinity stays only in threads without values: far outside int32
   double mx[3], mn[3];
 #pragma unroll
@@ -1479,10 +1479,8 @@ __global__ __launch_bounds__(kEncBlock) __attribute__((amdgpu_waves_per_eu(5))) 
 // does, and takes the partition's word offset from the word counts of the
 // partitions before it in its column (decoupled look-back: each partition
 // publishes its count as soon as it is fitted, and its inclusive prefix as
-// soon as it knows it).  Partitions take their index from a ticket in the
-// order their workgroups start, so every partition a workgroup waits on is
-// already running and publishes without waiting on later ones: the waits
-// end.  It then writes its record (and start) and packs its residuals from
+// soon as it knows it).  The waits are bounded (lb_exclusive): a partition
+// that is late is counted by the one that waits for it.  It then writes its record (and start) and packs its residuals from
 // the registers; the last partition of a column writes the header.
 
 // A look-back state: flag in the top two bits, a word count below them.
@@ -1498,135 +1496,271 @@ __device__ inline void lb_publish(uint64_t* st, uint64_t P, uint64_t v) {
   __hip_atomic_store(st + P, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// Words of partitions [first, P) of a column, by one wavefront: lane l reads
-// the state of partition hi - 1 - l, 64 predecessors per round, down to the
-// nearest one with an inclusive prefix; rounds wait (sleeping between
-// reads) while a partition closer than that has published nothing yet.
-__device__ inline uint64_t lb_exclusive(const uint64_t* st, uint64_t first, uint64_t P) {
-  const uint32_t lane = threadIdx.x & 63;
-  uint64_t acc = 0, hi = P;
-  while (hi > first) {
-    const uint64_t span = hi - first < 64 ? hi - first : 64;
-    const bool in = lane < span;
-    const uint64_t j = hi - 1 - lane;
-    uint64_t s = 0;
-    int stop;
-    while (true) {
-      s = in ? __hip_atomic_load(st + j, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0;
-      const uint64_t inc = __ballot(in && (s >> 62) == 2);
-      stop = inc ? __ffsll(static_cast<long long>(inc)) - 1 : int(span) - 1;
-      const uint64_t need = stop >= 63 ? ~0ull : (2ull << stop) - 1;  // lanes 0..stop
-      if (__ballot(in && (s >> 62) == 0) & need) {
-        __builtin_amdgcn_s_sleep(8);
-        continue;
-      }
-      break;
-    }
-    uint64_t x = in && int(lane) <= stop ? (s & kLbValue) : 0;
+__device__ inline U128 wave_sum_carry(U128 x) {
 #pragma unroll
-    for (int m = 32; m > 0; m >>= 1) x += shfl_xor64(x, m);
-    acc += x;
-    const bool found = __ballot(in && int(lane) == stop && (s >> 62) == 2) != 0;
-    if (found) break;
-    hi -= span;
+  for (int m = 32; m > 0; m >>= 1) x = add128(x, U128{shfl_xor64(x.lo, m), shfl_xor64(x.hi, m)});
+  return x;
+}
+
+// The word count of a partition, by one wavefront that keeps none of its
+// values: the model of fit_wave_regs from three reads.  Only for a partition
+// whose own workgroup is late (lb_exclusive).
+__device__ inline uint64_t count_words(const EncColumn& c, uint64_t j) {
+  const uint32_t lane = threadIdx.x & 63;
+  uint64_t start, len;
+  part_bounds(c, j, start, len);
+  const uint8_t* src = c.col + c.dtype * start;
+  uint64_t lo = ~uint64_t(0), hi = 0;
+  for (uint64_t t = lane; t < len; t += 64) {
+    const uint64_t x = load_value(src, c.dtype, t);
+    lo = x < lo ? x : lo;
+    hi = x > hi ? x : hi;
+  }
+  const uint64_t vmin = wave_min(lo), range = wave_max(hi) - vmin;
+  Model md{vmin, vmin, 0.0, bitlen64(range), false, 0, range};
+  if (len > 1 && !c.force_constant && range < (uint64_t(1) << 61)) {
+    U128 s{0, 0}, st{0, 0};
+    for (uint64_t t = lane; t < len; t += 64) {
+      const uint64_t y = load_value(src, c.dtype, t) - vmin;
+      s = add128(s, U128{y, 0});
+      st = add128(st, mul64x64(t, y));
+    }
+    s = wave_sum_carry(s);
+    st = wave_sum_carry(st);
+    const double th = ls_slope(len, s, st);
+    int64_t rmin = INT64_MAX, rmax = INT64_MIN;
+    for (uint64_t t = lane; t < len; t += 64) {
+      const int64_t r =
+          int64_t(load_value(src, c.dtype, t) - vmin) - predict(th, uint32_t(t));
+      rmin = r < rmin ? r : rmin;
+      rmax = r > rmax ? r : rmax;
+    }
+    choose_model(md, th, wave_min(rmin), wave_max(rmax));
+  }
+  return (len * md.bits + 63) >> 6;
+}
+
+// Words of the column's partitions before P, by one wavefront: kLbWindow
+// predecessors per round (lane l reads the state of partition hi - 1 - l),
+// down to the nearest one with an inclusive prefix; rounds wait (sleeping
+// between reads) while a partition closer than that has published nothing
+// yet.  What these reads fetch past the L2s is what bounds a large launch, so
+// the window is no wider than the number in flight asks for: with 1024
+// workgroups 16 (2e8 u64 values in partitions of 4096 564 us; 64: 584, 256:
+// 751, 4: 739), with 4096 wavefronts 64 (1e8 u32 values in partitions of 1024
+// 287 us; 16: 367, 256: 560).
+//
+// Workgroups start in the order of their index here, so that a predecessor
+// is running or done; but nothing guarantees it, so the wait is bounded:
+// after `polls` reads the wavefront counts the nearest missing partition
+// itself and goes on.  (An index from an atomic counter is such a guarantee,
+// at 13 ns for each of its workgroups: 680 us for 48,800 of them.)
+template <uint32_t kLbWindow>
+__device__ inline uint64_t lb_exclusive(uint64_t* st, const EncColumn& c, uint64_t P,
+                                        uint32_t polls) {
+  const uint32_t lane = threadIdx.x & 63;
+  const uint64_t first = c.part_base;
+  uint64_t acc = 0, hi = P;
+  uint32_t left = polls;
+  while (hi > first) {
+    const uint64_t span = hi - first < kLbWindow ? hi - first : kLbWindow;
+    const bool in = lane < span;
+    const uint64_t s =
+        in ? __hip_atomic_load(st + (hi - 1 - lane), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0;
+    const uint64_t inc = __ballot(in && (s >> 62) == 2);
+    const int stop = inc ? __ffsll(static_cast<long long>(inc)) - 1 : int(span) - 1;
+    const uint64_t need = stop >= 63 ? ~0ull : (2ull << stop) - 1;  // lanes 0..stop
+    const uint64_t missing = __ballot(in && (s >> 62) == 0) & need;
+    if (missing == 0) {
+      acc += wave_sum_u64(in && int(lane) <= stop ? (s & kLbValue) : 0);
+      if (inc != 0) break;  // always, where the column's first partition is in the span
+      hi -= span;
+      left = polls;
+      continue;
+    }
+    if (left != 0) {
+      --left;
+      __builtin_amdgcn_s_sleep(8);
+      continue;
+    }
+    const uint64_t late = hi - uint64_t(__ffsll(static_cast<long long>(missing)));
+    const uint64_t nw = count_words(c, late - first);
+    unsigned long long none = 0;  // what its workgroup published meanwhile stays
+    if (lane == 0)
+      __hip_atomic_compare_exchange_strong(
+          reinterpret_cast<unsigned long long*>(st + late), &none,
+          (unsigned long long)((late == first ? kLbInclusive : kLbCount) | nw),
+          __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
   return acc;
+}
+
+constexpr uint32_t kFusedBits = 61;
+constexpr uint64_t kFusedFullLen = 3840;  // see launch_encode_columns
+
+struct FusedShared {
+  FitShared fit;
+  uint64_t woff;
+  uint64_t join[3][kEncWaves][2];  // one for each join of the fit: a barrier less than one reused
+  // each wavefront's 16 rounds of residuals, packed: 2 b words per round, for
+  // b <= kFusedBits (at 64 a fifth workgroup would not fit a CU's LDS)
+  uint32_t words[kEncWaves][2 * kFusedBits * kEncRegs];
+};
+
+// The narrow fit of fit_regs, in binary64: offsets below 2^30 are exact
+// there, and so are a lane's sums of 16 (below 2^34, and 2^38 times k); a
+// conversion, an addition and a fused multiply-add per value where 64-bit
+// integers took eight issue slots.  kFull: no position is masked.
+template <bool kFull>
+__device__ __attribute__((always_inline)) inline void fit_regs_narrow(
+    FusedShared& sh, const uint64_t (&v)[kEncRegs], uint32_t t0, uint64_t len, Model& md,
+    int32_t (&r32)[kEncRegs], bool& small) {
+  const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const uint32_t low = uint32_t(md.vmin);
+  double sy = 0.0, sk = 0.0;  // sums of y and of k y, position t0 + 64 k
+#pragma unroll
+  for (int k = 0; k < kEncRegs; ++k) {
+    const uint32_t y = kFull || t0 + 64 * k < len ? uint32_t(v[k]) - low : 0;
+    const double d = double(y);
+    sy += d;
+    sk = __builtin_fma(d, double(k), sk);
+  }
+  uint64_t s = f64_to_u64(sy), st = uint64_t(t0) * s + 64 * f64_to_u64(sk);  // < 2^42 and < 2^54
+  wave_sum_u64x2(s, st);
+  if (lane == 0) {
+    sh.join[1][wave][0] = s;
+    sh.join[1][wave][1] = st;
+  }
+  __syncthreads();
+  s = st = 0;
+#pragma unroll
+  for (int w = 0; w < kEncWaves; ++w) {
+    s += sh.join[1][w][0];
+    st += sh.join[1][w][1];
+  }
+  const double th = block_slope_narrow(sh.fit, len, s, st);
+  small = __dmul_rn(fabs(th), double(len)) < 1073741824.0;
+  if (!small) {
+    md.theta1 = th;
+    return;
+  }
+  int32_t mn = INT32_MAX, mx = INT32_MIN;
+  double t = double(t0);
+#pragma unroll
+  for (int k = 0; k < kEncRegs; ++k) {
+    r32[k] = int32_t(uint32_t(v[k]) - low) - int32_t(floor(__dmul_rn(th, t)));
+    t += 64.0;
+    if (kFull || t0 + 64 * k < len) {
+      mn = min(mn, r32[k]);
+      mx = max(mx, r32[k]);
+    }
+  }
+  mn = wave_min(mn);
+  mx = wave_max(mx);
+  if (lane == 0) {
+    sh.join[2][wave][0] = uint64_t(uint32_t(mn));
+    sh.join[2][wave][1] = uint64_t(uint32_t(mx));
+  }
+  __syncthreads();
+#pragma unroll
+  for (int w = 0; w < kEncWaves; ++w) {
+    mn = min(mn, int32_t(uint32_t(sh.join[2][w][0])));
+    mx = max(mx, int32_t(uint32_t(sh.join[2][w][1])));
+  }
+  choose_model(md, th, mn, mx);
 }
 
 // The model of a partition held in registers as described above.  When
 // the residuals v - vmin - floor(theta1 t) fit int32 (`small`), r32 keeps
 // them for the packing.
-__device__ __attribute__((always_inline)) inline Model fit_regs(FitShared& sh, const uint64_t (&v)[kEncRegs],
+__device__ __attribute__((always_inline)) inline Model fit_regs(FusedShared& sh, const uint64_t (&v)[kEncRegs],
                                                                uint32_t t0, uint64_t len,
                                                                bool force_constant,
                                                                int32_t (&r32)[kEncRegs],
                                                                bool& small_out) {
   small_out = false;
-  const bool full = len == kEncRegLen;  // no position needs masking
-  // clamped loads hold the partition's last value: min and max unchanged
-  uint64_t vmin = v[0], vmax = v[0];
+  const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  // clamped loads hold the partition's last value: min and max unchanged.
+  // While a wavefront's values agree in their high halves the low ones do.
+  const uint32_t high = uint32_t(__builtin_amdgcn_readfirstlane(int(uint32_t(v[0] >> 32))));
+  uint32_t apart = 0, mn = uint32_t(v[0]), mx = mn;
 #pragma unroll
-  for (int k = 1; k < kEncRegs; ++k) {
-    vmin = v[k] < vmin ? v[k] : vmin;
-    vmax = v[k] > vmax ? v[k] : vmax;
+  for (int k = 0; k < kEncRegs; ++k) {
+    const uint32_t x = uint32_t(v[k]);
+    apart |= uint32_t(v[k] >> 32) ^ high;
+    mn = x < mn ? x : mn;
+    mx = x > mx ? x : mx;
   }
-  block_minmax_u64(sh, vmin, vmax);
+  uint64_t vmin, vmax;
+  if (__ballot(apart != 0) == 0) {
+    vmin = uint64_t(high) << 32 | wave_min(mn);
+    vmax = uint64_t(high) << 32 | wave_max(mx);
+  } else {
+    vmin = vmax = v[0];
+#pragma unroll
+    for (int k = 1; k < kEncRegs; ++k) {
+      vmin = v[k] < vmin ? v[k] : vmin;
+      vmax = v[k] > vmax ? v[k] : vmax;
+    }
+    vmin = wave_min(vmin);
+    vmax = wave_max(vmax);
+  }
+  if (lane == 0) {
+    sh.join[0][wave][0] = vmin;
+    sh.join[0][wave][1] = vmax;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int w = 0; w < kEncWaves; ++w) {
+    vmin = sh.join[0][w][0] < vmin ? sh.join[0][w][0] : vmin;
+    vmax = sh.join[0][w][1] > vmax ? sh.join[0][w][1] : vmax;
+  }
   const uint64_t range = vmax - vmin;
   Model md{vmin, vmin, 0.0, bitlen64(range), false, 0, range};
-  if (len > 1 && !force_constant && range < (uint64_t(1) << 61)) {
-    double th;
-    bool small = false;
-    if (range < kNarrowRange) {
-      uint64_t sy = 0, sty = 0;  // < 2^42 and < 2^54
+  if (len <= 1 || force_constant || range >= (uint64_t(1) << 61)) return md;
+  double th;
+  if (range < kNarrowRange) {
+    if (len == kEncRegLen)
+      fit_regs_narrow<true>(sh, v, t0, len, md, r32, small_out);
+    else
+      fit_regs_narrow<false>(sh, v, t0, len, md, r32, small_out);
+    if (small_out) return md;
+    th = md.theta1;
+    md.theta1 = 0.0;
+  } else {
+    U128 sv{0, 0}, stv{0, 0};
 #pragma unroll
-      for (int k = 0; k < kEncRegs; ++k) {
-        const uint32_t t = t0 + 64 * k;
-        const uint64_t y = full || t < len ? uint32_t(v[k]) - uint32_t(vmin) : 0;
-        sy += y;
-        sty += uint64_t(t) * y;
-      }
-      block_sum_u64x2(sh, sy, sty);
-      th = block_slope(sh, len, U128{sy, 0}, U128{sty, 0});
-      small = __dmul_rn(fabs(th), double(len)) < 1073741824.0;
-    } else {
-      U128 sv{0, 0}, stv{0, 0};
-#pragma unroll
-      for (int k = 0; k < kEncRegs; ++k) {
-        const uint32_t t = t0 + 64 * k;
-        const uint64_t x = full || t < len ? v[k] : 0;
-        sv = add128(sv, U128{x, 0});
-        stv = add128(stv, mul64x64(t, x));
-      }
-      block_sum_u128x2(sh, sv, stv);
-      th = block_slope(sh, len, sv, stv);
+    for (int k = 0; k < kEncRegs; ++k) {
+      const uint32_t t = t0 + 64 * k;
+      const uint64_t x = t < len ? v[k] : 0;
+      sv = add128(sv, U128{x, 0});
+      stv = add128(stv, mul64x64(t, x));
     }
-    int64_t rmin = INT64_MAX, rmax = INT64_MIN;
-    if (small) {
-      int32_t mn = INT32_MAX, mx = INT32_MIN;
-#pragma unroll
-      for (int k = 0; k < kEncRegs; ++k) {
-        const uint32_t t = t0 + 64 * k;
-        r32[k] = int32_t(uint32_t(v[k]) - uint32_t(vmin)) - predict32(th, t);
-        if (full || t < len) {
-          mn = min(mn, r32[k]);
-          mx = max(mx, r32[k]);
-        }
-      }
-      block_minmax_i32(sh, mn, mx);
-      small_out = true;
-      choose_model(md, th, mn, mx);
-      return md;
-    } else {
-#pragma unroll
-      for (int k = 0; k < kEncRegs; ++k) {
-        const uint32_t t = t0 + 64 * k;
-        const int64_t rr = int64_t(v[k] - vmin) - predict(th, t);
-        if (t < len) {
-          rmin = rr < rmin ? rr : rmin;
-          rmax = rr > rmax ? rr : rmax;
-        }
-      }
-    }
-    block_minmax_i64(sh, rmin, rmax);
-    choose_model(md, th, rmin, rmax);
-    small_out = small;
+    block_sum_u128x2(sh.fit, sv, stv);
+    th = block_slope(sh.fit, len, sv, stv);
   }
+  int64_t rmin = INT64_MAX, rmax = INT64_MIN;
+#pragma unroll
+  for (int k = 0; k < kEncRegs; ++k) {
+    const uint32_t t = t0 + 64 * k;
+    const int64_t rr = int64_t(v[k] - vmin) - predict(th, t);
+    if (t < len) {
+      rmin = rr < rmin ? rr : rmin;
+      rmax = rr > rmax ? rr : rmax;
+    }
+  }
+  block_minmax_i64(sh.fit, rmin, rmax);
+  choose_model(md, th, rmin, rmax);
   return md;
 }
 
-struct FusedShared {
-  FitShared fit;
-  uint64_t P, woff;
-  // each wavefront's 16 rounds of residuals, packed: 2 b words per round
-  uint32_t words[kEncWaves][2 * 64 * kEncRegs];
-};
-
-// One workgroup per partition (its index from a ticket): values loaded
+// One workgroup per partition: values loaded
 // once, model fitted, word count published; the residuals packed into LDS
 // (which needs no offset) while the partitions before it publish theirs;
 // then the look-back, the record, and the packed words copied out.
 __device__ __attribute__((always_inline)) inline void encode_fused_part(
-    FusedShared& sh, const EncColumn& c, uint64_t P, const EncScratch& scr, int* err) {
+    FusedShared& sh, const EncColumn& c, uint64_t P, const EncScratch& scr, uint32_t polls,
+    int* err) {
   const uint32_t lane = threadIdx.x & 63;
   const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   uint64_t start, len;
@@ -1656,7 +1790,7 @@ __device__ __attribute__((always_inline)) inline void encode_fused_part(
   }
   int32_t r32[kEncRegs];
   bool small;
-  const Model md = fit_regs(sh.fit, v, t0, len, c.force_constant != 0, r32, small);
+  const Model md = fit_regs(sh, v, t0, len, c.force_constant != 0, r32, small);
   const uint64_t nw = (len * md.bits + 63) >> 6;
   uint64_t* st = scr.woff;
   if (threadIdx.x == 0) lb_publish(st, P, (j == 0 ? kLbInclusive : kLbCount) | nw);
@@ -1665,7 +1799,7 @@ __device__ __attribute__((always_inline)) inline void encode_fused_part(
   const uint64_t rounds = (len + 63) / 64;
   const uint64_t r0 = uint64_t(wave) * kEncRegs;
   const uint32_t nr = r0 >= rounds ? 0 : uint32_t(rounds - r0 < kEncRegs ? rounds - r0 : kEncRegs);
-  const uint32_t nwb = 2 * b * nr;
+  const uint32_t nwb = b <= kFusedBits ? 2 * b * nr : 0;
   uint32_t* w32 = sh.words[wave];
   if (nwb) {
     for (uint32_t q = lane; q < nwb; q += 64) w32[q] = 0;
@@ -1706,7 +1840,7 @@ __device__ __attribute__((always_inline)) inline void encode_fused_part(
     wave_fence();
   }
   if (j != 0 && wave == 0) {
-    const uint64_t before = lb_exclusive(st, c.part_base, P);
+    const uint64_t before = lb_exclusive<16>(st, c, P, polls);
     if (lane == 0) {
       lb_publish(st, P, kLbInclusive | (before + nw));
       sh.woff = before;
@@ -1729,26 +1863,31 @@ __device__ __attribute__((always_inline)) inline void encode_fused_part(
     }
     if (j + 1 == c.m) finish_column(c, woff + nw, err);
   }
-  if (nwb) {
+  if (b != 0 && nr != 0) {
     const auto gdst = global_ptr(reinterpret_cast<uint32_t*>(c.blob + c.words_off) + 2 * woff);
     const uint64_t cap_w32 = c.cap > c.words_off ? (c.cap - c.words_off) / 4 : 0;
     const uint64_t avail = cap_w32 > 2 * woff ? cap_w32 - 2 * woff : 0;
     const uint64_t limit = 2 * nw < avail ? 2 * nw : avail;
+    if (b > kFusedBits) {  // wider than the buffer: from the values, in batches
+      uint32_t* gw32 = reinterpret_cast<uint32_t*>(c.blob + c.words_off) + 2 * woff;
+      if (c.dtype == 8)  // 32-bit residuals are narrower
+        pack_rounds(reinterpret_cast<const uint64_t*>(c.col) + start, len, md.base, md.theta1, 0, 0.0,
+                    0.0, b, gw32, limit, r0, r0 + nr, w32);
+      return;
+    }
     const uint64_t first = 2 * b * r0;
     const uint64_t count = first >= limit ? 0 : (limit - first < nwb ? limit - first : nwb);
     for (uint32_t q = lane; q < count; q += 64) gdst[first + q] = w32[q];
   }
 }
 
-// Before a one-pass encode: the look-back states (scr.woff) and the ticket
-// (scr.bsum[0]) start at 0, and every empty column's blob is written whole
+// Before a one-pass encode: the look-back states (scr.woff) start at 0, and every empty column's blob is written whole
 // (one launch instead of two).
 __global__ void k_fused_prepare(const EncColumn* __restrict__ cols, uint64_t ncols,
                                 EncColumn single, EncScratch scr, uint64_t nparts, int* err) {
   const uint64_t stride = uint64_t(gridDim.x) * blockDim.x;
   const uint64_t first = uint64_t(blockIdx.x) * blockDim.x + threadIdx.x;
   for (uint64_t i = first; i < nparts; i += stride) scr.woff[i] = 0;
-  if (first == 0) scr.bsum[0] = 0;
   for (uint64_t i = first; i < ncols; i += stride) {
     const EncColumn& c = cols ? cols[i] : single;
     if (c.m == 0) finish_column(c, 0, err);
@@ -1757,24 +1896,19 @@ __global__ void k_fused_prepare(const EncColumn* __restrict__ cols, uint64_t nco
 
 __global__ __launch_bounds__(kEncBlock) __attribute__((amdgpu_waves_per_eu(4))) void k_encode_fused(
     const EncColumn* __restrict__ cols, uint64_t ncols, EncColumn single, uint64_t nparts,
-    EncScratch scr, int* err) {
+    EncScratch scr, uint32_t polls, int* err) {
   __shared__ FusedShared sh;
-  if (threadIdx.x == 0)
-    sh.P = atomicAdd(reinterpret_cast<unsigned long long*>(scr.bsum), 1ull);
-  __syncthreads();
-  const uint64_t Pw = sh.P;  // the same in every lane: made scalar
-  const uint64_t P = (uint64_t(uint32_t(__builtin_amdgcn_readfirstlane(int(uint32_t(Pw >> 32))))) << 32) |
-                     uint32_t(__builtin_amdgcn_readfirstlane(int(uint32_t(Pw))));
+  const uint64_t P = blockIdx.x;
   if (P >= nparts) return;
   const EncColumn c = column_of(cols, ncols, single, P);
-  encode_fused_part(sh, c, P, scr, err);
+  encode_fused_part(sh, c, P, scr, polls, err);
 }
 
 // Partition P of k_encode_fused_wave, of at most 64 kN values.
 template <int kN>
 __device__ __attribute__((always_inline)) inline void encode_fused_wave(
     const EncColumn& c, uint64_t P, uint64_t j, uint64_t start, uint64_t len,
-    const EncScratch& scr, uint32_t* w32, int* err) {
+    const EncScratch& scr, uint32_t polls, uint32_t* w32, int* err) {
   const uint32_t lane = threadIdx.x & 63;
   uint64_t v[kN];
   if (c.dtype == 8) {
@@ -1810,7 +1944,7 @@ __device__ __attribute__((always_inline)) inline void encode_fused_wave(
   }
   uint64_t woff = 0;
   if (j != 0) {
-    woff = lb_exclusive(st, c.part_base, P);
+    woff = lb_exclusive<64>(st, c, P, polls);
     if (lane == 0) lb_publish(st, P, kLbInclusive | (woff + nw));
   }
   if (lane == 0) {
@@ -1839,27 +1973,17 @@ __device__ __attribute__((always_inline)) inline void encode_fused_wave(
 }
 
 // The one-pass encoder for partitions of at most 64 kR values: one
-// wavefront per partition, no workgroup barrier after the ticket.  Values in
+// wavefront per partition, no workgroup barrier.  Values in
 // registers, model by wavefront shuffles, word count published, residuals
 // packed in the wavefront's LDS slice, look-back, record and words written.
 template <int kR>
 __global__ __launch_bounds__(kEncBlock) void k_encode_fused_wave(
     const EncColumn* __restrict__ cols, uint64_t ncols, EncColumn single, uint64_t nparts,
-    EncScratch scr, int* err) {
+    EncScratch scr, uint32_t polls, int* err) {
   __shared__ uint32_t words[kEncWaves][2 * 64 * kR];
-  __shared__ uint64_t ticket;
   const uint32_t lane = threadIdx.x & 63;
   const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  // one ticket per workgroup, whose waves take partitions 4 ticket ..
-  // 4 ticket + 3 (a ticket per wavefront, 2e6 device-scope atomics on one
-  // word for 2e9 values, doubled the time of such a launch)
-  if (threadIdx.x == 0)
-    ticket = atomicAdd(reinterpret_cast<unsigned long long*>(scr.bsum), 1ull);
-  __syncthreads();
-  const uint64_t tk = ticket;
-  const uint64_t P = kEncWaves * ((uint64_t(uint32_t(__builtin_amdgcn_readfirstlane(int(uint32_t(tk >> 32))))) << 32) |
-                                  uint32_t(__builtin_amdgcn_readfirstlane(int(uint32_t(tk))))) +
-                     wave;
+  const uint64_t P = uint64_t(blockIdx.x) * kEncWaves + wave;
   if (P >= nparts) return;
   const EncColumn c = column_of(cols, ncols, single, P);
   uint64_t start, len;
@@ -1870,7 +1994,7 @@ __global__ __launch_bounds__(kEncBlock) void k_encode_fused_wave(
     return;
   }
   by_length<kR, kShortRegs>(len, [&](auto r) __attribute__((always_inline)) {
-    encode_fused_wave<r.n>(c, P, j, start, len, scr, words[wave], err);
+    encode_fused_wave<r.n>(c, P, j, start, len, scr, polls, words[wave], err);
   });
 }
 
@@ -1953,14 +2077,19 @@ hipError_t launch_encode_columns(leco_ctx* ctx, const EncColumn* cols_dev, uint6
   const bool wave_fit = max_len <= kWaveEncMax ||
                         (max_len <= 2 * kWaveEncMax && ctx->tune.encode_wave32);
   const uint64_t pw = (nparts + kEncWaves - 1) / kEncWaves;
-  const auto fused = [&](uint32_t mode, uint64_t workgroups) {
-    return mode == 1 || (mode == 2 && workgroups <= uint64_t(kFusedAutoPerCu) * ctx->num_cus);
+  const auto fused = [&](uint32_t mode, uint64_t workgroups, uint64_t per_cu) {
+    return mode == 1 || (mode == 2 && workgroups <= per_cu * ctx->num_cus);
   };
   const bool one_pass_wave = nparts != 0 && regs == kRegLS && ctx->tune.encode_wave &&
-                             max_len <= kWaveEncMax && fused(ctx->tune.encode_fused_wave, pw);
+                             max_len <= kWaveEncMax && fused(ctx->tune.encode_fused_wave, pw, kFusedWavePerCu);
+  // One read of the column instead of two pays where the workgroups' registers
+  // are full: 1e8 u64 values in partitions of 4096 288 us for 333, of 4000 305
+  // for 332, of 3500 340 for 323; u32 values 250 for 229.
+  const bool full = cols_dev == nullptr && single.dtype == 8 && single.fixed_len > kFusedFullLen;
   const bool one_pass = nparts != 0 && regs == kRegLS && !one_pass_wave &&
                         max_len <= kEncRegLen && !(wave_fit && ctx->tune.encode_wave) &&
-                        fused(ctx->tune.encode_fused, nparts);
+                        (fused(ctx->tune.encode_fused, nparts, kFusedPerCu) ||
+                         (full && ctx->tune.encode_fused == 2));
   if (one_pass_wave || one_pass) {
     const uint64_t items = nparts > ncols ? nparts : ncols;
     const uint64_t g = (items + 255) / 256;
@@ -1968,10 +2097,12 @@ hipError_t launch_encode_columns(leco_ctx* ctx, const EncColumn* cols_dev, uint6
                        cols_dev, ncols, single, scr, nparts, ctx->err_dev);
     if (one_pass_wave)
       hipLaunchKernelGGL(k_encode_fused_wave<kWaveRegs>, dim3(uint32_t(pw)), dim3(kEncBlock), 0,
-                         stream, cols_dev, ncols, single, nparts, scr, ctx->err_dev);
+                         stream, cols_dev, ncols, single, nparts, scr, ctx->tune.lookback_polls,
+                         ctx->err_dev);
     else
       hipLaunchKernelGGL(k_encode_fused, dim3(uint32_t(nparts)), dim3(kEncBlock), 0, stream,
-                         cols_dev, ncols, single, nparts, scr, ctx->err_dev);
+                         cols_dev, ncols, single, nparts, scr, ctx->tune.lookback_polls,
+                         ctx->err_dev);
     return hipGetLastError();
   }
   if (nparts != 0) {

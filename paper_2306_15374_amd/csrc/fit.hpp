@@ -209,11 +209,39 @@ __device__ inline double ls_slope(uint64_t len, U128 sv, U128 stv) {
   return slope;
 }
 
+// The same for at most 4096 values less than 2^30 above the smallest (sy < 2^42
+// and sty < 2^54), in about a third of the operations: N in two parts whose
+// binary64 products and differences are exact (below 2^47), joined by one
+// rounding, and D = n^2 (n^2 - 1) / 12 < 2^45, exact (4 divides n^2 (n^2 - 1),
+// and a multiple of 3 is divided by 3's inverse modulo 2^64).
+__device__ inline double ls_slope_narrow(uint64_t len, uint64_t sy, uint64_t sty) {
+  const uint32_t n = uint32_t(len), n2 = n * n, mask = (1u << 22) - 1;  // n^2 <= 2^24
+  const double dn = double(n), st = double(n * (n - 1) / 2);
+  const double hi = __builtin_fma(dn, double(uint32_t(sty >> 22)),
+                                  -__dmul_rn(st, double(uint32_t(sy >> 22))));
+  const double lo = __builtin_fma(dn, double(uint32_t(sty) & mask),
+                                  -__dmul_rn(st, double(uint32_t(sy) & mask)));
+  const uint64_t D = (uint64_t(n2) * (n2 - 1) / 4) * 0xaaaaaaaaaaaaaaabull;
+  double slope = __builtin_fma(hi, 4194304.0, lo) / u64_to_f64(D);
+  if (slope == 0.0) slope = 0.0;  // +0.0, never -0.0
+  return slope;
+}
+
 // The slope computed once (by wave 0) and broadcast through LDS.
 template <class Sh>
 __device__ inline double block_slope(Sh& sh, uint64_t len, U128 sv, U128 stv) {
   if ((threadIdx.x >> 6) == 0) {
     const double th = ls_slope(len, sv, stv);
+    if (threadIdx.x == 0) sh.theta1 = th;
+  }
+  __syncthreads();
+  return sh.theta1;
+}
+
+template <class Sh>
+__device__ inline double block_slope_narrow(Sh& sh, uint64_t len, uint64_t sy, uint64_t sty) {
+  if ((threadIdx.x >> 6) == 0) {
+    const double th = ls_slope_narrow(len, sy, sty);
     if (threadIdx.x == 0) sh.theta1 = th;
   }
   __syncthreads();

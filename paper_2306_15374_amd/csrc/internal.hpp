@@ -21,15 +21,23 @@ struct Tune {
   // One pass over the column with a decoupled look-back: a workgroup per
   // partition (partitions of 2049..4096) or a wavefront per partition (at
   // most 1024).  0 = never, 1 = always where it applies, 2 = for launches of
-  // at most kFusedAutoPerCu workgroups per CU.
+  // at most kFusedPerCu or kFusedWavePerCu workgroups per CU, and for 8-byte
+  // columns in partitions that nearly fill a workgroup's registers.
   uint32_t encode_fused = 2;
   uint32_t encode_fused_wave = 2;
+  // Reads of a late predecessor's state before a one-pass encoder's wavefront
+  // counts that partition itself (about 1 us each).
+  uint32_t lookback_polls = 256;
 };
 
-// Past about two workgroups per CU (2e6 8-byte values at partitions of 1024
-// or 4096) the two-pass encoder is faster; below, its seven launches cost more
-// than the one-pass kernel's look-back.
-constexpr uint32_t kFusedAutoPerCu = 2;
+// A wavefront per partition: up to two workgroups per CU (1e6 u32 values in
+// partitions of 1024 17.6 us in two passes, 15.2 in one; of four per CU in
+// partitions of 128 14.5 and 16.0).  A workgroup per partition: while all of
+// them are resident, four per CU (4.2e6 values in partitions of 4096 u64 24.2
+// and 19.2, u32 22.4 and 19.3; 8e6 u64 values in partitions of 2049, 15 per
+// CU, 46.0 and 52.3).
+constexpr uint32_t kFusedWavePerCu = 2;
+constexpr uint32_t kFusedPerCu = 4;
 
 // Reads LECO_TILE_LOG2, LECO_DECODE_BLOCKS_PER_CU, LECO_XCD_REMAP,
 // LECO_RA_LPT, LECO_ENCODE_WAVE, LECO_ENCODE_WAVE32, LECO_ENCODE_FUSED and
