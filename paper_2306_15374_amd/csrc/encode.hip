@@ -1470,6 +1470,89 @@ __global__ __launch_bounds__(kEncBlock) __attribute__((amdgpu_waves_per_eu(5))) 
                 b, gw32, limit, k_begin, k_end, lds[wave]);
 }
 
+// Packs partitions of kPackShortMin to kPackShortMax values of one column,
+// as many per wavefront as make up to 512 values: 64 consecutive values of the
+// column per round, each with its own partition's model from LDS, into words
+// that are consecutive in the blob.  With a wavefront per partition a short
+// one pays the latency of its metadata, and a round of its last few values, for
+// itself.  magic = 2^20 / fixed_len + 1: position * magic >> 20 is the partition (exact
+// below 512 positions and lengths to 256).
+constexpr uint64_t kPackShortMin = 32, kPackShortMax = 256;
+constexpr uint32_t kPackShortValues = 64 * kPackBatch;
+constexpr uint32_t kPackShortParts = kPackShortValues / uint32_t(kPackShortMin);
+
+struct ShortPart {
+  uint64_t base;
+  double theta1;
+  uint32_t bit0, bits;  // first bit among the wavefront's words, residual width
+};
+
+template <class T>
+__device__ __attribute__((always_inline)) inline void pack_short(
+    const EncColumn& c, uint64_t P0, uint32_t count, uint32_t magic, const EncScratch& scr,
+    ShortPart* part, uint32_t* w32) {
+  const uint32_t lane = threadIdx.x & 63;
+  const uint32_t L = uint32_t(c.fixed_len);
+  const uint64_t start = P0 * L;
+  const uint32_t n = uint32_t(c.n - start < uint64_t(count) * L ? c.n - start : uint64_t(count) * L);
+  const uint64_t woff = meta_load(scr.woff, P0);
+  const uint64_t words = meta_load(scr.woff, P0 + count - 1) + meta_load(scr.nwords, P0 + count - 1) - woff;
+  if (words == 0) return;
+  const T* src = reinterpret_cast<const T*>(c.col) + start;
+  uint64_t u[kPackBatch];
+#pragma unroll
+  for (uint32_t r = 0; r < kPackBatch; ++r) u[r] = load_clamped(src, 64 * r + lane, n);
+  bool fits = true;
+  if (lane < count) {
+    const uint64_t P = P0 + lane;
+    const double theta1 = __longlong_as_double(static_cast<long long>(scr.theta[P]));
+    part[lane] = ShortPart{scr.base[P], theta1, uint32_t(64 * (scr.woff[P] - woff)), scr.bits[P]};
+    fits = prediction_fits_i32(theta1, L);
+  }
+  const bool fits32 = __ballot(!fits) == 0;
+  const uint32_t nw = 2 * uint32_t(words);  // <= 2 kPackShortValues
+  for (uint32_t q = lane; q < nw; q += 64) w32[q] = 0;
+  wave_fence();
+#pragma unroll
+  for (uint32_t r = 0; r < kPackBatch; ++r) {
+    const uint32_t f = 64 * r + lane;
+    if (f < n) {
+      const uint32_t i = f * magic >> 20, t = f - i * L;
+      const ShortPart m = part[i];
+      uint64_t p;
+      if (c.regressor == 2 && scr.kind[P0 + i]) {
+        const uint32_t len = n - i * L < L ? n - i * L : L;
+        p = uint64_t(poly_predict(m.theta1, __longlong_as_double(static_cast<long long>(scr.c2[P0 + i])),
+                                  __longlong_as_double(static_cast<long long>(scr.c3[P0 + i])), t, len));
+      } else {
+        p = fits32 ? uint64_t(int64_t(predict32(m.theta1, t))) : uint64_t(predict(m.theta1, t));
+      }
+      or_bits(w32, m.bit0 + t * m.bits, m.bits, (u[r] - m.base) - p);
+    }
+  }
+  wave_fence();
+  const uint64_t cap_w32 = c.cap > c.words_off ? (c.cap - c.words_off) / 4 : 0;
+  const uint64_t avail = cap_w32 > 2 * woff ? cap_w32 - 2 * woff : 0;
+  const uint32_t limit = nw < avail ? nw : uint32_t(avail);
+  const auto gdst = global_ptr(reinterpret_cast<uint32_t*>(c.blob + c.words_off) + 2 * woff);
+  for (uint32_t q = lane; q < limit; q += 64) gdst[q] = w32[q];
+}
+
+__global__ __launch_bounds__(kEncBlock) void k_pack_short(EncColumn c, uint64_t nparts,
+                                                         uint32_t per, uint32_t magic,
+                                                         EncScratch scr) {
+  __shared__ uint32_t lds[kEncWaves][2 * kPackShortValues];
+  __shared__ ShortPart part[kEncWaves][kPackShortParts];
+  const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const uint64_t P0 = (uint64_t(blockIdx.x) * kEncWaves + wave) * per;
+  if (P0 >= nparts) return;
+  const uint32_t count = uint32_t(nparts - P0 < per ? nparts - P0 : per);
+  if (c.dtype == 8)
+    pack_short<uint64_t>(c, P0, count, magic, scr, part[wave], lds[wave]);
+  else
+    pack_short<uint32_t>(c, P0, count, magic, scr, part[wave], lds[wave]);
+}
+
 // ---- one pass: fit, word offset by look-back, record and pack ----------------------
 //
 // For least-squares columns whose partitions hold at most kEncRegLen
@@ -2133,7 +2216,18 @@ hipError_t launch_encode_columns(leco_ctx* ctx, const EncColumn* cols_dev, uint6
     hipLaunchKernelGGL(k_layout<kEncBlock>, dim3(uint32_t(lg)), dim3(kEncBlock), 0, stream,
                        cols_dev, ncols, single, nparts, scr, mode, ctx->err_dev);
   if (nparts == 0) return hipGetLastError();
-  if (wave)
+  // Several short partitions to a wavefront once that leaves a wavefront for
+  // every SIMD, or four where few share one: 1e6 u32 values in partitions of
+  // 64 25.7 us, so 22.3, of 128 18.5 and 17.6, but of 256 15.3 and 15.5 (5e7
+  // values: 605 and 374, 317 and 225, 188 and 153).
+  const uint64_t per = single.fixed_len ? kPackShortValues / single.fixed_len : 0;
+  const uint64_t waves = uint64_t(ctx->num_cus) * (single.fixed_len <= 128 ? 4 : 16);
+  if (wave && cols_dev == nullptr && single.fixed_len >= kPackShortMin &&
+      single.fixed_len <= kPackShortMax && nparts >= per * waves)
+    hipLaunchKernelGGL(k_pack_short, dim3(uint32_t((nparts + per * kEncWaves - 1) / (per * kEncWaves))),
+                       dim3(kEncBlock), 0, stream, single, nparts, uint32_t(per),
+                       uint32_t((1u << 20) / single.fixed_len + 1), scr);
+  else if (wave)
     hipLaunchKernelGGL(k_pack<true>, dim3(uint32_t(pw)), dim3(kEncBlock), 0, stream, cols_dev,
                        ncols, single, nparts, scr);
   else

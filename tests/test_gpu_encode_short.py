@@ -53,3 +53,18 @@ def test_mixed_lengths(codec, ref, dtype):
     col = column(int(starts[-1]), dtype, 1 << 18, 9)
     got = codec.encode(torch.from_numpy(col).cuda(), starts=starts)
     assert np.array_equal(got.cpu().numpy(), ref.encode(col, starts=starts))
+
+
+@pytest.mark.parametrize("regressor", ["ls", "minimax", "poly"])
+@pytest.mark.parametrize("dtype,top", [(np.uint32, 1 << 16), (np.uint64, 1 << 40), (np.uint64, 1 << 63)])
+def test_many_short(codec, ref, regressor, dtype, top):
+    """Enough partitions for several to a wavefront, lengths at the limits of
+    that packing, and last partitions of one value and of all but one."""
+    import torch
+    for L in (31, 32, 33, 64, 100, 127, 170, 171, 255, 256, 257):
+        for rest in (1, L - 1):
+            n = L * ((1024 if L <= 128 else 4096) * max(1, 512 // L) + 3) + rest
+            col = column(n, dtype, top, L)
+            print(f"[short] many {regressor} {np.dtype(dtype)} L={L} n={n}", flush=True)
+            got = codec.encode(torch.from_numpy(col).cuda(), fixed_len=L, regressor=regressor)
+            assert np.array_equal(got.cpu().numpy(), ref.encode(col, fixed_len=L, regressor=regressor)), (L, n)
