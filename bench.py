@@ -748,7 +748,7 @@ def bench_encode_latency(args):
     """Encode time of one sorted-key uint64 column from 1e4 to 1e8 values at
     partitions of 1024 and 4096, launches back to back on one stream: the
     default context (a one-pass encoder for launches of at most two
-    workgroups per CU, else two passes) against one with the one-pass
+    or four workgroups per CU, else two passes) against one with the one-pass
     encoders off.  Both contexts' blobs are compared byte for byte."""
     import torch
     import paper_2306_15374_amd as P

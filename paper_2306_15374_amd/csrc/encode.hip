@@ -517,8 +517,9 @@ __device__ __attribute__((always_inline)) inline Model fit_block(FitShared& sh, 
 }
 
 // Six waves per SIMD (at most 80 VGPRs; 114 unconstrained): the extra
-// waves of loads in flight outweigh the registers the 128-bit-sum path
-// spills.  Encode of 2e8 u64 values at L 4096: sorted keys 0.73-0.74 ->
+// waves of loads in flight outweigh the 26 registers the 128-bit-sum path
+// spills.  (8-byte partitions of 3841..4096 values take one pass since.)
+// Encode of 2e8 u64 values at L 4096: sorted keys 0.73-0.74 ->
 // 0.70 ms (0.76 at four waves), a noisy line 0.66 -> 0.64 ms; partitions
 // spanning 2^30 or more, which take that path, 1.07 -> 1.22 ms.
 __global__ __launch_bounds__(kEncBlock) __attribute__((amdgpu_waves_per_eu(6))) void k_fit_block(
@@ -1426,7 +1427,8 @@ __device__ __attribute__((always_inline)) inline void pack_rounds(const T* src, 
 // One wavefront per partition (kWave, four per workgroup), or one workgroup
 // per partition whose four wavefronts take consecutive quarters of its
 // rounds (each a whole number of batches).  Five waves per SIMD, as
-// k_fit_block (95 VGPRs instead of 105, no spills).
+// the fit had (95 VGPRs instead of 105; 4 spilled per wavefront-partition
+// kernel since its last batch has sizes of its own).
 template <bool kWave>
 __global__ __launch_bounds__(kEncBlock) __attribute__((amdgpu_waves_per_eu(5))) void k_pack(
     const EncColumn* __restrict__ cols, uint64_t ncols, EncColumn single, uint64_t nparts,
