@@ -100,12 +100,18 @@ __device__ __attribute__((always_inline)) inline int strip_slope(StripPoint<C> f
   return 2;
 }
 
-// The width a line must stay below to be stored instead of a model of
-// `bits` > 0 bits, with a margin for the stored predictions: floors of
-// binary64 products, which differ from theta t by less than 1, plus up to 1
-// where a product rounds up onto an integer.  Residuals spanning 2^(bits-1)
-// or more need `bits` bits again; they span more than W - 2.
-__device__ inline int64_t strip_beat(uint32_t bits) { return (int64_t(1) << (bits - 1)) + 3; }
+// The width from which a line cannot be stored instead of a model of `bits` >
+// 0 bits, for offsets of range `range` < 2^61.  A stored prediction is floor(q),
+// q the binary64 product, and q is within e of theta t: theta is rounded once
+// or (from 2^53 on, where dy is no binary64 number) twice and the product
+// once, so e <= 3 2^-53 |theta t|, and |theta t| <= 2 range at the minimiser,
+// whose width is at most that of slope 0.  Residuals therefore span more than
+// W - 1 - 2e, with 2e <= 3 2^-51 range, and 2^(bits-1) or more need `bits`
+// bits again.  (A margin of 3 whatever the range lost lines from about 2^56
+// on.)  Below 2^49 the range adds nothing.
+__device__ inline int64_t strip_beat(uint32_t bits, uint64_t range) {
+  return (int64_t(1) << (bits - 1)) + 3 + int64_t(range >> 49);
+}
 
 // Binary64 keys are exact for partitions of at most 2^log2s values (S =
 // 2^log2s, log2s <= 20) whose range is below this; offsets fit 32 bits.
@@ -204,7 +210,7 @@ __device__ __attribute__((always_inline)) inline int strip_slope_regs(
     return touch_of(kmx, kmn, ey, et, S, 1.0 / S);
   };
   return strip_slope<double, double>({0.0, y_first}, {double(len - 1), y_last},
-                                     double(strip_beat(bits)), touch, dy, dt);
+                                     double(strip_beat(bits, 0)), touch, dy, dt);
 }
 
 // The same for a partition of any length, its values read again in each
@@ -234,7 +240,7 @@ __device__ __attribute__((always_inline)) inline int strip_slope_stream(
     double dy, dt;
     const int r = strip_slope<double, double>({0.0, double(offset(0))},
                                               {double(len - 1), double(offset(len - 1))},
-                                              double(strip_beat(bits)), touch, dy, dt);
+                                              double(strip_beat(bits, range)), touch, dy, dt);
     theta = dy / dt;
     return r;
   }
@@ -265,7 +271,7 @@ __device__ __attribute__((always_inline)) inline int strip_slope_stream(
   int64_t dy, dt;
   const int r = strip_slope<int64_t, __int128>({0, int64_t(offset(0))},
                                                {int64_t(len - 1), int64_t(offset(len - 1))},
-                                               __int128(strip_beat(bits)), touch, dy, dt);
+                                               __int128(strip_beat(bits, range)), touch, dy, dt);
   if (r == 1 && range >> 53) {
     // dy and its multiples may round differently: the fraction is that of
     // the upper touching points' whole edge, or when there is one point, of
