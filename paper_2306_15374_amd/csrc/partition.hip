@@ -1735,22 +1735,20 @@ __device__ __attribute__((always_inline)) inline bool merge_walk(
             for (uint32_t q = 0; q < cnt; ++q) {
               const uint64_t tq = t0 + q;
               if (lin && tq < len_l) {
-                const int64_t rr = int64_t(uint64_t(__double_as_longlong(w.scan[q]))) -
-                                   predict(th, uint32_t(tq));
+                // counted from the thread's own smallest value: below kWide
+                // for the values of its union, wherever the batch's others lie
+                const uint64_t y = uint64_t(__double_as_longlong(w.scan[q])) - (vmin - all.vmin);
+                const int64_t rr = int64_t(y) - predict(th, uint32_t(tq));
                 rmin = rr < rmin ? rr : rmin;
                 rmax = rr > rmax ? rr : rmax;
               }
             }
           }
         }
+        // likewise (the batch's spread is below 2^50 there)
         if (narrow64 && mn <= mx) {
-          rmin = int64_t(mn);
-          rmax = int64_t(mx);
-        }
-        // counted from the thread's own smallest value
-        if (rmin <= rmax) {
-          rmin -= int64_t(vmin - all.vmin);
-          rmax -= int64_t(vmin - all.vmin);
+          rmin = int64_t(mn) - int64_t(vmin - all.vmin);
+          rmax = int64_t(mx) - int64_t(vmin - all.vmin);
         }
       };
       // a batch of one: its slope (thread 0's) and a scan by all threads
