@@ -300,20 +300,6 @@ __device__ bool greedy_walk(const uint8_t* __restrict__ col, uint32_t dtype, uin
     const bool valid = j < b;
     K d = make_key(static_cast<K*>(nullptr), 0, 0);
     if (valid) d = make_key(static_cast<K*>(nullptr), win[j - base + 1], win[j - base]);
-    // Differences within the partition's own leave D~ alone, so that each of
-    // these values costs D~: no scan where that is allowed, none of them must
-    // begin a partition and all have room.  One partition of 2e5 u64 values
-    // took 4.8 ms (in order, 64 values per 1.4 us) and takes 2.3.
-    const bool start_here = forced && valid && ((forced[j >> 6] >> (j & 63)) & 1ull);
-    if (have && double(w_old) <= thr) {
-      const uint64_t count = b - p < 64 ? b - p : 64;
-      const bool apart = valid && (start_here || key_less(d, kmin) || key_less(kmax, d));
-      if (__ballot(apart) == 0 && p + count - 1 - i < max_len) {
-        if (kFix && lane == 0) clear_bits(bitmap, p, p + count);
-        p += count;
-        continue;
-      }
-    }
     // inclusive prefix min / max over the lanes up to this one; the invalid
     // lanes are the last ones and never feed a valid lane
     K mn = d, mx = d;
@@ -334,6 +320,7 @@ __device__ bool greedy_walk(const uint8_t* __restrict__ col, uint32_t dtype, uin
     if (lane == 0) w_prev = w_old;
     const uint64_t len = j - i;
     const int64_t cost = int64_t((len + 1) * w_new) - int64_t(len * w_prev);
+    const bool start_here = forced && valid && ((forced[j >> 6] >> (j & 63)) & 1ull);
     const bool in_start = forced && valid && ((inside[j >> 6] >> (j & 63)) & 1ull);
     const bool include = len < max_len && !start_here && (in_start || double(cost) <= thr);
     const uint64_t split = __ballot(valid && !include);
@@ -345,6 +332,21 @@ __device__ bool greedy_walk(const uint8_t* __restrict__ col, uint32_t dtype, uin
       w_old = uint32_t(__shfl(int(w_new), last, 64));
       have = true;
       p += uint64_t(last) + 1;
+      // Differences within the partition's own leave D~ alone, so that each
+      // of their values costs D~: whole steps without a scan where that is
+      // allowed, none of them must begin a partition and all have room.  One
+      // partition of 2e5 u64 values took 4.8 ms (in order, 64 values per 1.4
+      // us) and takes 1.9.
+      if (double(w_old) <= thr) {
+        for (; p + 64 <= wend && p + 63 - i < max_len; p += 64) {
+          const uint64_t x = p + lane;
+          const K e = make_key(static_cast<K*>(nullptr), win[x - base + 1], win[x - base]);
+          bool apart = key_less(e, kmin) || key_less(kmax, e);
+          if (forced) apart = apart || ((forced[x >> 6] >> (x & 63)) & 1ull);
+          if (__ballot(apart) != 0) break;
+          if (kFix && lane == 0) clear_bits(bitmap, p, p + 64);
+        }
+      }
     } else {
       const uint64_t js = p + uint64_t(__ffsll(static_cast<long long>(split)) - 1);
       if (kFix) {
