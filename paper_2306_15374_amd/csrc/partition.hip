@@ -1097,6 +1097,7 @@ constexpr uint64_t kHullBuildMin = 128;        // shorter partitions are scanned
 constexpr uint64_t kHullBuildNow = 2048;       // longer ones get hulls after kSoloMerges merges
 constexpr uint32_t kSoloMerges = 8;            // (a build costs about what 16 whole scans do)
 constexpr uint64_t kBatchNew = 1024;           // values a batch may add
+constexpr uint64_t kReachMin = 64, kReachMax = 512;  // and without hulls, at least (reach)
 constexpr uint64_t kSoloMin = 256;             // longer neighbours: sized alone without hulls
 constexpr uint64_t kHullAppendMax = 8192;      // and longer than this with them
 constexpr uint64_t kDeadScanMax = 16384;       // longest partition a batch scans whole without hulls
@@ -1561,6 +1562,12 @@ __device__ __attribute__((always_inline)) inline bool merge_walk(
   uint64_t vb = 0, ve = 0;  // values staged (column positions)
   uint64_t sa = s[st.a];
   uint32_t solo = 0;        // merges sized one at a time since the last refusal
+  // Values a batch without hulls may add at least: twice as many as the longer
+  // of the last two merged partitions got to hold.  Where chains end after a
+  // merge or two, scans of 512 more values were most of a batch: 2e5 values in
+  // clusters of 40, split around starting partitions, 6.8 ms and now 3.6.  (64
+  // everywhere: merges of long lines 11% slower.)
+  uint64_t reach = kReachMax, held = kReachMax / 2;
   while (k < ke) {
     if (st.a + 1 == k) {
       // No merge pending: the next kWalk steps are decided from the sizes
@@ -1677,7 +1684,7 @@ __device__ __attribute__((always_inline)) inline bool merge_walk(
       const bool via_hull = hr.state == kHullValid;
       const uint64_t j = k + tid;
       const uint64_t len0 = lold + l0;
-      uint64_t lcap = via_hull ? lold + kBatchNew : len0 + (len0 > 512 ? len0 : 512);
+      uint64_t lcap = via_hull ? lold + kBatchNew : len0 + (len0 > reach ? len0 : reach);
       if (lcap > max_len) lcap = max_len;
       const uint64_t e_l = j < w1 ? w.s[j - w0 + 1] : 0;
       const bool act = j < w1 && (tid == 0 || e_l - sa <= lcap);
@@ -1718,20 +1725,25 @@ __device__ __attribute__((always_inline)) inline bool merge_walk(
       const double pmax = __dmul_rn(fabs(th), double(len_l));  // bounds every |product|
       int64_t rmin = INT64_MAX, rmax = INT64_MIN;
       uint32_t bits = bitlen64(range);
-      // the values of [tb, lmax) staged in LDS, each read by every thread at
+      // the unions that a line is fitted to are the first ones; only their
+      // values need a scan (1e5 values in clusters of 40, far apart: 3.2 ms
+      // and now 2.7)
+      const uint32_t nlin = spread < kWide ? nact : first_of(w, 2, !lin);
+      const uint64_t lscan = nlin ? w.s[k - w0 + nlin] - sa : 0;
+      // the values of [tb, lscan) staged in LDS, each read by every thread at
       // once, every thread predicting with its own slope; with narrow64 (in
       // every thread) offsets and predictions below 2^50, exact in binary64
       const auto scan = [&](uint64_t tb, bool narrow64) {
         double mx = -__builtin_inf(), mn = __builtin_inf();
         const double own = lin ? double(uint32_t(len_l)) : 0.0;
-        for (uint64_t t0 = tb; t0 < lmax; t0 += kWalk) {
+        for (uint64_t t0 = tb; t0 < lscan; t0 += kWalk) {
           const uint64_t t = t0 + tid;
-          const uint32_t cnt = lmax - t0 < kWalk ? uint32_t(lmax - t0) : kWalk;
+          const uint32_t cnt = lscan - t0 < kWalk ? uint32_t(lscan - t0) : kWalk;
           __syncthreads();  // every read of the block before is done
-          const uint64_t x = t < lmax ? read(t) - all.vmin : 0;
+          const uint64_t x = t < lscan ? read(t) - all.vmin : 0;
           // past the end: NaN, which maximum and minimum pass over
           if (narrow64)
-            w.scan[tid] = t < lmax ? double(x) : __builtin_nan("");
+            w.scan[tid] = t < lscan ? double(x) : __builtin_nan("");
           else
             w.scan[tid] = __longlong_as_double(static_cast<long long>(x));
           __syncthreads();
@@ -1832,7 +1844,10 @@ __device__ __attribute__((always_inline)) inline bool merge_walk(
       continue;
     }
     // step k+f refuses: boundary k+f is kept and partition k+f is current
-    const uint64_t kk = k + f;
+    const uint64_t kk = k + f, lnow = w.s[kk - w0] - sa;
+    reach = 2 * (held > lnow ? held : lnow);
+    reach = reach < kReachMin ? kReachMin : (reach > kReachMax ? kReachMax : reach);
+    held = lnow;
     // (one thread reads the bit: another's read might follow the write below)
     bool met = false;
     if (kFix) {
