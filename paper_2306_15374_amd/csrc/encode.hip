@@ -1680,7 +1680,6 @@ __device__ inline uint64_t lb_exclusive(uint64_t* st, const EncColumn& c, uint64
   return acc;
 }
 
-constexpr uint32_t kFusedBits = 61;
 constexpr uint64_t kFusedFullLen = 3840;  // see launch_encode_columns
 
 struct FusedShared {
@@ -1688,8 +1687,10 @@ struct FusedShared {
   uint64_t woff;
   uint64_t join[3][kEncWaves][2];  // one for each join of the fit: a barrier less than one reused
   // each wavefront's 16 rounds of residuals, packed: 2 b words per round, for
-  // b <= kFusedBits (at 64 a fifth workgroup would not fit a CU's LDS)
-  uint32_t words[kEncWaves][2 * kFusedBits * kEncRegs];
+  // every b (4 workgroups to a CU, as many as its registers allow; wider than
+  // 61 bits from a second read of the values, 5e7 full-width values took 254
+  // us in partitions of 4096, more than two passes' 243, and take 202)
+  uint32_t words[kEncWaves][2 * 64 * kEncRegs];
 };
 
 // The narrow fit of fit_regs, in binary64: offsets below 2^30 are exact
@@ -1884,7 +1885,7 @@ __device__ __attribute__((always_inline)) inline void encode_fused_part(
   const uint64_t rounds = (len + 63) / 64;
   const uint64_t r0 = uint64_t(wave) * kEncRegs;
   const uint32_t nr = r0 >= rounds ? 0 : uint32_t(rounds - r0 < kEncRegs ? rounds - r0 : kEncRegs);
-  const uint32_t nwb = b <= kFusedBits ? 2 * b * nr : 0;
+  const uint32_t nwb = 2 * b * nr;
   uint32_t* w32 = sh.words[wave];
   if (nwb) {
     for (uint32_t q = lane; q < nwb; q += 64) w32[q] = 0;
@@ -1948,18 +1949,11 @@ __device__ __attribute__((always_inline)) inline void encode_fused_part(
     }
     if (j + 1 == c.m) finish_column(c, woff + nw, err);
   }
-  if (b != 0 && nr != 0) {
+  if (nwb) {
     const auto gdst = global_ptr(reinterpret_cast<uint32_t*>(c.blob + c.words_off) + 2 * woff);
     const uint64_t cap_w32 = c.cap > c.words_off ? (c.cap - c.words_off) / 4 : 0;
     const uint64_t avail = cap_w32 > 2 * woff ? cap_w32 - 2 * woff : 0;
     const uint64_t limit = 2 * nw < avail ? 2 * nw : avail;
-    if (b > kFusedBits) {  // wider than the buffer: from the values, in batches
-      uint32_t* gw32 = reinterpret_cast<uint32_t*>(c.blob + c.words_off) + 2 * woff;
-      if (c.dtype == 8)  // 32-bit residuals are narrower
-        pack_rounds(reinterpret_cast<const uint64_t*>(c.col) + start, len, md.base, md.theta1, 0, 0.0,
-                    0.0, b, gw32, limit, r0, r0 + nr, w32);
-      return;
-    }
     const uint64_t first = 2 * b * r0;
     const uint64_t count = first >= limit ? 0 : (limit - first < nwb ? limit - first : nwb);
     for (uint32_t q = lane; q < count; q += 64) gdst[first + q] = w32[q];
