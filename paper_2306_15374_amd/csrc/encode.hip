@@ -440,23 +440,26 @@ __device__ inline void block_minmax_i32(FitShared& sh, int32_t& mn, int32_t& mx)
 
 // The model of one partition, by the whole workgroup (identical in every
 // thread).  Partitions of at most kEncRegLen values are held in registers;
-// longer ones are streamed twice.
-template <class T>
-__device__ __attribute__((always_inline)) inline Model fit_block(FitShared& sh, const T* src, uint64_t len, bool force_constant) {
+// longer ones are streamed twice.  kKnown: at most kEncRegLen values, vmin and
+// vmax are theirs.
+template <bool kKnown, class T>
+__device__ __attribute__((always_inline)) inline Model fit_block_range(FitShared& sh, const T* src, uint64_t len, bool force_constant,
+                                                                      uint64_t vmin, uint64_t vmax) {
   const uint32_t tid = threadIdx.x;
-  const bool in_regs = len <= kEncRegLen;
+  const bool in_regs = kKnown || len <= kEncRegLen;
   const auto gsrc = global_ptr(src);
   uint64_t v[kEncRegs];
-  uint64_t vmin = ~uint64_t(0), vmax = 0;
   U128 sv{0, 0}, stv{0, 0};
   if (in_regs) {
 #pragma unroll
     for (int k = 0; k < kEncRegs; ++k) v[k] = load_clamped(src, tid + k * kEncBlock, len);
-    vmin = vmax = v[0];
+    if (!kKnown) {
+      vmin = vmax = v[0];
 #pragma unroll
-    for (int k = 1; k < kEncRegs; ++k) {
-      vmin = v[k] < vmin ? v[k] : vmin;
-      vmax = v[k] > vmax ? v[k] : vmax;
+      for (int k = 1; k < kEncRegs; ++k) {
+        vmin = v[k] < vmin ? v[k] : vmin;
+        vmax = v[k] > vmax ? v[k] : vmax;
+      }
     }
   } else {
     // streamed: range and raw sums in one pass
@@ -468,7 +471,7 @@ __device__ __attribute__((always_inline)) inline Model fit_block(FitShared& sh, 
       stv = add128(stv, mul64x64(t, x));
     }
   }
-  block_minmax_u64(sh, vmin, vmax);
+  if (!kKnown) block_minmax_u64(sh, vmin, vmax);
   const uint64_t range = vmax - vmin;
   Model md{vmin, vmin, 0.0, bitlen64(range), false, 0, range};
   if (len > 1 && !force_constant && range < (uint64_t(1) << 61)) {
@@ -514,6 +517,11 @@ __device__ __attribute__((always_inline)) inline Model fit_block(FitShared& sh, 
     choose_model(md, th, rmin, rmax);
   }
   return md;
+}
+
+template <class T>
+__device__ __attribute__((always_inline)) inline Model fit_block(FitShared& sh, const T* src, uint64_t len, bool force_constant) {
+  return fit_block_range<false>(sh, src, len, force_constant, ~uint64_t(0), 0);
 }
 
 // Six waves per SIMD (at most 80 VGPRs; 114 unconstrained): the extra
@@ -1061,7 +1069,9 @@ __device__ __attribute__((always_inline)) inline Model fit_poly(FitShared& fs, c
   const uint32_t tid = threadIdx.x;
   kind = 0;
   c2_out = c3_out = 0.0;
-  if (!force_constant && len >= 3 && len <= kEncRegLen) {
+  const bool in_regs = !force_constant && len >= 3 && len <= kEncRegLen;
+  uint64_t vmin = 0, vmax = 0;
+  if (in_regs) {
     T v[kEncRegs];
 #pragma unroll
     for (int k = 0; k < kEncRegs; ++k) v[k] = T(load_clamped(src, tid + k * kEncBlock, len));
@@ -1071,7 +1081,8 @@ __device__ __attribute__((always_inline)) inline Model fit_poly(FitShared& fs, c
       lo = v[k] < lo ? v[k] : lo;
       hi = v[k] > hi ? v[k] : hi;
     }
-    uint64_t vmin = lo, vmax = hi;
+    vmin = lo;
+    vmax = hi;
     block_minmax_u64(fs, vmin, vmax);
     if (vmax - vmin < kPolyNarrowRange) {
       uint32_t y[kEncRegs];
@@ -1083,7 +1094,13 @@ __device__ __attribute__((always_inline)) inline Model fit_poly(FitShared& fs, c
                                                   c2_out, c3_out);
     }
   }
-  Model md = fit_block(fs, src, len, force_constant);
+  // Wider: the values read again here and by the polynomials.  Kept in
+  // registers (the same loads, as far as the compiler sees: it is told that
+  // src may have changed) they cost the narrow fit an occupancy step, 6-9%.
+  asm volatile("" : "+s"(src));
+  Model md = in_regs ? fit_block_range<true>(fs, src, len, false, vmin, vmax)
+                     : fit_block(fs, src, len, force_constant);
+  asm volatile("" : "+s"(src));
   if (force_constant || len < 3 || len > kPolyMaxLen || md.range >= kPolyMaxRange) return md;
   uint64_t y[kEncRegs];
 #pragma unroll
@@ -1161,7 +1178,7 @@ __device__ inline void store_poly(const EncScratch& s, uint64_t P, uint32_t kind
   s.c3[P] = uint64_t(__double_as_longlong(c3));
 }
 
-__global__ __launch_bounds__(kEncBlock) void k_fit_poly(const EncColumn* __restrict__ cols,
+__global__ __launch_bounds__(kEncBlock, 4) void k_fit_poly(const EncColumn* __restrict__ cols,
                                                        uint64_t ncols, EncColumn single,
                                                        uint64_t nparts, EncScratch scr) {
   __shared__ FitShared fs;
