@@ -39,9 +39,10 @@ struct BatchSink {
   // polynomial predictions by forward differences (decode_range_poly) only
   // when storing alone, for the same reason
   static constexpr bool kGramWalk = kStore && !kFilter;
-  static constexpr bool kAlign = kStore && !kFilter;
+  static constexpr uint32_t kLineShare = kStore && !kFilter ? 8192 / sizeof(OutT) : 0;
   OutT* out;
   FilterSink f;
+  __device__ uint32_t phase() const { return uint32_t(reinterpret_cast<uintptr_t>(out) / sizeof(OutT)); }
   __device__ bool visit_segment(const Part& p, uint32_t t0, uint32_t t1) {
     return kStore ? true : f.visit_segment(p, t0, t1);
   }

@@ -354,6 +354,14 @@ __device__ bool decode_tile(const uint8_t* __restrict__ blob, const Header& h, u
     PieceRec* table = reinterpret_cast<PieceRec*>(stage + kWaveStageWords);
     constexpr uint32_t kSegs = piece_segs<Sink>();
     uint32_t* bitmap = stage + kWaveStageWords + kSegs * sizeof(PieceRec) / 4;
+    // Whole lines for shares of 8 KB of output and more, where the lines that
+    // two rounds share cost most: 5e7 u32 values at L = 1000 in 2^11-value
+    // shares 51.7 -> 48.0 us, u64 53.6 -> 52.3 at 2^10; in half of that the
+    // values on their own cost more than they save (59.9 -> 62.6, 61.5 ->
+    // 62.3).  Lines of the output, not of the column: 1e8 u32 values from
+    // position 13 on 137 -> 97 us, 141 by positions.
+    const uint32_t line = Sink::kLineShare != 0 && g1 - g0 >= Sink::kLineShare ? kWave - 1 : 0;
+    const uint32_t phase = uint32_t(__builtin_amdgcn_readfirstlane(int(sink.phase())));
     while (g0 < g1) {
       // lane k < kSegs: partition j0 + k, a segment of the piece if it
       // starts before g1
@@ -433,12 +441,13 @@ __device__ bool decode_tile(const uint8_t* __restrict__ blob, const Header& h, u
           const int64_t qoff = int32_t(__builtin_amdgcn_readfirstlane(r.qoff));
           const uint64_t s0 = g0 > p.start ? g0 : p.start;
           const uint64_t s1 = ge < p.start + p.len ? ge : p.start + p.len;
-          // the values before the next multiple of kWave on their own, so
-          // that the rounds after them write whole cache lines (1e8 u32 values
-          // at L = 1000: 115 -> 94 us, L = 333: 147 -> 112; L = 1024 80)
+          // The values before the next address of the output that is a
+          // multiple of kWave values on their own, so that the rounds after
+          // them write whole cache lines.
           uint64_t c = s0;
-          if (Sink::kAlign && (uint32_t(s0) & (kWave - 1))) {
-            c = (s0 | (kWave - 1)) + 1;
+          const uint32_t past = Sink::kLineShare != 0 ? (uint32_t(s0) + phase) & line : 0;
+          if (past) {
+            c = s0 + (kWave - past);
             if (c > s1) c = s1;
             decode_few(p, uint32_t(s0 - p.start), uint32_t(c - s0), qoff, stage, sink);
             if (c == s1) continue;
@@ -509,9 +518,14 @@ struct StoreSink {
   static constexpr bool kWholeTile = true;
   static constexpr bool kFlat = kFlatRuns;
   static constexpr bool kGramWalk = true;
-  static constexpr bool kAlign = true;
+  static constexpr uint32_t kLineShare = 8192 / sizeof(OutT);
   OutT* out;
   uint64_t origin;
+  // Value g lies (g + phase()) % kWave values past a multiple of kWave of
+  // them in memory.
+  __device__ uint32_t phase() const {
+    return uint32_t(reinterpret_cast<uintptr_t>(out) / sizeof(OutT)) - uint32_t(origin);
+  }
   __device__ bool visit_segment(const Part&, uint32_t, uint32_t) { return true; }
   __device__ void put(uint64_t g, uint64_t v) {
     __builtin_nontemporal_store(OutT(v), global_ptr(out + (g - origin)));
@@ -685,7 +699,8 @@ struct FilterSink {
   static constexpr bool kWholeTile = false;  // may skip segments by their model bounds
   static constexpr bool kFlat = false;
   static constexpr bool kGramWalk = false;
-  static constexpr bool kAlign = false;
+  static constexpr uint32_t kLineShare = 0;
+  __device__ uint32_t phase() const { return 0; }
   uint64_t lo, hi;
   uint64_t sum_lo, sum_hi, count;
   int prune;
