@@ -1095,7 +1095,7 @@ struct MergeState {
 //
 // Vertices per hull: sorted normal samples, one partition of 500,000 of which
 // merges with 900 short ones behind it, have 65 to 128.  Without hulls each of
-// those merges scans the whole of it: 89 ms at 64, 25 now.
+// those merges scans the whole of it: 89 ms at 64, 24 now.
 constexpr uint32_t kHullMax = 128;
 constexpr uint64_t kHullBuildMin = 128;        // shorter partitions are scanned whole
 constexpr uint64_t kHullBuildNow = 2048;       // longer ones get hulls after kSoloMerges merges
@@ -1118,8 +1118,7 @@ constexpr uint32_t kWalk = 256;                // threads of a walker, steps of 
 constexpr uint32_t kWalkWaves = kWalk / 64;
 constexpr uint32_t kHalo = 16;                 // farthest chord end of the first filter
 constexpr uint32_t kPeelCap = 640;             // points of a hull under construction
-constexpr uint32_t kHullGiveUp = 2 * kHullMax; // vertices of a part of the points: no hull
-static_assert(kHullGiveUp + kWalk <= kPeelCap, "a block fits behind a peeled list");
+static_assert(kHullMax + kWalk <= kPeelCap, "a block fits behind a hull");
 constexpr uint32_t kStageVals = 1024;          // values staged with a window, when no more
 static_assert(kWalk == uint32_t(kEncBlock), "workgroup reductions");
 
@@ -1329,7 +1328,7 @@ __device__ __attribute__((always_inline)) inline HullRegs hull_extend_t(WalkLds&
         n[side] = w.n[side];
         cur[side] = w.cur[side];
       }
-      dead = n[0] > kHullGiveUp || n[1] > kHullGiveUp;
+      dead = n[0] > kPeelCap - kWalk || n[1] > kPeelCap - kWalk;
       if (dead) break;
     }
   }
@@ -1499,19 +1498,12 @@ __device__ __attribute__((always_inline)) inline void range_scan(
   // offsets and predictions below 2^50: differences exact in binary64
   if (range < (uint64_t(1) << 32) && __dmul_rn(fabs(th), double(len)) < 0x1p50) {
     double mx = -__builtin_inf(), mn = __builtin_inf();
-    // the next kR values are loaded while these are used
-    uint64_t x[kR];
-#pragma unroll
-    for (uint32_t k = 0; k < kR; ++k) {
-      const uint64_t t = threadIdx.x + kWalk * k;
-      x[k] = load_value(src, dtype, t < len ? t : len - 1);
-    }
     for (uint64_t t0 = threadIdx.x; t0 < len; t0 += kWalk * kR) {
-      uint64_t next[kR];
+      uint64_t x[kR];
 #pragma unroll
       for (uint32_t k = 0; k < kR; ++k) {
-        const uint64_t t = t0 + kWalk * (kR + k);
-        next[k] = load_value(src, dtype, t < len ? t : len - 1);
+        const uint64_t t = t0 + kWalk * k;
+        x[k] = load_value(src, dtype, t < len ? t : len - 1);
       }
 #pragma unroll
       for (uint32_t k = 0; k < kR; ++k) {
@@ -1520,7 +1512,6 @@ __device__ __attribute__((always_inline)) inline void range_scan(
         const double r = double(uint32_t(x[k] - vmin)) - floor(__dmul_rn(th, tt));
         mx = fmax(mx, r);
         mn = fmin(mn, r);
-        x[k] = next[k];
       }
     }
     g.maxmin(mx, mn);
