@@ -1060,13 +1060,6 @@ __device__ inline uint64_t shfl_up64(uint64_t x, int d) {
   return uint64_t(__shfl_up(static_cast<unsigned long long>(x), d, 64));
 }
 
-// Lane k's value of x, k uniform across the wavefront.
-__device__ inline uint64_t readlane64(uint64_t x, uint32_t k) {
-  const uint32_t lo = uint32_t(__builtin_amdgcn_readlane(int(uint32_t(x)), int(k)));
-  const uint32_t hi = uint32_t(__builtin_amdgcn_readlane(int(uint32_t(x >> 32)), int(k)));
-  return (uint64_t(hi) << 32) | lo;
-}
-
 // The summary of [x, z) from those of [x, y) and [y, z).
 __device__ inline RangeSum join(const RangeSum& a, const RangeSum& b, uint64_t a_len) {
   RangeSum r;
@@ -1116,7 +1109,6 @@ struct ChainHull {  // side 0: upper, side 1: lower
 
 constexpr uint32_t kWalk = 256;                // threads of a walker, steps of a batch
 constexpr uint32_t kWalkWaves = kWalk / 64;
-constexpr uint32_t kHalo = 16;                 // farthest chord end of the first filter
 constexpr uint32_t kPeelCap = 640;             // points of a hull under construction
 static_assert(kHullMax + kWalk <= kPeelCap, "a block fits behind a hull");
 constexpr uint32_t kStageVals = 1024;          // values staged with a window, when no more
@@ -2029,8 +2021,8 @@ __global__ void k_pair_reuse(uint64_t m, const uint8_t* __restrict__ changed,
 
 namespace {
 
-// Device buffers of one call, freed on every exit path.
-// Device arrays of one call, of one allocation for each commit.
+// Device arrays of one call, one allocation for each commit, freed on every
+// exit path.
 struct Buffers {
   std::vector<std::pair<void**, size_t>> wanted;
   std::vector<void*> ptrs;
