@@ -1419,7 +1419,8 @@ __device__ __attribute__((always_inline)) inline void pack_batch(
   wave_fence();
 }
 
-template <class T>
+// kTails: the last rounds in the smallest batch that holds them.
+template <bool kTails, class T>
 __device__ __attribute__((always_inline)) inline void pack_rounds(const T* src, uint64_t len, uint64_t base, double theta1,
                                    uint32_t kind, double c2, double c3, uint32_t b,
                                    uint32_t* gw32, uint64_t limit, uint64_t k_begin,
@@ -1427,11 +1428,10 @@ __device__ __attribute__((always_inline)) inline void pack_rounds(const T* src, 
   const bool fits32 = prediction_fits_i32(theta1, len);
   const auto gdst = global_ptr(gw32);
   uint64_t k0 = k_begin;
-  for (; k0 + kPackBatch / 2 < k_end; k0 += kPackBatch)
+  for (; k0 + (kTails ? kPackBatch / 2 : 0) < k_end; k0 += kPackBatch)
     pack_batch<kPackBatch>(src, len, base, theta1, fits32, kind, c2, c3, b, gdst, limit, k0,
                            uint32_t(k_end - k0 < kPackBatch ? k_end - k0 : kPackBatch), w32);
-  if (k0 >= k_end) return;
-  // the rest, in the smallest batch that holds it
+  if (!kTails || k0 >= k_end) return;
   const uint32_t nr = uint32_t(k_end - k0);
   if (nr > 2)
     pack_batch<4>(src, len, base, theta1, fits32, kind, c2, c3, b, gdst, limit, k0, nr, w32);
@@ -1444,9 +1444,10 @@ __device__ __attribute__((always_inline)) inline void pack_rounds(const T* src, 
 // One wavefront per partition (kWave, four per workgroup), or one workgroup
 // per partition whose four wavefronts take consecutive quarters of its
 // rounds (each a whole number of batches).  Five waves per SIMD, as
-// the fit had (95 VGPRs instead of 105; 4 spilled per wavefront-partition
-// kernel since its last batch has sizes of its own).
-template <bool kWave>
+// the fit had (95 VGPRs instead of 105).  kTails: a smaller last batch, whose
+// code beside the full batches' spills 4 registers instead of 2 (2e8 u64
+// values at L 1024 335 us with, 324 without).
+template <bool kWave, bool kTails>
 __global__ __launch_bounds__(kEncBlock) __attribute__((amdgpu_waves_per_eu(5))) void k_pack(
     const EncColumn* __restrict__ cols, uint64_t ncols, EncColumn single, uint64_t nparts,
     EncScratch scr) {
@@ -1482,10 +1483,10 @@ __global__ __launch_bounds__(kEncBlock) __attribute__((amdgpu_waves_per_eu(5))) 
     c3 = __longlong_as_double(static_cast<long long>(meta_load(scr.c3, P)));
   }
   if (c.dtype == 8)
-    pack_rounds(reinterpret_cast<const uint64_t*>(c.col) + start, len, base, theta1, kind, c2, c3,
+    pack_rounds<kTails>(reinterpret_cast<const uint64_t*>(c.col) + start, len, base, theta1, kind, c2, c3,
                 b, gw32, limit, k_begin, k_end, lds[wave]);
   else
-    pack_rounds(reinterpret_cast<const uint32_t*>(c.col) + start, len, base, theta1, kind, c2, c3,
+    pack_rounds<kTails>(reinterpret_cast<const uint32_t*>(c.col) + start, len, base, theta1, kind, c2, c3,
                 b, gw32, limit, k_begin, k_end, lds[wave]);
 }
 
@@ -2235,16 +2236,25 @@ hipError_t launch_encode_columns(leco_ctx* ctx, const EncColumn* cols_dev, uint6
   // values: 605 and 374, 317 and 225, 188 and 153).
   const uint64_t per = single.fixed_len ? kPackShortValues / single.fixed_len : 0;
   const uint64_t waves = uint64_t(ctx->num_cus) * (single.fixed_len <= 128 ? 4 : 16);
+  // Two whole batches of rounds to a partition of 8-byte values: without the
+  // code of smaller ones (2e8 values 635-640 -> 613 us, 1e8 within noise).
+  // u32 values (426 -> 437), one batch (u64 L 512 359 -> 368) and partly filled
+  // ones (L 800 336 -> 344) are better with it.
+  const uint64_t rounds = (single.fixed_len + 63) / 64;
+  const bool tails = cols_dev != nullptr || single.dtype != 8 || rounds <= kPackBatch || rounds % kPackBatch != 0;
   if (wave && cols_dev == nullptr && single.fixed_len >= kPackShortMin &&
       single.fixed_len <= kPackShortMax && nparts >= per * waves)
     hipLaunchKernelGGL(k_pack_short, dim3(uint32_t((nparts + per * kEncWaves - 1) / (per * kEncWaves))),
                        dim3(kEncBlock), 0, stream, single, nparts, uint32_t(per),
                        uint32_t((1u << 20) / single.fixed_len + 1), scr);
+  else if (wave && tails)
+    hipLaunchKernelGGL((k_pack<true, true>), dim3(uint32_t(pw)), dim3(kEncBlock), 0, stream, cols_dev,
+                       ncols, single, nparts, scr);
   else if (wave)
-    hipLaunchKernelGGL(k_pack<true>, dim3(uint32_t(pw)), dim3(kEncBlock), 0, stream, cols_dev,
+    hipLaunchKernelGGL((k_pack<true, false>), dim3(uint32_t(pw)), dim3(kEncBlock), 0, stream, cols_dev,
                        ncols, single, nparts, scr);
   else
-    hipLaunchKernelGGL(k_pack<false>, dim3(uint32_t(nparts)), dim3(kEncBlock), 0, stream, cols_dev,
+    hipLaunchKernelGGL((k_pack<false, true>), dim3(uint32_t(nparts)), dim3(kEncBlock), 0, stream, cols_dev,
                        ncols, single, nparts, scr);
   return hipGetLastError();
 }
