@@ -1,5 +1,5 @@
-// LeCo encoder for gfx950 (section 3.1 regressor, section 3.3 encoder), in
-// two passes over the input that need no ordering between partitions:
+// LeCo encoder for gfx950 (section 3.1 regressor, section 3.3 encoder).  Every
+// encode fits, lays out and packs:
 //
 //   fit    every partition's model: range, exact least-squares sums, slope,
 //          residual range, the choice between the line and the constant
@@ -7,17 +7,25 @@
 //          the minimax regressor also the minimax line (k_fit_minimax*,
 //          minimax.hpp), with the polynomial regressor the degree-2 and
 //          degree-3 polynomials (k_fit_poly*);
-//   scan   the exclusive prefix of the word counts gives every partition's
+//   layout the exclusive prefix of the word counts gives every partition's
 //          word offset; the records, starts, header and padding are written;
-//   pack   every partition's residuals, recomputed from its stored model,
-//          are bit-packed into its word span (section 3.3 storage format).
+//   pack   every partition's residuals are bit-packed into its word span
+//          (section 3.3 storage format).
+//
+// In two passes these are kernels of their own: no partition waits on another,
+// and the packing reads the column a second time and recomputes the residuals
+// from the stored models.  In one pass (k_encode_fused*, least squares) a
+// partition's values stay in registers from the fit to the packing, and its
+// word offset comes from a look-back over the counts that the partitions
+// before it have published.  launch_encode_columns takes one pass for small
+// launches, where launches and latency count, and for 8-byte columns whose
+// partitions nearly fill a workgroup's registers.  Both work on a table of
+// columns, so one sequence of launches encodes one column or thousands.
 //
 // The fits take one wavefront per partition when every partition holds at
-// most kWaveEncodeMax values (16 per lane) or twice that (32 per lane):
-// values in registers, shuffle reductions, no workgroup barrier.  Longer
-// partitions get a whole workgroup.  Works on a table of columns, so one
-// sequence of launches encodes one column or thousands.  The column is read twice; in
-// exchange no partition waits on another.
+// most kWaveEncodeMax values (2 to 16 per lane, by the partition's length) or
+// twice that (32 per lane): values in registers, reductions by lane
+// permutations, no workgroup barrier.  Longer partitions get a whole workgroup.
 //
 // Register-resident partitions whose range is below 2^30 (the usual case)
 // fit on a narrow path: y = v - vmin fits 32 bits, the exact sums fit 64-bit
@@ -909,11 +917,11 @@ __device__ inline uint64_t uniform64(uint64_t x) {
 //   residuals  y and every |floor| are below 2^52, so their differences and
 //              extremes are exact in binary64, line, degree 2 and degree 3
 //              side by side (25 instructions a value).
-// Bound by vector issue: 1260 vector instructions a wavefront of 1000 values,
-// 205 of the kernel's 270 us for 1e8.  Against integer sums and residuals in
-// three passes, encode of 1e8 values: two sines u32 L 1000 575 -> 427 us,
-// sorted keys u64 L 1000 590 -> 440, cubic blocks u64 L 2000 568 -> 484 and
-// L 4096 (a workgroup each) 692 -> 458.
+// Bound by vector issue: 1170 vector instructions a wavefront of 1000 values,
+// 190 of the kernel's 235 us for 1e8.  Against integer sums and residuals in
+// three passes, encode of 1e8 values: two sines u32 L 1000 586 -> 412 us,
+// sorted keys u64 L 1000 620 -> 448, cubic blocks u64 L 2000 577 -> 415 and
+// L 4096 (a workgroup each) 716 -> 474.
 template <int kT, int kR, class Group>
 __device__ __attribute__((always_inline)) inline Model fit_poly_narrow(
     const uint32_t (&y0)[kR], uint32_t tid, uint32_t n, uint64_t vmin, uint64_t range, Group& group,
@@ -2181,7 +2189,11 @@ hipError_t launch_encode_columns(leco_ctx* ctx, const EncColumn* cols_dev, uint6
                              max_len <= kWaveEncMax && fused(ctx->tune.encode_fused_wave, pw, kFusedWavePerCu);
   // One read of the column instead of two pays where the workgroups' registers
   // are full: 1e8 u64 values in partitions of 4096 288 us for 333, of 4000 305
-  // for 332, of 3500 340 for 323; u32 values 250 for 229.
+  // for 332, of 3500 340 for 323; u32 values 250 for 229.  Whatever they span:
+  // 5e7 values in 4096s of range 2^40 231 us for 338, full-width ones 202 for
+  // 243.  Of tables and variable starts the host knows only the longest
+  // partition, not how many are as full: two passes (1e8 values in 512 columns
+  // of 4096s 389 us, 294 in one pass, and in variable ones 350 and 312).
   const bool full = cols_dev == nullptr && single.dtype == 8 && single.fixed_len > kFusedFullLen;
   const bool one_pass = nparts != 0 && regs == kRegLS && !one_pass_wave &&
                         max_len <= kEncRegLen && !(wave_fit && ctx->tune.encode_wave) &&

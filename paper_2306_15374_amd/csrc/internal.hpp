@@ -40,8 +40,9 @@ constexpr uint32_t kFusedWavePerCu = 2;
 constexpr uint32_t kFusedPerCu = 4;
 
 // Reads LECO_TILE_LOG2, LECO_DECODE_BLOCKS_PER_CU, LECO_XCD_REMAP,
-// LECO_RA_LPT, LECO_ENCODE_WAVE, LECO_ENCODE_WAVE32, LECO_ENCODE_FUSED and
-// LECO_ENCODE_FUSED_WAVE overrides from the environment.
+// LECO_RA_LPT, LECO_ENCODE_WAVE, LECO_ENCODE_WAVE32, LECO_ENCODE_FUSED,
+// LECO_ENCODE_FUSED_WAVE and LECO_LOOKBACK_POLLS overrides from the
+// environment.
 void tune_from_env(Tune& t);
 
 // One column for the encoder: input, partitioning, output blob.  A table of

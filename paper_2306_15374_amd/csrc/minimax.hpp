@@ -29,10 +29,12 @@
 //
 // This replaced convex hulls (per-thread chains of 16 points merged pairwise
 // in LDS, every hull edge tested).  Encode of 1e8 values, before -> now: noisy
-// line u32 L 1024 1.69 -> 0.36 ms, sorted keys u64 L 2000 3.63 -> 0.39, L 4096
-// 2.12 -> 0.45 and L 10,000 (streamed) 3.74 -> 0.76.  The register-held
-// passes are bound by vector issue (64 binary64 instructions a pass and
-// lane, about 40 more for the reduction).
+// line u32 L 1024 1.69 -> 0.30 ms, sorted keys u64 L 2000 3.66 -> 0.37, L 4096
+// 2.14 -> 0.45 and L 10,000 (streamed) 3.76 -> 0.76; 2e7 u64 values in 4096s of
+// range 2^29 to 2^40 (read again in every pass) 0.50 -> 0.15 to 0.17.  The
+// register-held passes are bound by vector issue (64 binary64 instructions a
+// pass and lane, about 40 more for the reduction): 1210 instructions a
+// partition of 1024 values, 193 of the kernel's 215 us for 1e8.
 #pragma once
 
 #include "fit.hpp"

@@ -36,7 +36,9 @@
 //
 // What bounds a column whose runs are long (a noisy polyline of 1e7 values:
 // partitions of two values merged into partitions of up to 370,000) is the
-// latency of the batches along its longest run: 256 steps in about 8 us.  With
+// latency of the batches along its longest run, one chunk per round: a walker
+// takes 33 us for 256 steps by itself and 50 to 60 where every second CU has
+// one, and a round lasts as long as its slowest (112 rounds of 350 us).  With
 // one wavefront, 64 steps a batch, every added value broadcast to all lanes
 // and the hulls kept by a serial chain it was 60 us for 64, and short chunks
 // re-walked most of the column in every round: 512 -> 48 ms (in order: hulls
@@ -168,7 +170,6 @@ __device__ inline uint32_t split_ahead(const uint64_t* win, uint64_t p, uint64_t
   int32_t w_old = 0;
   uint64_t prev = win[reach ? lane : 0];  // lanes past b read nothing past it
   K mn = make_key(static_cast<K*>(nullptr), 0, 0), mx = mn;
-#pragma unroll 2
   for (uint32_t k = 1; k <= kSplitAhead; ++k) {
     const bool on = next == 0 && k <= reach;
     if (__ballot(on) == 0) break;
@@ -2058,8 +2059,7 @@ constexpr uint64_t kRoundGrid = 1024;  // workgroups of a round that works off a
 // walked again in each round until its run is the right one, so long chunks
 // save work (256 boundaries made a thousand walkers re-walk 20,000 chunks 93
 // times each), as long as there is a walker for every CU: about a thousand
-// chunks of 1024 (four batches, 40 us: below, a round costs its launch) to
-// 4096 boundaries.  Partitions that are sized one at a time (kSoloMin) take
+// chunks of 1024 (four batches, 130 us by itself) to 4096 boundaries.  Partitions that are sized one at a time (kSoloMin) take
 // as long each as a batch of short ones: 16 per chunk.
 uint32_t chunk_log2(uint64_t m, uint64_t n) {
   if (n / m > leco::kSoloMin) return 4;
