@@ -37,8 +37,8 @@
 // What bounds a column whose runs are long (a noisy polyline of 1e7 values:
 // partitions of two values merged into partitions of up to 370,000) is the
 // latency of the batches along its longest run, one chunk per round: a walker
-// takes 33 us for 256 steps by itself and 50 to 60 where every second CU has
-// one, and a round lasts as long as its slowest (112 rounds of 350 us).  With
+// takes 20 to 33 us for 256 steps and 50 to 60 where every second CU has one,
+// and a round lasts as long as its slowest (58 rounds, 28 ms).  With
 // one wavefront, 64 steps a batch, every added value broadcast to all lanes
 // and the hulls kept by a serial chain it was 60 us for 64, and short chunks
 // re-walked most of the column in every round: 512 -> 48 ms (in order: hulls
